@@ -168,29 +168,33 @@ void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift) {
     g.rank = cv.take<uint32_t>(N);
     g.perm = cv.take<int32_t>(N);
     g.inv = cv.take<int32_t>(N);
-    g.qs = cv.take<uint64_t>(N);
+    g.pts = cv.take<float4>(N);
+    g.qs = reinterpret_cast<uint64_t*>(g.pts);
     g.redo = cv.take<uint32_t>(N);
     g.nredo = cv.take<uint32_t>(64);
 }
 
 // quantise, count, scan, scatter.  rec may be NULL; with recp the records are
 // packed in path order first and gathered into the sorted order.
-hipError_t run_grid(const pg_paths* p, GridBufs& g, VRec* rec, hipStream_t s, VRec* recp) {
+hipError_t run_grid(const pg_paths* p, GridBufs& g, GridFor use, VRec* rec, hipStream_t s, VRec* recp) {
     const int64_t N = p->n_vertices;
     hipError_t e;
     if ((e = launch_fill(g.flag, 64 * sizeof(int32_t), s)) != hipSuccess) return e;
     if ((e = launch_fill(g.cells, (size_t)(g.ncells + 1) * 4, s)) != hipSuccess) return e;
     if ((e = launch_quantize_count(N, p->pos, g.shift, g.cells, g.cellid, g.rank, g.flag, s)) != hipSuccess) return e;
     if ((e = launch_scan_exclusive(g.cells, g.cells, g.ncells, g.partials, s)) != hipSuccess) return e;
-    if ((e = launch_cell_range(g.ncells, g.shift, g.cells, g.range, s)) != hipSuccess) return e;
+    const bool knn = use == GridFor::kNeighbours;
+    uint64_t* qs = knn ? nullptr : g.qs;
+    float4* pts = knn ? g.pts : nullptr;
+    if (knn && (e = launch_cell_range(g.ncells, g.shift, g.cells, g.range, s)) != hipSuccess) return e;
     if (rec && recp) {
         if ((e = launch_pack_records(N, *p, recp, g.flag, s)) != hipSuccess) return e;
-        if ((e = launch_scatter(N, *p, g.shift, g.cellid, g.rank, g.cells, g.perm, g.inv, g.qs, nullptr, s)) !=
-            hipSuccess)
+        if ((e = launch_scatter(N, *p, g.shift, g.cellid, g.rank, g.cells, g.perm, g.inv, qs, pts, nullptr,
+                                s)) != hipSuccess)
             return e;
         return launch_gather_records(N, g.perm, recp, rec, s);
     }
-    return launch_scatter(N, *p, g.shift, g.cellid, g.rank, g.cells, g.perm, g.inv, g.qs, rec, s);
+    return launch_scatter(N, *p, g.shift, g.cellid, g.rank, g.cells, g.perm, g.inv, qs, pts, rec, s);
 }
 
 int shift_of(const pg_params* q, int64_t N) { return q && q->cell_shift ? q->cell_shift : default_shift(N); }
@@ -294,8 +298,8 @@ pg_status pg_knn(const pg_paths* paths, int32_t k, int32_t cell_shift, int64_t* 
         if ((e = launch_fill(row_ptr, sizeof(int64_t), s)) != hipSuccess) return hip_fail(e, "fill");
         return finish(s, nullptr, nullptr, 0);
     }
-    if ((e = run_grid(paths, g, nullptr, s)) != hipSuccess) return hip_fail(e, "grid build");
-    e = launch_knn(N, K, shift, g.qs, g.perm, g.inv, g.range, nullptr, col, row_ptr, g.redo, g.nredo, false, s);
+    if ((e = run_grid(paths, g, GridFor::kNeighbours, nullptr, s)) != hipSuccess) return hip_fail(e, "grid build");
+    e = launch_knn(N, K, shift, g.pts, g.inv, g.range, nullptr, col, row_ptr, g.redo, g.nredo, false, s);
     if (e != hipSuccess) return hip_fail(e, "knn");
     return finish(s, nullptr, g.flag, 0);
 }
@@ -409,7 +413,7 @@ pg_status pg_clusters(const pg_paths* paths, int32_t k, int32_t cell_shift, int3
     carve_clusters(cv, cb, N, k);
     if (N == 0) return finish(s, nullptr, nullptr, 0);
     hipError_t e;
-    if ((e = run_grid(paths, g, nullptr, s)) != hipSuccess) return hip_fail(e, "grid build");
+    if ((e = run_grid(paths, g, GridFor::kClusters, nullptr, s)) != hipSuccess) return hip_fail(e, "grid build");
     if ((e = run_clusters(paths, g, cb, s)) != hipSuccess) return hip_fail(e, "clusters");
     if ((e = launch_centre_out(N, g, cb, centre, s)) != hipSuccess) return hip_fail(e, "centre output");
     return finish(s, nullptr, g.flag, PG_FLAG_CHECK);

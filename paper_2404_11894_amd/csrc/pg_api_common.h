@@ -75,19 +75,23 @@ struct GridBufs {
     int64_t ncells = 0;
     int32_t* flag = nullptr;
     uint32_t* cells = nullptr;     // counts, then start by Hilbert position (ncells + 1)
-    uint2* range = nullptr;        // [start, end) of each cell by Morton number (ncells)
+    uint2* range = nullptr;        // [start, end) of each cell, row-major (ncells; kNN only)
     uint32_t* partials = nullptr;
     uint32_t* cellid = nullptr;
     uint32_t* rank = nullptr;
     int32_t* perm = nullptr;       // sorted -> path order
     int32_t* inv = nullptr;        // path order -> sorted
-    uint64_t* qs = nullptr;        // sorted packed quantised positions
+    float4* pts = nullptr;         // kNN: sorted quantised positions, path id in w (its bits)
+    uint64_t* qs = nullptr;        // clusters: sorted packed quantised positions (the same memory)
     uint32_t* redo = nullptr;      // kNN queries handed to the exact search
     uint32_t* nredo = nullptr;
 };
 
 void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift);
-hipError_t run_grid(const pg_paths* p, GridBufs& g, VRec* rec, hipStream_t s, VRec* recp = nullptr);
+// What the grid is built for: the neighbour search (points and cell ranges) or
+// the cluster relation (packed positions).
+enum class GridFor { kNeighbours, kClusters };
+hipError_t run_grid(const pg_paths* p, GridBufs& g, GridFor use, VRec* rec, hipStream_t s, VRec* recp = nullptr);
 hipError_t launch_gather_records(int64_t N, const int32_t* perm, const VRec* recp, VRec* rec, hipStream_t s);
 
 // The cluster neighbour relation (pg_clusters.hip).  Arrays indexed by a

@@ -1215,7 +1215,7 @@ hipError_t cluster_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, c
     ClusterRender& cr = r.cr;
     {
         ProfScope ps(s, "grid");
-        PG_TRY(run_grid(p, g, r.rec, s));
+        PG_TRY(run_grid(p, g, GridFor::kClusters, r.rec, s));
     }
     PG_TRY(run_clusters(p, g, cb, s));
     const Consts c = make_consts(q, r.K);

@@ -9,9 +9,9 @@
 // Grid: cell = q >> shift per axis, G = 2^(20-shift) cells per axis.  The
 // vertices are sorted by the position of their cell along the Hilbert curve,
 // so neighbouring cells are close in memory (the gathers of the kNN, the
-// edge weights and every propagation step stay in a small window); a table
-// indexed by the cell's Morton number gives each cell's [start, end) in that
-// order without re-encoding during the search.  Counting sort = atomic
+// edge weights and every propagation step stay in a small window); a row-major
+// table gives each cell's [start, end) in that order without re-encoding during
+// the search.  Counting sort = atomic
 // histogram (which also yields each vertex's rank inside its cell) +
 // exclusive scan + scatter.  The order of vertices inside a cell is not
 // deterministic; nothing downstream depends on it (every comparison breaks
@@ -48,14 +48,16 @@ hipError_t launch_quantize_count(int64_t N, const float* pos, int shift, uint32_
     return hipGetLastError();
 }
 
-// range[m] = [start, end) of the cell with Morton number m, from the
-// exclusive scan `start` of the counts in Hilbert order.
+// range[(z G + y) G + x] = [start, end) of cell (x, y, z), from the exclusive
+// scan `start` of the counts in Hilbert order.  Row-major, so that the search
+// reaches the cell at a wave-uniform offset with one scalar add.
 __global__ __launch_bounds__(kBlock) void k_cell_range(int64_t ncells, int shift, const uint32_t* __restrict__ start,
                                                        uint2* __restrict__ range) {
     const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= ncells) return;
-    const uint32_t u = (uint32_t)m;
-    const uint32_t h = hilbert3(compact1by2(u), compact1by2(u >> 1), compact1by2(u >> 2), kQBits - shift);
+    const int lg = kQBits - shift;
+    const uint32_t u = (uint32_t)m, mask = (1u << lg) - 1u;
+    const uint32_t h = hilbert3(u & mask, (u >> lg) & mask, u >> (2 * lg), lg);
     range[m] = make_uint2(start[h], start[h + 1]);
 }
 
@@ -213,14 +215,17 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P, int s
                                                     const uint32_t* __restrict__ rank,
                                                     const uint32_t* __restrict__ cell_start,
                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv,
-                                                    uint64_t* __restrict__ qsorted, VRec* __restrict__ rec) {
+                                                    uint64_t* __restrict__ qsorted, float4* __restrict__ pts,
+                                                    VRec* __restrict__ rec) {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= N) return;
     (void)shift;
     int64_t s = (int64_t)cell_start[cellid[v]] + rank[v];
     perm[s] = (int32_t)v;
     inv[v] = (int32_t)s;
-    qsorted[s] = qpack(quant(P.pos[3 * v]), quant(P.pos[3 * v + 1]), quant(P.pos[3 * v + 2]));
+    const uint32_t qx = quant(P.pos[3 * v]), qy = quant(P.pos[3 * v + 1]), qz = quant(P.pos[3 * v + 2]);
+    if (qsorted) qsorted[s] = qpack(qx, qy, qz);
+    if (pts) pts[s] = make_float4((float)qx, (float)qy, (float)qz, __int_as_float((int32_t)v));   // exact: below 2^24
     if (rec) {
         VRec r;
         fill_record(P, v, r);
@@ -230,10 +235,10 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P, int s
 
 hipError_t launch_scatter(int64_t N, const pg_paths& paths, int shift, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
-                          uint64_t* qsorted, VRec* rec, hipStream_t s) {
+                          uint64_t* qsorted, float4* pts, VRec* rec, hipStream_t s) {
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, paths, shift, cellid,
-                       rank, cell_start, perm, inv, qsorted, rec);
+                       rank, cell_start, perm, inv, qsorted, pts, rec);
     return hipGetLastError();
 }
 
@@ -297,10 +302,10 @@ hipError_t launch_pack_records(int64_t N, const pg_paths& paths, VRec* rec, int3
 // sorted ascending by (d2, id) and right-aligned in an array of KM slots; the
 // KM-(K-1) leading slots hold (0, 0), which no candidate can move past, so the
 // current worst is always slot KM-1 and every index is a compile-time
-// constant.  Cells are searched in Chebyshev shells r = 0, 1, 2, ...; after a
-// shell every unvisited vertex is at least `gap` quantisation steps away on
-// some axis, so the search stops once the worst kept distance is < gap^2 (a
-// candidate at exactly gap could still win on a smaller id).
+// constant.  Cells are searched in Chebyshev shells; after the shells up to r
+// every unvisited vertex is at least `gap` quantisation steps away on some axis,
+// so the search stops once the worst kept distance is < gap^2 (a candidate at
+// exactly gap could still win on a smaller id).
 
 __device__ inline bool key_less(uint64_t d1, uint32_t o1, uint64_t d2, uint32_t o2) {
     return d1 < d2 || (d1 == d2 && o1 < o2);
@@ -339,13 +344,11 @@ __device__ __forceinline__ void list_reset(uint64_t (&d)[KM], uint32_t (&o)[KM],
 // cell whose box is farther from q than the current (K-1)-th distance cannot
 // contribute and is skipped without reading it (only once the list is full:
 // before that the worst key is (inf, inf)); a cell at exactly that distance is
-// still read, since a tie may win on id.  Candidates are loaded two at a time.
+// still read, since a tie may win on id.
 template <int KM>
-__device__ __forceinline__ void shell_search(int64_t s, int m, int shift, int32_t qx, int32_t qy, int32_t qz,
-                                             const uint64_t* __restrict__ qs, const int32_t* __restrict__ perm,
-                                             const uint2* __restrict__ cell_range, uint64_t (&d)[KM],
-                                             uint32_t (&o)[KM]) {
-    (void)m;
+__device__ __forceinline__ void shell_search(int64_t s, int shift, int32_t qx, int32_t qy, int32_t qz,
+                                             const float4* __restrict__ pts, const uint2* __restrict__ cell_range,
+                                             uint64_t (&d)[KM], uint32_t (&o)[KM]) {
     const int G = 1 << (kQBits - shift);
     const int cx = qx >> shift, cy = qy >> shift, cz = qz >> shift;
     const int64_t cs = (int64_t)1 << shift;
@@ -365,30 +368,12 @@ __device__ __forceinline__ void shell_search(int64_t s, int m, int shift, int32_
                     if (x < 0 || x >= G) continue;
                     const int64_t gx = dx < 0 ? (int64_t)qx - ((int64_t)(x + 1) * cs - 1) : (dx > 0 ? (int64_t)x * cs - qx : 0);
                     if ((uint64_t)(gx * gx + gy * gy + gz * gz) > d[KM - 1]) continue;   // whole cell too far
-                    const uint32_t cell = morton3((uint32_t)x, (uint32_t)y, (uint32_t)z);
-                    const uint2 cr = cell_range[cell];
-                    const uint32_t beg = cr.x, end = cr.y;
-                    uint32_t t = beg;
-                    for (; t + 1 < end; t += 2) {
-                        const uint64_t p0 = qs[t], p1 = qs[t + 1];
-                        const uint32_t o0 = (uint32_t)perm[t], o1 = (uint32_t)perm[t + 1];
-                        int32_t ax, ay, az;
-                        if ((int64_t)t != s) {
-                            qunpack(p0, ax, ay, az);
-                            const int64_t ex = ax - qx, ey = ay - qy, ez = az - qz;
-                            list_insert<KM>(d, o, (uint64_t)(ex * ex + ey * ey + ez * ez), o0);
-                        }
-                        if ((int64_t)t + 1 != s) {
-                            qunpack(p1, ax, ay, az);
-                            const int64_t ex = ax - qx, ey = ay - qy, ez = az - qz;
-                            list_insert<KM>(d, o, (uint64_t)(ex * ex + ey * ey + ez * ez), o1);
-                        }
-                    }
-                    if (t < end && (int64_t)t != s) {
-                        int32_t ax, ay, az;
-                        qunpack(qs[t], ax, ay, az);
-                        const int64_t ex = ax - qx, ey = ay - qy, ez = az - qz;
-                        list_insert<KM>(d, o, (uint64_t)(ex * ex + ey * ey + ez * ez), (uint32_t)perm[t]);
+                    const uint2 cr = cell_range[((uint32_t)z * (uint32_t)G + (uint32_t)y) * (uint32_t)G + (uint32_t)x];
+                    for (uint32_t t = cr.x; t < cr.y; ++t) {
+                        if ((int64_t)t == s) continue;
+                        const float4 p = pts[t];
+                        const int64_t ex = (int32_t)p.x - qx, ey = (int32_t)p.y - qy, ez = (int32_t)p.z - qz;
+                        list_insert<KM>(d, o, (uint64_t)(ex * ex + ey * ey + ez * ez), __float_as_uint(p.w));
                     }
                 }
             }
@@ -442,135 +427,275 @@ __device__ __forceinline__ void knn_write(int64_t s, int K, int m, uint32_t self
 struct KeyFmt {
     int idb;
     uint64_t sat, idmask;
+    double satd;   // sat where it can bind (d2 < 2^42), else larger than any d2
 };
 
 inline KeyFmt key_fmt(int64_t N) {
     int idb = 1;
     while (idb < 31 && ((int64_t)1 << idb) < N) ++idb;
-    return KeyFmt{idb, (~0ull) >> idb, ((uint64_t)1 << idb) - 1};
+    const uint64_t sat = (~0ull) >> idb;
+    return KeyFmt{idb, sat, ((uint64_t)1 << idb) - 1, sat < (1ull << 50) ? (double)sat : 1e18};
 }
 
-__device__ __forceinline__ uint64_t make_key(uint64_t d2, uint32_t oid, const KeyFmt& f) {
-    return ((d2 < f.sat ? d2 : f.sat) << f.idb) | (uint64_t)oid;
+// The exact key of a candidate at (dx, dy, dz) quantisation steps from the
+// query.  The differences are whole numbers below 2^21, so the double-precision
+// sum of squares is exact, and adding 2^52 leaves it in the mantissa's low bits.
+__device__ __forceinline__ uint64_t make_key(float dx, float dy, float dz, uint32_t id, const KeyFmt& f) {
+    const double x = dx, y = dy, z = dz;
+    const double d2 = fmin(fma(x, x, fma(y, y, z * z)), f.satd);
+    const uint64_t u = (uint64_t)__double_as_longlong(d2 + 4503599627370496.0) & 0x000fffffffffffffull;
+    return (u << f.idb) | (uint64_t)id;
 }
 
-// Insert c into the ascending list if it beats the last key, as a merge: slot
-// p keeps its key if c is not below it, takes c if c falls between slots p-1
-// and p, and the key of slot p-1 otherwise.  The comparisons against c are
-// independent of each other (a bubble pass would chain them), and each slot
-// costs one 64-bit compare and two selects.
+// Insert c into the ascending list (unchanged if c is not below the last key),
+// as a merge: slot p keeps its key if c is not below it, takes c if c falls
+// between slots p-1 and p, and the key of slot p-1 otherwise.  The comparisons
+// against c are independent of each other (a bubble pass would chain them), and
+// each slot costs one 64-bit compare and two selects.
 template <int KM>
 __device__ __forceinline__ void key_insert(uint64_t (&k)[KM], uint64_t c) {
-    if (c < k[KM - 1]) {
-        bool lt[KM];
-        uint64_t v[KM];
+    bool lt[KM];
+    uint64_t v[KM];
 #pragma unroll
-        for (int p = 0; p < KM; ++p) {
-            lt[p] = c < k[p];
-            // an empty asm hides that v[p] equals k[p]: the selects below then
-            // reuse lt[] instead of being rebuilt as min/max with compares of their own
-            v[p] = k[p];
-            asm("" : "+v"(v[p]));
-        }
-#pragma unroll
-        for (int p = KM - 1; p > 0; --p) k[p] = lt[p] ? (lt[p - 1] ? v[p - 1] : c) : v[p];
-        k[0] = lt[0] ? c : v[0];
+    for (int p = 0; p < KM; ++p) {
+        lt[p] = c < k[p];
+        // an empty asm hides that v[p] equals k[p]: the selects below then
+        // reuse lt[] instead of being rebuilt as min/max with compares of their own
+        v[p] = k[p];
+        asm("" : "+v"(v[p]));
     }
+#pragma unroll
+    for (int p = KM - 1; p > 0; --p) k[p] = lt[p] ? (lt[p - 1] ? v[p - 1] : c) : v[p];
+    k[0] = lt[0] ? c : v[0];
 }
 
-// The list is seeded with the kKnnWin vertices on either side of the query in
-// cell order (the same trip count on every lane, loads coalesced across the
-// wave), which gives the shells a tight bound to prune cells with from the
-// start; the shells then skip that index range, so every vertex is offered
-// once.  Seeding with 16 on either side: kNN 5% faster on the 68.8M-vertex
-// cloud at the finest cell size, unchanged on the 22M-vertex ball.
+// The search starts from the kKnnWin vertices on either side of the query in
+// cell order (the nearer half first), which gives the shells a tight bound to
+// prune cells with from the start; the shells then skip that index range, so
+// every vertex is offered once.
 constexpr int kKnnWin = 16;
 
+// Per-lane scratch of the search, in LDS: cell ranges still to be read, and
+// candidates that passed the distance filter (positions in sorted order).
+// [entry][lane], so a wave's accesses never conflict.  8 + 8 entries are 6 KB a
+// wave, which leaves room for the 6 waves per SIMD that the registers allow:
+// 12 + 8 entries (5 waves) took 14.5 ms where these take 13.1 on 20M vertices at
+// k = 16, 6 + 8 13.5 ms.
+constexpr int kKnnRanges = 8;
+constexpr int kKnnPend = 8;
+constexpr int kKnnKeep = kKnnPend / 2;
+struct KnnScratch {
+    uint2 range[kKnnRanges][kBlock];
+    uint32_t pend[kKnnPend][kBlock];
+};
+
+// The search is bound by the instructions a wave issues (the VALU was busy 94%
+// of the time when every lane searched by itself, 32 thousand instructions a
+// wave on a dense cloud of 69M vertices), and what a wave issues is the union of
+// what its 64 lanes do.  So the lanes stay together wherever the work is heavy:
+//  * cells are tested at offsets the whole wave shares, in single precision
+//    (gap and table index a few operations each), and only queued;
+//  * the queued ranges are then read as one flat loop per lane, so a wave
+//    takes as many steps as its busiest lane has candidates in all, not the
+//    sum over cells of the fullest lane's;
+//  * a candidate is first compared in single precision with the current
+//    bound, and only those that pass are queued for the sorted list, which
+//    the lanes extend together (64-bit keys, exact).  When a lane's queue is
+//    full, half of it is taken in; the lanes behind it catch up meanwhile.
+// Single-precision values only decide what is looked at again: distances are
+// rounded by at most 2^-22 of their value and the bound is raised by 2^-20, so
+// nothing that could enter the list is dropped.
+// Neighbour lists with the grid build, before and after: 20M vertices (k = 16)
+// 17.0 -> 13.1 ms; 64M vertices at the default cells 103 -> 60 ms; 29 thousand
+// (k = 8) 0.190 -> 0.119 ms.
 template <int KM>
-__device__ __forceinline__ void key_shell_search(int64_t N, int64_t s, int shift, int32_t qx, int32_t qy, int32_t qz,
-                                                 const uint64_t* __restrict__ qs, const int32_t* __restrict__ perm,
-                                                 const uint2* __restrict__ cell_range, const KeyFmt f,
-                                                 uint64_t (&k)[KM]) {
-    const int64_t lo = s - kKnnWin < 0 ? 0 : s - kKnnWin;
-    const int64_t hi = s + kKnnWin >= N ? N - 1 : s + kKnnWin;
-    for (int o = -kKnnWin; o <= kKnnWin; ++o) {
-        const int64_t t = s + o;
-        if (o == 0 || t < 0 || t >= N) continue;
-        int32_t ax, ay, az;
-        qunpack(qs[t], ax, ay, az);
-        const int64_t ex = ax - qx, ey = ay - qy, ez = az - qz;
-        key_insert<KM>(k, make_key((uint64_t)(ex * ex + ey * ey + ez * ez), (uint32_t)perm[t], f));
+struct KnnSearch {
+    const float4* __restrict__ pts;
+    const uint2* __restrict__ cells;
+    KeyFmt f;
+    float qx, qy, qz;
+    uint32_t lo, nwin;      // seeded index range: [lo, lo + nwin]
+    float bound;            // not below the worst kept squared distance; inf until the list is full
+    int nr, np;             // queued ranges, pending candidates
+    uint64_t k[KM];
+    KnnScratch* sc;
+
+    // Reads the queued ranges, one candidate per lane and step, and lets those
+    // within the bound into the list.  The one place where the list grows: it is
+    // unrolled over registers, and a second copy of it spills.
+    __device__ __forceinline__ void drain(bool flush_all) {
+        const int tid = threadIdx.x;
+        int i = 0;
+        uint2 r = make_uint2(0u, ~0u);
+        float4 p = make_float4(NAN, 0.f, 0.f, 0.f);   // a lane without a candidate: no distance passes
+        if (nr > 0) {
+            r = sc->range[0][tid];
+            p = pts[r.x];
+        }
+        for (;;) {
+            const float dx = p.x - qx, dy = p.y - qy, dz = p.z - qz;
+            const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            const bool take = d2 <= bound && r.x - lo > nwin;
+            if (take) sc->pend[np][tid] = r.x;
+            np += take ? 1 : 0;
+            if (++r.x >= r.y) {
+                p.x = NAN;
+                r.y = ~0u;
+                if (++i < nr) r = sc->range[i][tid];
+            }
+            if (i < nr) p = pts[r.x];   // in flight over the next turn's bookkeeping
+            const bool more = __any(i < nr);
+            if (__any(np == kKnnPend) || (flush_all && !more)) {
+                // no branch of its own per lane: a lane without a candidate offers
+                // the largest key, which changes nothing
+                const int keep = more ? kKnnKeep : 0;
+                do {
+                    const bool has = np > 0;
+                    np -= has ? 1 : 0;
+                    const float4 c = pts[has ? sc->pend[np][tid] : lo];
+                    const uint64_t key = make_key(c.x - qx, c.y - qy, c.z - qz, __float_as_uint(c.w), f);
+                    key_insert<KM>(k, has ? key : ~0ull);
+                } while (__any(np > keep));
+                bound = k[KM - 1] == ~0ull ? INFINITY : (float)(k[KM - 1] >> f.idb) * (1.0f + 0x1p-20f);
+            }
+            if (!more) break;
+        }
+        nr = 0;
     }
-    const int G = 1 << (kQBits - shift);
-    const int cx = qx >> shift, cy = qy >> shift, cz = qz >> shift;
-    const int64_t cs = (int64_t)1 << shift;
-    for (int r = 0;; ++r) {
-        for (int dz = -r; dz <= r; ++dz) {
-            const int z = cz + dz;
-            if (z < 0 || z >= G) continue;
-            const int64_t gz = dz < 0 ? (int64_t)qz - ((int64_t)(z + 1) * cs - 1) : (dz > 0 ? (int64_t)z * cs - qz : 0);
-            for (int dy = -r; dy <= r; ++dy) {
-                const int y = cy + dy;
-                if (y < 0 || y >= G) continue;
-                const int64_t gy = dy < 0 ? (int64_t)qy - ((int64_t)(y + 1) * cs - 1) : (dy > 0 ? (int64_t)y * cs - qy : 0);
-                const bool face = (dz == -r || dz == r || dy == -r || dy == r);
-                const int step = (face || r == 0) ? 1 : 2 * r;
-                for (int dx = -r; dx <= r; dx += step) {
-                    const int x = cx + dx;
-                    if (x < 0 || x >= G) continue;
-                    const int64_t gx = dx < 0 ? (int64_t)qx - ((int64_t)(x + 1) * cs - 1) : (dx > 0 ? (int64_t)x * cs - qx : 0);
-                    if ((uint64_t)(gx * gx + gy * gy + gz * gz) > (k[KM - 1] >> f.idb)) continue;   // cell too far
-                    const uint32_t cell = morton3((uint32_t)x, (uint32_t)y, (uint32_t)z);
-                    const uint2 cr = cell_range[cell];
-                    const uint32_t beg = cr.x, end = cr.y;
-                    for (uint32_t t = beg; t < end; ++t) {
-                        if ((int64_t)t >= lo && (int64_t)t <= hi) continue;   // seeded (or the query)
-                        int32_t ax, ay, az;
-                        qunpack(qs[t], ax, ay, az);
-                        const int64_t ex = ax - qx, ey = ay - qy, ez = az - qz;
-                        key_insert<KM>(k, make_key((uint64_t)(ex * ex + ey * ey + ez * ez), (uint32_t)perm[t], f));
+
+    __device__ __forceinline__ void queue(uint32_t a, uint32_t e) {
+        if (a < e) sc->range[nr++][threadIdx.x] = make_uint2(a, e);
+    }
+
+    __device__ __forceinline__ void run(uint32_t N, uint32_t s, int shift) {
+        nr = np = 0;
+        bound = INFINITY;
+        const uint32_t a1 = s < kKnnWin / 2 ? 0u : s - kKnnWin / 2, e1 = N - s <= kKnnWin / 2 ? N : s + kKnnWin / 2 + 1;
+        const uint32_t a2 = s < kKnnWin ? 0u : s - kKnnWin, e2 = N - s <= kKnnWin ? N : s + kKnnWin + 1;
+        queue(a1, s);
+        queue(s + 1, e1);
+        lo = s;
+        nwin = 0;
+        const int lg = kQBits - shift, G = 1 << lg;
+        const int cx = (int)qx >> shift, cy = (int)qy >> shift, cz = (int)qz >> shift;
+        const uint32_t cell0 = ((uint32_t)cz << (2 * lg)) + ((uint32_t)cy << lg) + (uint32_t)cx;
+        const float cs = (float)(1 << shift);
+        // distance to the neighbouring cells on either side of each axis
+        const float lx = qx - (float)(cx << shift) + 1.0f, ly = qy - (float)(cy << shift) + 1.0f,
+                    lz = qz - (float)(cz << shift) + 1.0f;
+        const float hx = cs + 1.0f - lx, hy = cs + 1.0f - ly, hz = cs + 1.0f - lz;
+        auto gap1 = [&](int d, float l, float h) {   // to the cells at offset d (uniform) on one axis; exact
+            return d == 0 ? 0.0f : (d < 0 ? l + (float)(-d - 1) * cs : h + (float)(d - 1) * cs);
+        };
+        // Passes over the cells at Chebyshev distance (rin, rout] from the
+        // query's own: first the 27 around it, then, where the bound is known,
+        // all that it can still reach at once (one shell more where the list is
+        // not full yet).  (iz, iy, ix): the next cells to test, the same for the
+        // whole wave, rows nearest first.  Each turn drains what is queued, then
+        // tests cells until the queue may be full or the pass is through.
+        bool live = true;
+        int rin = -1, rout = -1, iz = 0, iy = 0, ix = 0;
+        int stage = 0;           // 0, 1: the nearer and farther seeds, 2: cells
+        bool pass_end = true;
+        for (;;) {
+            drain(pass_end);
+            if (pass_end) {
+                if (stage == 0) {
+                    queue(a2, a1);
+                    queue(e1, e2);
+                } else if (stage == 1) {
+                    lo = a2;
+                    nwin = e2 - 1 - a2;
+                    rout = 1;
+                    pass_end = false;
+                } else {
+                    // the nearest unvisited cell on any axis: every unvisited vertex is at least `gap` steps away
+                    float gap = INFINITY;
+                    const float rc = (float)rout * cs;
+                    if (cx - rout > 0) gap = fminf(gap, lx + rc);
+                    if (cx + rout < G - 1) gap = fminf(gap, hx + rc);
+                    if (cy - rout > 0) gap = fminf(gap, ly + rc);
+                    if (cy + rout < G - 1) gap = fminf(gap, hy + rc);
+                    if (cz - rout > 0) gap = fminf(gap, lz + rc);
+                    if (cz + rout < G - 1) gap = fminf(gap, hz + rc);
+                    live = live && gap < INFINITY && !(bound < gap * gap * (1.0f - 0x1p-22f));
+                    if (!__any(live)) break;
+                    rin = rout++;
+                    pass_end = false;
+                }
+                ++stage;
+                iz = iy = ix = 0;
+            }
+            while (!pass_end && !__any(nr > kKnnRanges - 4)) {
+                const int dz = zigzag(iz), dy = zigzag(iy);
+                const float gz = gap1(dz, lz, hz), gzz = gz * gz;
+                const bool okz = live && (uint32_t)(cz + dz) < (uint32_t)G && gzz <= bound;
+                const float gy = gap1(dy, ly, hy), gyz = fmaf(gy, gy, gzz);
+                const bool oky = okz && (uint32_t)(cy + dy) < (uint32_t)G && gyz <= bound;
+                bool row_end = !__any(oky);
+                if (!row_end) {
+                    // a row through the cube already read has two parts
+                    const bool holed = abs(dz) <= rin && abs(dy) <= rin;
+                    const int n1 = holed ? rout - rin : 2 * rout + 1, n = holed ? 2 * n1 : n1;
+                    const int row = (dz << (2 * lg)) + (dy << lg);
+                    uint2 cr[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {   // up to four lookups in flight
+                        const int i = ix + u, dx = i < n1 ? i - rout : rin + 1 + i - n1;
+                        cr[u] = make_uint2(0u, 0u);
+                        if (i < n) {
+                            const float gx = gap1(dx, lx, hx);
+                            if (oky && (uint32_t)(cx + dx) < (uint32_t)G && fmaf(gx, gx, gyz) <= bound)
+                                cr[u] = cells[cell0 + (uint32_t)(row + dx)];
+                        }
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) queue(cr[u].x, cr[u].y);
+                    ix += 4;
+                    row_end = ix >= n;
+                }
+                if (row_end) {
+                    ix = 0;
+                    if (++iy > 2 * rout || !__any(okz)) {
+                        iy = 0;
+                        if (++iz > 2 * rout) pass_end = true;
                     }
                 }
             }
         }
-        int64_t gap = INT64_MAX;
-        const int c3[3] = {cx, cy, cz};
-        const int64_t q3[3] = {qx, qy, qz};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (c3[a] - r > 0) gap = min(gap, q3[a] - (int64_t)(c3[a] - r) * cs + 1);
-            if (c3[a] + r < G - 1) gap = min(gap, (int64_t)(c3[a] + r + 1) * cs - q3[a]);
-        }
-        if (gap == INT64_MAX) break;
-        if ((k[KM - 1] >> f.idb) < (uint64_t)(gap * gap)) break;
     }
-}
 
-// WPE: the minimum waves per SIMD the compiler must fit the search in.  For
-// lists of up to 16 keys a bound of 6 or 8 (whichever compiles without
-// spills: 8 for 7 and 9-14 keys, 6 for 8, 15 and 16) fits it in 55-68
-// registers, 7-8 resident waves instead of 4, which hides more of the
-// candidate loads' latency (at 15 keys the bound of 6 ran 3% faster than 8);
-// longer lists take no bound (1).
+    // 0, -1, 1, -2, 2, ...
+    static __device__ __forceinline__ int zigzag(int i) { return (i & 1) ? -((i + 1) >> 1) : (i >> 1); }
+};
+
+// WPE: the minimum waves per SIMD the compiler must fit the search in: 6 for
+// lists of up to 16 keys (80 registers, nothing spilled; 7 and 8 spill and are
+// 2% and 13% slower at k = 16, 5 is 4% slower); longer lists take no bound.
 template <int KM, int WPE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) void k_knn(int64_t N, int K, int shift, const uint64_t* __restrict__ qs,
-                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ inv,
-                                                const uint2* __restrict__ cell_range,
-                                                int32_t* __restrict__ col_sorted, int32_t* __restrict__ col_canon,
-                                                int64_t* __restrict__ row_ptr, uint32_t* __restrict__ redo,
-                                                uint32_t* __restrict__ nredo, const KeyFmt f) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) void k_knn(
+    int64_t N, int K, int shift, const float4* __restrict__ pts, const int32_t* __restrict__ inv,
+    const uint2* __restrict__ cell_range, int32_t* __restrict__ col_sorted, int32_t* __restrict__ col_canon,
+    int64_t* __restrict__ row_ptr, uint32_t* __restrict__ redo, uint32_t* __restrict__ nredo, const KeyFmt f) {
+    __shared__ KnnScratch scratch;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t s = tile * blockDim.x + threadIdx.x;
     if (s >= N) return;
     const int m = K - 1;
-    int32_t qx, qy, qz;
-    qunpack(qs[s], qx, qy, qz);
-    const uint32_t self = (uint32_t)perm[s];
-    uint64_t k[KM];
+    const float4 q = pts[s];
+    const uint32_t self = __float_as_uint(q.w);
+    KnnSearch<KM> ks;
+    ks.pts = pts;
+    ks.cells = cell_range;
+    ks.f = f;
+    ks.sc = &scratch;
+    ks.qx = q.x;
+    ks.qy = q.y;
+    ks.qz = q.z;
 #pragma unroll
-    for (int p = 0; p < KM; ++p) k[p] = p < KM - m ? 0ull : ~0ull;
-    if (m > 0) key_shell_search<KM>(N, s, shift, qx, qy, qz, qs, perm, cell_range, f, k);
-    const bool sat = m > 0 && (k[KM - 1] >> f.idb) >= f.sat;   // a kept distance saturated: redo exactly
+    for (int p = 0; p < KM; ++p) ks.k[p] = p < KM - m ? 0ull : ~0ull;
+    if (m > 0) ks.run((uint32_t)N, (uint32_t)s, shift);
+    const bool sat = m > 0 && (ks.k[KM - 1] >> f.idb) >= f.sat;   // a kept distance saturated: redo exactly
     const uint32_t slot = wave_append(nredo, sat);
     if (sat) {
         redo[slot] = (uint32_t)s;
@@ -580,7 +705,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
         col_sorted[eidx(s, 0, K)] = (int32_t)s;
 #pragma unroll
         for (int p = 0; p < KM; ++p)
-            if (p >= KM - m) col_sorted[eidx(s, 1 + p - (KM - m), K)] = inv[(uint32_t)(k[p] & f.idmask)];
+            if (p >= KM - m) col_sorted[eidx(s, 1 + p - (KM - m), K)] = inv[(uint32_t)(ks.k[p] & f.idmask)];
         for (int l = K; l < ell_k4(K); ++l) col_sorted[eidx(s, l, K)] = (int32_t)s;
     }
     if (col_canon) {
@@ -588,7 +713,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
         row[0] = (int32_t)self;
 #pragma unroll
         for (int p = 0; p < KM; ++p)
-            if (p >= KM - m) row[1 + p - (KM - m)] = (int32_t)(k[p] & f.idmask);
+            if (p >= KM - m) row[1 + p - (KM - m)] = (int32_t)(ks.k[p] & f.idmask);
     }
     if (row_ptr) {
         row_ptr[self] = (int64_t)self * K;
@@ -598,8 +723,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
 
 // Exact (d2, id) search for the queries the fast path handed over.
 template <int KM>
-__global__ __launch_bounds__(kBlock) void k_knn_exact(int64_t N, int K, int shift, const uint64_t* __restrict__ qs,
-                                                      const int32_t* __restrict__ perm,
+__global__ __launch_bounds__(kBlock) void k_knn_exact(int64_t N, int K, int shift, const float4* __restrict__ pts,
                                                       const int32_t* __restrict__ inv,
                                                       const uint2* __restrict__ cell_range,
                                                       int32_t* __restrict__ col_sorted,
@@ -611,14 +735,12 @@ __global__ __launch_bounds__(kBlock) void k_knn_exact(int64_t N, int K, int shif
     const int m = K - 1;
     for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n; idx += gridDim.x * blockDim.x) {
         const int64_t s = redo[idx];
-        int32_t qx, qy, qz;
-        qunpack(qs[s], qx, qy, qz);
-        const uint32_t self = (uint32_t)perm[s];
+        const float4 q = pts[s];
         uint64_t d[KM];
         uint32_t o[KM];
         list_reset<KM>(d, o, m);
-        shell_search<KM>(s, m, shift, qx, qy, qz, qs, perm, cell_range, d, o);
-        knn_write<KM>(s, K, m, self, N, inv, d, o, col_sorted, col_canon, row_ptr);
+        shell_search<KM>(s, shift, (int32_t)q.x, (int32_t)q.y, (int32_t)q.z, pts, cell_range, d, o);
+        knn_write<KM>(s, K, m, __float_as_uint(q.w), N, inv, d, o, col_sorted, col_canon, row_ptr);
     }
 }
 
@@ -630,8 +752,8 @@ __global__ __launch_bounds__(kBlock) void k_redo_all(int64_t N, uint32_t* __rest
     if (i == 0) *nredo = (uint32_t)N;
 }
 
-hipError_t launch_knn(int64_t N, int K, int shift, const uint64_t* qsorted, const int32_t* perm,
-                      const int32_t* inv, const uint2* cell_range, int32_t* col_sorted, int32_t* col_canon,
+hipError_t launch_knn(int64_t N, int K, int shift, const float4* pts, const int32_t* inv,
+                      const uint2* cell_range, int32_t* col_sorted, int32_t* col_canon,
                       int64_t* row_ptr, uint32_t* redo, uint32_t* nredo, bool exact_only, hipStream_t s) {
     if (N == 0) return hipSuccess;
     const int m = K - 1;
@@ -640,15 +762,13 @@ hipError_t launch_knn(int64_t N, int K, int shift, const uint64_t* qsorted, cons
     const KeyFmt f = key_fmt(N);
     auto go = [&](auto km) {
         constexpr int KM = decltype(km)::value;
-        constexpr int WPE = KM == 8 ? 6 : (KM <= 14 ? 8 : (KM <= 16 ? 6 : 1));
+        constexpr int WPE = KM <= 16 ? 6 : 1;
         if (exact_only)
             hipLaunchKernelGGL(k_redo_all, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, redo, nredo);
         else
             hipLaunchKernelGGL((k_knn<KM, WPE>), dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, K,
-                               shift, qsorted, perm, inv, cell_range, col_sorted, col_canon, row_ptr, redo, nredo,
-                               f);
-        hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, qsorted, perm, inv,
-                           cell_range, col_sorted, col_canon, row_ptr, (const uint32_t*)redo,
+                               shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, redo, nredo, f);
+        hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, (const uint32_t*)redo,
                            (const uint32_t*)nredo);
     };
     // k = 8..17 get a list of exactly K-1 keys: a sentinel slot costs its

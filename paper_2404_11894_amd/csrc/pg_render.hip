@@ -89,13 +89,13 @@ hipError_t render_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, co
     GridBufs& g = r.g;
     {
         ProfScope ps(s, "grid");
-        PG_TRY(run_grid(p, g, r.rec, s, r.recp));
+        PG_TRY(run_grid(p, g, GridFor::kNeighbours, r.rec, s, r.recp));
     }
     if (N == 0) {
         if (out && out->row_ptr) PG_TRY(launch_fill(out->row_ptr, sizeof(int64_t), s));
     } else {
         ProfScope ps(s, "knn");
-        PG_TRY(launch_knn(N, K, g.shift, g.qs, g.perm, g.inv, g.range, r.col, out ? out->col : nullptr,
+        PG_TRY(launch_knn(N, K, g.shift, g.pts, g.inv, g.range, r.col, out ? out->col : nullptr,
                           out ? out->row_ptr : nullptr, g.redo, g.nredo, (q->flags & PG_FLAG_EXACT_KNN) != 0, s));
     }
     const Consts c = make_consts(q, K);
