@@ -349,7 +349,11 @@ pg_status pg_edges(const pg_paths* paths, const pg_params* params, const int64_t
  * phase, so propagation is the shift to the predecessor.)
  * lplus holds L_0 on entry and L_D on return.  traj, if not NULL, receives
  * L_1..L_D as [D][N][3].  row_ptr / col: the k-nearest layout, checked as in
- * pg_edges. */
+ * pg_edges.  Where the work pays for it, the size call asks for room to move
+ * the graph to the spatially sorted order and iterate there (same results bit
+ * for bit); a workspace that only holds the path-order buffers (20 bytes per
+ * vertex plus alignment) is accepted for every graph and iterates in path
+ * order. */
 pg_status pg_propagate_workspace_size(const pg_paths* paths, const pg_params* params, size_t* bytes);
 pg_status pg_propagate(const pg_paths* paths, const pg_params* params, const int64_t* row_ptr,
                        const int32_t* col, const float* w_ind, const float* b, float* lplus, float* traj,
@@ -361,8 +365,8 @@ pg_status pg_propagate(const pg_paths* paths, const pg_params* params, const int
  * the same arguments, results and errors, but no workspace argument.  Its
  * workspace is a static device array of PG_STATIC_SCRATCH_BYTES (64 MiB) that
  * the library holds on every GPU it runs on until the process ends; the call
- * allocates nothing.  It serves graphs whose pg_propagate_workspace_size is at
- * most that (20 bytes per vertex plus alignment: N up to about 3.3 million)
+ * allocates nothing.  It serves graphs whose path-order buffers fit in that
+ * (20 bytes per vertex plus alignment: N up to about 3.3 million)
  * and returns PG_ERR_WORKSPACE for larger ones.  The array's address on the
  * current device (which must be the stream's) is looked up on the first call
  * there.  Every call on one GPU uses the same array, so calls that overlap in

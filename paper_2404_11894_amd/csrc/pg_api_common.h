@@ -40,7 +40,9 @@ Consts make_consts(const pg_params* q, int K);
 int32_t default_shift(int64_t N);
 int shift_of(const pg_params* q, int64_t N);
 // pg_propagate after g_error is cleared: validation, the workspace check
-// against propagate_size, and the launches (shared with pg_propagate_static).
+// against propagate_size (what the path-order iteration needs; a larger
+// workspace may let the iterations run in the sorted order), and the launches
+// (shared with pg_propagate_static).
 size_t propagate_size(const pg_paths* p, const pg_params* q);
 pg_status propagate_run(const pg_paths* paths, const pg_params* params, const int64_t* row_ptr, const int32_t* col,
                         const float* w_ind, const float* b, float* lplus, float* traj, void* ws, size_t ws_bytes,
@@ -85,8 +87,14 @@ struct GridBufs {
     uint64_t* qs = nullptr;        // clusters: sorted packed quantised positions (the same memory)
     uint32_t* redo = nullptr;      // kNN queries handed to the exact search
     uint32_t* nredo = nullptr;
+    // what the scatter writes besides perm and inv (each nullable)
+    uint64_t* out_qs = nullptr;
+    float4* out_pts = nullptr;
+    VRec* out_rec = nullptr;
 };
 
+void carve_order(Carver& cv, GridBufs& g, int64_t N, int shift);
+hipError_t run_order(const pg_paths* p, GridBufs& g, int32_t* flag, hipStream_t s);
 void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift);
 // What the grid is built for: the neighbour search (points and cell ranges) or
 // the cluster relation (packed positions).

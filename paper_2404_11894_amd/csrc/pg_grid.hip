@@ -210,7 +210,7 @@ __device__ inline void store_record(VRec* dst, const VRec& r) {
     for (int k = 0; k < 5; ++k) d4[k] = s4[k];
 }
 
-__global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P, int shift,
+__global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P,
                                                     const uint32_t* __restrict__ cellid,
                                                     const uint32_t* __restrict__ rank,
                                                     const uint32_t* __restrict__ cell_start,
@@ -219,10 +219,10 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P, int s
                                                     VRec* __restrict__ rec) {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= N) return;
-    (void)shift;
     int64_t s = (int64_t)cell_start[cellid[v]] + rank[v];
     perm[s] = (int32_t)v;
     inv[v] = (int32_t)s;
+    if (!qsorted && !pts) return;
     const uint32_t qx = quant(P.pos[3 * v]), qy = quant(P.pos[3 * v + 1]), qz = quant(P.pos[3 * v + 2]);
     if (qsorted) qsorted[s] = qpack(qx, qy, qz);
     if (pts) pts[s] = make_float4((float)qx, (float)qy, (float)qz, __int_as_float((int32_t)v));   // exact: below 2^24
@@ -233,11 +233,11 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P, int s
     }
 }
 
-hipError_t launch_scatter(int64_t N, const pg_paths& paths, int shift, const uint32_t* cellid,
+hipError_t launch_scatter(int64_t N, const pg_paths& paths, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
                           uint64_t* qsorted, float4* pts, VRec* rec, hipStream_t s) {
     if (N == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, paths, shift, cellid,
+    hipLaunchKernelGGL(k_scatter, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, paths, cellid,
                        rank, cell_start, perm, inv, qsorted, pts, rec);
     return hipGetLastError();
 }

@@ -244,23 +244,25 @@ __host__ __device__ inline int64_t c16_size(int64_t N, int K) { return div_up(N,
 // four escaped ids are read from the four list slots at its start, with no
 // branch of their own (the list is as long as the ELL, so p0 + 3 stays
 // inside it; slots past the row's own escapes are never selected).
-template <int KT>
+// START (a caller's rows, which need not begin with the row itself): slot 0 is
+// an offset like the others and the row's start in the list is start[i].
+template <int KT, bool START = false>
 __device__ __forceinline__ void c16_row_ids(int64_t i, int K, const int16_t* __restrict__ c16,
                                             const uint32_t* __restrict__ c16_base, const int32_t* __restrict__ ovf,
-                                            int32_t (&j)[KT]) {
+                                            int32_t (&j)[KT], const uint16_t* __restrict__ start = nullptr) {
     static_assert(KT % 4 == 0 && KT > 0, "compile-time K4 only");
     constexpr int NO = (KT + 7) / 8;
     const int64_t b16 = c16_row(i, K);
     i32x4 d[NO];
 #pragma unroll
     for (int o = 0; o < NO; ++o) d[o] = ld_quad_nt(reinterpret_cast<const int32_t*>(c16 + b16 + o * kOctStride));
-    const int64_t p0 = (int64_t)c16_base[i >> 6] + (uint32_t)(d[0][0] & 0xffff);
+    const int64_t p0 = (int64_t)c16_base[i >> 6] + (START ? (uint32_t)start[i] : (uint32_t)(d[0][0] & 0xffff));
     // more than four escaped ids take a load of their own
     const int32_t e0 = ovf[p0], e1 = ovf[p0 + 1], e2 = ovf[p0 + 2], e3 = ovf[p0 + 3];
     int r = 0;
-    j[0] = (int32_t)i;
+    if (!START) j[0] = (int32_t)i;
 #pragma unroll
-    for (int l = 1; l < KT; ++l) {
+    for (int l = START ? 0 : 1; l < KT; ++l) {
         const int32_t word = d[l >> 3][(l & 7) >> 1];
         const int32_t off = (l & 1) ? (word >> 16) : (int32_t)(int16_t)(word & 0xffff);
         int32_t v = (int32_t)(i + off);
@@ -490,7 +492,7 @@ hipError_t launch_quantize_count(int64_t N, const float* pos, int shift, uint32_
 size_t scan_partials_bytes(int64_t n);
 hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials,
                                  hipStream_t s);
-hipError_t launch_scatter(int64_t N, const pg_paths& paths, int shift, const uint32_t* cellid,
+hipError_t launch_scatter(int64_t N, const pg_paths& paths, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
                           uint64_t* qsorted, float4* pts, VRec* rec, hipStream_t s);
 // redo: [N] scratch list, nredo: one counter (queries the fast 64-bit-key
@@ -548,9 +550,19 @@ hipError_t launch_spmv_scatter(int64_t N, int K, const int32_t* col, const float
 hipError_t launch_shift(int64_t N, const int32_t* succ, const float* y, float* x, hipStream_t s, int tile = 0);
 hipError_t launch_check_rows(int64_t N, int K, const int64_t* row_ptr, int32_t* flag, hipStream_t s);
 // compact ids of the sliced ELL (see c16_row_sum): c16 [c16_size], c16_base
-// [n_slices + 1], ovf [ell_size] (room for every id), cnt / partials scratch
+// [n_slices + 1], ovf [ell_size] (room for every id), cnt / partials scratch;
+// start (nullable, [N]): slot 0 is kept as an id and the rows' list starts go
+// there (c16_row_ids<KT, true>)
 hipError_t launch_c16_build(int64_t N, int K, const int32_t* col, int16_t* c16, uint32_t* cnt, uint32_t* c16_base,
-                            uint32_t* partials, int32_t* ovf, hipStream_t s);
+                            uint32_t* partials, int32_t* ovf, hipStream_t s, uint16_t* start = nullptr);
+// a caller's path-order graph moved to the sorted order and iterated there
+hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t* inv, const int32_t* col,
+                           const float* w, const float* b, const float* x0, const float* alpha,
+                           const int32_t* succ, int32_t* scol, float* sw, float* sb, float* sx, float* salpha,
+                           int32_t* ssucc, hipStream_t s);
+hipError_t launch_spmv_sorted(int64_t N, int K, const int16_t* c16, const uint16_t* start, const uint32_t* c16_base,
+                              const int32_t* ovf, const float* w, const float* x, const float* b, const float* alpha,
+                              float* y, hipStream_t s);
 hipError_t launch_spmv_c16(int64_t N, int K, const int16_t* c16, const uint32_t* c16_base, const int32_t* ovf,
                            const int32_t* col, const float* w, const float* x, const float* b, const float* alpha,
                            float* y, hipStream_t s, int tile = 0, int tile_group = 0);

@@ -142,15 +142,17 @@ hipError_t launch_spmv_scatter(int64_t N, int K, const int32_t* col, const float
 // and the row's octets are written as 16-byte stores.  Rows past N keep
 // offset 0 in every slot.
 __global__ __launch_bounds__(kBlock) void k_c16_build(int64_t N, int K, const int32_t* __restrict__ col,
-                                                      int16_t* __restrict__ c16, uint32_t* __restrict__ cnt) {
+                                                      int16_t* __restrict__ c16, uint32_t* __restrict__ cnt,
+                                                      uint16_t* __restrict__ row_start) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t nsl = div_up(N, kSlice);
     if ((i >> 6) >= nsl) return;   // whole waves leave together (a slice is one wave)
     const int K4 = ell_k4(K), K8 = c16_k8(K);
+    const int l0 = row_start ? 0 : 1;
     uint32_t n = 0;
     if (i < N)
-        for (int l = 1; l < K4; ++l) {
+        for (int l = l0; l < K4; ++l) {
             const int64_t off = (int64_t)col[eidx(i, l, K)] - i;
             n += (off < -32767 || off > 32767) ? 1u : 0u;
         }
@@ -161,6 +163,7 @@ __global__ __launch_bounds__(kBlock) void k_c16_build(int64_t N, int K, const in
         if (lane >= o) inc += t;
     }
     const uint32_t start = inc - n;
+    if (row_start && i < N) row_start[i] = (uint16_t)start;
     const int64_t b16 = c16_row(i, K);
     for (int o = 0; 8 * o < K8; ++o) {
         int32_t words[4];
@@ -169,7 +172,7 @@ __global__ __launch_bounds__(kBlock) void k_c16_build(int64_t N, int K, const in
             for (int e = 0; e < 2; ++e) {
                 const int l = 8 * o + 2 * h + e;
                 int32_t val = 0;
-                if (l == 0) {
+                if (l == 0 && !row_start) {
                     val = (int32_t)(start & 0xffffu);
                 } else if (i < N && l < K4) {
                     const int64_t off = (int64_t)col[eidx(i, l, K)] - i;
@@ -188,12 +191,13 @@ __global__ __launch_bounds__(kBlock) void k_c16_build(int64_t N, int K, const in
 __global__ __launch_bounds__(kBlock) void k_c16_escapes(int64_t N, int K, const int32_t* __restrict__ col,
                                                         const int16_t* __restrict__ c16,
                                                         const uint32_t* __restrict__ c16_base,
+                                                        const uint16_t* __restrict__ row_start,
                                                         int32_t* __restrict__ ovf) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= N) return;
-    int64_t p = (int64_t)c16_base[i >> 6] + (uint16_t)c16[c16_row(i, K)];
+    int64_t p = (int64_t)c16_base[i >> 6] + (row_start ? row_start[i] : (uint16_t)c16[c16_row(i, K)]);
     const int K4 = ell_k4(K);
-    for (int l = 1; l < K4; ++l) {
+    for (int l = row_start ? 0 : 1; l < K4; ++l) {
         const int32_t j = col[eidx(i, l, K)];
         const int64_t off = (int64_t)j - i;
         if (off < -32767 || off > 32767) ovf[p++] = j;
@@ -201,15 +205,15 @@ __global__ __launch_bounds__(kBlock) void k_c16_escapes(int64_t N, int K, const 
 }
 
 hipError_t launch_c16_build(int64_t N, int K, const int32_t* col, int16_t* c16, uint32_t* cnt, uint32_t* c16_base,
-                            uint32_t* partials, int32_t* ovf, hipStream_t s) {
+                            uint32_t* partials, int32_t* ovf, hipStream_t s, uint16_t* start) {
     if (N == 0) return hipSuccess;
     const int64_t nsl = div_up(N, kSlice);
     hipLaunchKernelGGL(k_c16_build, dim3((unsigned)div_up(nsl * kSlice, kBlock)), dim3(kBlock), 0, s, N, K, col,
-                       c16, cnt);
+                       c16, cnt, start);
     hipError_t e = launch_scan_exclusive(cnt, c16_base, nsl, partials, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_c16_escapes, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, K, col, c16,
-                       c16_base, ovf);
+                       c16_base, (const uint16_t*)start, ovf);
     return hipGetLastError();
 }
 
@@ -260,6 +264,123 @@ __global__ __launch_bounds__(kBlock) void k_check_rows(int64_t N, int K, const i
 hipError_t launch_check_rows(int64_t N, int K, const int64_t* row_ptr, int32_t* flag, hipStream_t s) {
     hipLaunchKernelGGL(k_check_rows, dim3((unsigned)div_up(N + 1, kBlock)), dim3(kBlock), 0, s, N, K, row_ptr,
                        flag);
+    return hipGetLastError();
+}
+
+// ------------------------------------- a caller's graph in sorted order ---
+// pg_propagate takes rows and ids in path order, where neighbours lie anywhere
+// in memory: every gathered x costs a cache line of its own (5M vertices, K =
+// 16: 970 us an iteration, 1.1 TB/s of the bytes it needs).  Moved once to the
+// spatially sorted order, the iteration runs as the render's does (145 us).
+//
+// Row s of the sliced ELL = row perm[s] of the caller's, ids through inv, with
+// b, L_0, albedo and successors beside it.  Ids from callers are not trusted:
+// one out of range points at row N, which holds 0, with weight 0 (x has N + 1
+// rows); the padding slots hold the row itself and are left out of the sums.  One thread per quad, a row's
+// quads in neighbouring lanes, so its 4 K bytes are read from whole lines.
+__global__ __launch_bounds__(kBlock) void k_relayout(int64_t N, int K, const int32_t* __restrict__ perm,
+                                                     const int32_t* __restrict__ inv, const int32_t* __restrict__ col,
+                                                     const float* __restrict__ w, const float* __restrict__ b,
+                                                     const float* __restrict__ x0, const float* __restrict__ alpha,
+                                                     const int32_t* __restrict__ succ, int32_t* __restrict__ scol,
+                                                     float* __restrict__ sw, float* __restrict__ sb,
+                                                     float* __restrict__ sx, float* __restrict__ salpha,
+                                                     int32_t* __restrict__ ssucc) {
+    const int nq = ell_k4(K) / 4;
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (t == 0) st3(sx, N, f3{0.f, 0.f, 0.f});
+    const int64_t s = t / nq;
+    if (s >= N) return;
+    const int q = (int)(t - s * nq);
+    const int64_t v = perm[s];
+    const int64_t row = v * (int64_t)K;
+    int32_t j[4];
+    float ww[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int l = 4 * q + c;
+        j[c] = l < K ? col[row + l] : -1;
+        ww[c] = l < K ? w[row + l] : 0.0f;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const bool ok = (uint32_t)j[c] < (uint32_t)N;
+        j[c] = ok ? inv[j[c]] : (4 * q + c < K ? (int32_t)N : (int32_t)s);
+        ww[c] = ok ? ww[c] : 0.0f;
+    }
+    const int64_t e = ell_row(s, K) + q * kQuadStride;
+    *reinterpret_cast<i32x4*>(scol + e) = i32x4{j[0], j[1], j[2], j[3]};
+    *reinterpret_cast<f32x4*>(sw + e) = f32x4{ww[0], ww[1], ww[2], ww[3]};
+    if (q != 0) return;
+    st3(sb, s, ld3(b, v));
+    st3(sx, s, ld3(x0, v));
+    salpha[s] = alpha[v];
+    const int32_t u = succ[v];
+    ssucc[s] = u >= 0 ? inv[u] : -1;
+}
+
+hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t* inv, const int32_t* col,
+                           const float* w, const float* b, const float* x0, const float* alpha,
+                           const int32_t* succ, int32_t* scol, float* sw, float* sb, float* sx, float* salpha,
+                           int32_t* ssucc, hipStream_t s) {
+    if (N == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_relayout, dim3((unsigned)div_up(N * (ell_k4(K) / 4), kBlock)), dim3(kBlock), 0, s, N, K, perm, inv, col, w,
+                       b, x0, alpha, succ, scol, sw, sb, sx, salpha, ssucc);
+    return hipGetLastError();
+}
+
+// One thread per row over the compact ids, every product rounded and the K
+// products added pairwise in the order of k_spmv's lane reduction (slot l with
+// slot l + KP/2, then KP/4, ..., the slots past K contributing 0), so the two
+// give the same results bit for bit.  Left to itself the compiler interleaves
+// gathers and products (73 registers at K = 16, 210 us on 5M vertices); with all
+// gathers issued first (86 registers) it takes 141 us.
+template <int KT, int BS>
+__global__ __launch_bounds__(BS) void k_spmv_sorted(int64_t N, int K, const int16_t* __restrict__ c16,
+                                                    const uint16_t* __restrict__ start,
+                                                    const uint32_t* __restrict__ c16_base,
+                                                    const int32_t* __restrict__ ovf, const float* __restrict__ w,
+                                                    const float* __restrict__ x, const float* __restrict__ b,
+                                                    const float* __restrict__ alpha, float* __restrict__ y) {
+#pragma clang fp contract(off)
+    const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+    if (i >= N) return;
+    constexpr int NQ = KT / 4, KP = KT <= 4 ? 4 : (KT <= 8 ? 8 : (KT <= 16 ? 16 : 32));
+    const int64_t base = ell_row(i, K);
+    f32x4 ww[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) ww[q] = ld_quad_nt(w + base + q * kQuadStride);
+    int32_t j[KT];
+    c16_row_ids<KT, true>(i, K, c16, c16_base, ovf, j, start);
+    f3 a[KP];
+#pragma unroll
+    for (int l = 0; l < KT; ++l) a[l] = ld3(x, j[l]);
+    __builtin_amdgcn_sched_barrier(0);   // every gather in flight before the first product
+#pragma unroll
+    for (int l = 0; l < KP; ++l) {
+        const float wl = l < KT ? ww[(l < KT ? l : 0) >> 2][l & 3] : 0.0f;
+        a[l] = l < K && l < KT ? f3{wl * a[l].x, wl * a[l].y, wl * a[l].z} : f3{0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int o = KP / 2; o > 0; o >>= 1)
+#pragma unroll
+        for (int l = 0; l < o; ++l) a[l] = f3{a[l].x + a[l + o].x, a[l].y + a[l + o].y, a[l].z + a[l + o].z};
+    const f3 bb = ld3(b, i);
+    const float al = alpha[i];
+    st3_nt(y, i, f3{fmaf(al, a[0].x, bb.x), fmaf(al, a[0].y, bb.y), fmaf(al, a[0].z, bb.z)});
+}
+
+hipError_t launch_spmv_sorted(int64_t N, int K, const int16_t* c16, const uint16_t* start, const uint32_t* c16_base,
+                              const int32_t* ovf, const float* w, const float* x, const float* b, const float* alpha,
+                              float* y, hipStream_t s) {
+    if (N == 0) return hipSuccess;
+    constexpr int BS = 512;   // as the render's aggregation over the compact ids
+    dispatch_k4(K, [&](auto kt) {
+        constexpr int KT = decltype(kt)::value;
+        if constexpr (KT > 0)
+            hipLaunchKernelGGL((k_spmv_sorted<KT, BS>), dim3((unsigned)div_up(N, BS)), dim3(BS), 0, s, N, K, c16, start,
+                               c16_base, ovf, w, x, b, alpha, y);
+    });
     return hipGetLastError();
 }
 
