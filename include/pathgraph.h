@@ -281,7 +281,7 @@ typedef struct pg_records {
 /* Pass 1: traces every path and writes path_offsets[P+1] (device); N to
  * *n_vertices (host; the call synchronises the stream once).  The records
  * stay in the workspace, which holds max_depth record slots per path
- * (96 bytes each, 16 more with a point light) plus the paths' extra
+ * (88 bytes each, 24 more with a point light) plus the paths' extra
  * samples: pg_trace_workspace_size grows with P * max_depth. */
 pg_status pg_trace_workspace_size(const pg_tracer* t, size_t* bytes);
 pg_status pg_trace_count(const pg_tracer* t, int64_t* path_offsets, int64_t* n_vertices, void* ws,

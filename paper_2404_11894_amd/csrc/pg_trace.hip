@@ -195,11 +195,16 @@ struct Out {
     float *dir_pl, *l_pl;
 };
 
-// One traced vertex in the slab: 24 floats (32 with a point light), so a lane
-// stores it as 6 (8) 16-byte pieces of its own lines:
-//   pos albedo | dir_in - | l_sun dir_env.x | dir_env.yz l_env.xy | l_env.z dir_out | l_phase -
-//   [| dir_pl - | l_pl -]
-constexpr int kRec = 6, kRecPl = 8;
+// One traced vertex in the slab, stored by its lane in 16-byte pieces of its own
+// lines: 88 bytes (112 with a point light).
+//   pos albedo | dir_in l_phase.x | l_sun dir_env.x | dir_env.yz l_env.xy | l_env.z dir_out
+//   then l_phase.yz: 8 bytes in an array of their own, or the point light's
+//   l_phase.yz dir_pl.xy | dir_pl.z l_pl
+struct Slab {
+    float4* rec;
+    float2* tail;   // without a point light
+};
+constexpr int kRec = 5, kRecPl = 7;
 
 // The M extra emitter samples at a path's first vertex pt (paper, handling
 // direct light): sun and uniform-sphere environment shadow rays from a
@@ -308,13 +313,21 @@ __device__ __forceinline__ void track(const Tracer& tr, Walk& w, int behind) {
     }
 }
 
+// The radiance that arrives along the continuation if it escapes.
+template <bool PL>
+__device__ __forceinline__ void store_phase(const Slab& slab, int64_t slot, float x, float y, float z) {
+    float4* r = slab.rec + slot * (PL ? kRecPl : kRec);
+    r[1].w = x;
+    *(PL ? reinterpret_cast<float2*>(r + 5) : slab.tail + slot) = make_float2(y, z);
+}
+
 // The flight has ended: at the path's next vertex, whose sun ray starts, or
 // outside, which ends the path.
 template <bool PL, bool EXTRA>
-__device__ __forceinline__ void flight_ended(const Tracer& tr, Walk& w, float4* __restrict__ slab,
+__device__ __forceinline__ void flight_ended(const Tracer& tr, Walk& w, const Slab& slab,
                                              uint32_t* __restrict__ count, const Out& o, float* __restrict__ ecam) {
     const pg_tracer& t = tr.t;
-    float4* r = slab + ((int64_t)w.p * t.max_depth + w.nv) * (PL ? kRecPl : kRec);
+    const int64_t slot = (int64_t)w.p * t.max_depth + w.nv;
     const float ex = w.hit ? 0.0f : (float)t.env_L[0], ey = w.hit ? 0.0f : (float)t.env_L[1],
                 ez = w.hit ? 0.0f : (float)t.env_L[2];
     if (w.nv < 0) {
@@ -322,7 +335,7 @@ __device__ __forceinline__ void flight_ended(const Tracer& tr, Walk& w, float4* 
         ecam[3 * (int64_t)w.p + 1] = ey;
         ecam[3 * (int64_t)w.p + 2] = ez;
     } else {
-        r[5] = make_float4(ex, ey, ez, 0.0f);
+        store_phase<PL>(slab, slot, ex, ey, ez);
     }
     const bool first = w.nv < 0;
     if (w.hit) w.o = d3(w.o.x + w.s * w.dir.x, w.o.y + w.s * w.dir.y, w.o.z + w.s * w.dir.z);
@@ -344,9 +357,9 @@ __device__ __forceinline__ void flight_ended(const Tracer& tr, Walk& w, float4* 
         return;
     }
     w.d = w.dir;
-    r += PL ? kRecPl : kRec;
+    float4* r = slab.rec + (slot + 1) * (PL ? kRecPl : kRec);
     r[0] = make_float4((float)w.o.x, (float)w.o.y, (float)w.o.z, (float)albedo_at(t, w.o));
-    r[1] = make_float4((float)w.d.x, (float)w.d.y, (float)w.d.z, 0.0f);
+    r[1] = make_float4((float)w.d.x, (float)w.d.y, (float)w.d.z, 0.0f);   // l_phase.x when the flight has ended
     const D3 sun = d3(t.sun_dir[0], t.sun_dir[1], t.sun_dir[2]);
     w.cast(kSun, sun, exit_distance(w.o, sun));
 }
@@ -362,10 +375,11 @@ __device__ __forceinline__ void sun_ended(Walk& w) {
 // The environment ray (with a point light: its ray) has ended: the
 // continuation is sampled and the record's emitter samples are stored.
 template <bool PL>
-__device__ __forceinline__ void shadow_ended(const Tracer& tr, Walk& w, float4* __restrict__ slab,
+__device__ __forceinline__ void shadow_ended(const Tracer& tr, Walk& w, const Slab& slab,
                                              uint32_t* __restrict__ count) {
     const pg_tracer& t = tr.t;
-    float4* r = slab + ((int64_t)w.p * t.max_depth + w.nv) * (PL ? kRecPl : kRec);
+    const int64_t slot = (int64_t)w.p * t.max_depth + w.nv;
+    float4* r = slab.rec + slot * (PL ? kRecPl : kRec);
     if (w.ray == kEnv) {
         w.Te = w.T;
         r[2] = make_float4((float)(t.sun_E[0] * w.Ts), (float)(t.sun_E[1] * w.Ts), (float)(t.sun_E[2] * w.Ts),
@@ -383,16 +397,16 @@ __device__ __forceinline__ void shadow_ended(const Tracer& tr, Walk& w, float4* 
             w.cast(kPoint, dl, tmax);
             return;
         }
-        r[6] = make_float4((float)w.dir.x, (float)w.dir.y, (float)w.dir.z, 0.0f);
-        r[7] = make_float4((float)(t.pl_I[0] * w.T / r2), (float)(t.pl_I[1] * w.T / r2), (float)(t.pl_I[2] * w.T / r2),
-                           0.0f);
+        reinterpret_cast<float2*>(r + 5)[1] = make_float2((float)w.dir.x, (float)w.dir.y);
+        r[6] = make_float4((float)w.dir.z, (float)(t.pl_I[0] * w.T / r2), (float)(t.pl_I[1] * w.T / r2),
+                           (float)(t.pl_I[2] * w.T / r2));
     }
     const double h2 = w.rng.uniform();   // azimuth number first
     const double h1 = w.rng.uniform();
     const D3 wo = sample_hg(w.d, t.g, h1, h2);
     r[4] = make_float4((float)(t.env_L[2] * w.Te), (float)wo.x, (float)wo.y, (float)wo.z);
     if (w.nv == t.max_depth - 1) {   // the last vertex has no continuation
-        r[5] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        store_phase<PL>(slab, slot, 0.0f, 0.0f, 0.0f);
         count[w.p] = (uint32_t)t.max_depth;
         w.state = kIdle;
         return;
@@ -412,7 +426,7 @@ __device__ __forceinline__ void shadow_ended(const Tracer& tr, Walk& w, float4* 
 //    the rays of all lanes that have come to a kind together, but leaves a kind
 //    once at most 1 / kBehind of its lanes are still on such a ray: those miss
 //    the round and go on with the next one's.
-// 20M vertices on a ball (21 a path, depth 64), with the copy below: 14.5 -> 6.4
+// 20M vertices on a ball (21 a path, depth 64), with the copy below: 14.5 -> 6.7
 // ms (queue and wider records alone 9.0); a dense cloud whose rays mostly end at
 // the first step 4.7 -> 3.6 ms.  Refilling at 16 lanes or leaving at 1/5 and 1/16
 // changes at most 8%.  Without rounds (an event handled once enough lanes wait
@@ -426,7 +440,7 @@ constexpr int kRefill = 8, kBehind = 8;
 constexpr int kTraceBlocks = 2048;
 template <bool PL, bool EXTRA>
 __global__ __launch_bounds__(kBlock) void k_trace(Tracer tr, uint32_t P, uint32_t* __restrict__ next,
-                                                  uint32_t* __restrict__ count, float4* __restrict__ slab, Out o,
+                                                  uint32_t* __restrict__ count, Slab slab, Out o,
                                                   float* __restrict__ ecam) {
     Walk w;
     const int lane = threadIdx.x & (kWave - 1);
@@ -468,7 +482,7 @@ __global__ __launch_bounds__(kBlock) void k_trace(Tracer tr, uint32_t P, uint32_
 template <bool PL>
 __global__ __launch_bounds__(kBlock) void k_trace_compact(int64_t P, int64_t maxd, const int64_t* __restrict__ off,
                                                           const uint32_t* __restrict__ start,
-                                                          const float4* __restrict__ slab, Out o, int32_t* flag) {
+                                                          Slab slab, Out o, int32_t* flag) {
     const int64_t slot = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (slot >= P * maxd) return;
     const int64_t p = slot / maxd, k = slot - p * maxd;
@@ -481,7 +495,7 @@ __global__ __launch_bounds__(kBlock) void k_trace_compact(int64_t P, int64_t max
     if (k >= c) return;
     const int64_t v = a + k;
     float f[4 * kRecPl];
-    const float4* r = slab + slot * (PL ? kRecPl : kRec);
+    const float4* r = slab.rec + slot * (PL ? kRecPl : kRec);
 #pragma unroll
     for (int q = 0; q < (PL ? kRecPl : kRec); ++q) {
         const float4 x = r[q];
@@ -489,6 +503,11 @@ __global__ __launch_bounds__(kBlock) void k_trace_compact(int64_t P, int64_t max
         f[4 * q + 1] = x.y;
         f[4 * q + 2] = x.z;
         f[4 * q + 3] = x.w;
+    }
+    if (!PL) {
+        const float2 x = slab.tail[slot];
+        f[20] = x.x;
+        f[21] = x.y;
     }
     o.albedo[v] = f[3];
 #pragma unroll
@@ -499,10 +518,10 @@ __global__ __launch_bounds__(kBlock) void k_trace_compact(int64_t P, int64_t max
         o.dir_env[3 * v + q] = f[11 + q];
         o.l_env[3 * v + q] = f[14 + q];
         o.dir_out[3 * v + q] = f[17 + q];
-        o.l_phase[3 * v + q] = f[20 + q];
+        o.l_phase[3 * v + q] = f[q == 0 ? 7 : 19 + q];
         if (PL) {
-            o.dir_pl[3 * v + q] = f[24 + q];
-            o.l_pl[3 * v + q] = f[28 + q];
+            o.dir_pl[3 * v + q] = f[22 + q];
+            o.l_pl[3 * v + q] = f[25 + q];
         }
     }
 }
@@ -560,7 +579,7 @@ struct TraceWs {
     uint32_t* next;    // the path queue's counter
     uint32_t* count;
     uint32_t* part;
-    float4* rec;       // kRec (kRecPl) pieces per slot
+    Slab slab;
     Out fb;            // the extra samples' arrays
     float* ecam;
 };
@@ -575,7 +594,8 @@ static TraceWs carve_trace(Carver& cv, const pg_tracer* t) {
     w.next = cv.take<uint32_t>(64);
     w.count = cv.take<uint32_t>(P + 1);
     w.part = cv.take<uint32_t>(scan_partials_bytes(P + 1) / 4);
-    w.rec = cv.take<float4>(S * (pl ? kRecPl : kRec));
+    w.slab.rec = cv.take<float4>(S * (pl ? kRecPl : kRec));
+    w.slab.tail = pl ? nullptr : cv.take<float2>(S);
     w.fb = Out{};
     w.fb.fb_l_sun = F ? cv.take<float>(F) : nullptr;
     w.fb.fb_dir_env = F ? cv.take<float>(F) : nullptr;
@@ -604,7 +624,7 @@ hipError_t run_trace_count(const pg_tracer* t, int64_t* path_offsets, float* e_c
         const dim3 grid((unsigned)std::min<int64_t>(kTraceBlocks, div_up(P, kBlock)));
         auto go = [&](auto pl, auto extra) {
             hipLaunchKernelGGL((k_trace<decltype(pl)::value, decltype(extra)::value>), grid, dim3(kBlock), 0, s, tr,
-                               (uint32_t)P, w.next, w.count, w.rec, w.fb, w.ecam);
+                               (uint32_t)P, w.next, w.count, w.slab, w.fb, w.ecam);
         };
         const bool extra = t->extra_samples > 0;
         if (tr.point_light && extra) go(std::true_type{}, std::true_type{});
@@ -636,10 +656,10 @@ hipError_t run_trace_write(const pg_tracer* t, const int64_t* path_offsets, cons
     const dim3 grid((unsigned)div_up(P * maxd, kBlock));
     if (tr.point_light)
         hipLaunchKernelGGL(k_trace_compact<true>, grid, dim3(kBlock), 0, s, P, maxd, path_offsets,
-                           (const uint32_t*)w.count, (const float4*)w.rec, out, w.flag);
+                           (const uint32_t*)w.count, w.slab, out, w.flag);
     else
         hipLaunchKernelGGL(k_trace_compact<false>, grid, dim3(kBlock), 0, s, P, maxd, path_offsets,
-                           (const uint32_t*)w.count, (const float4*)w.rec, out, w.flag);
+                           (const uint32_t*)w.count, w.slab, out, w.flag);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = hipMemcpyAsync(o.e_cam, w.ecam, (size_t)P * 12, hipMemcpyDeviceToDevice, s)) != hipSuccess) return e;
     if (t->extra_samples > 0) {
