@@ -170,8 +170,8 @@ void carve_order(Carver& cv, GridBufs& g, int64_t N, int shift) {
 }
 
 void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift) {
+    g.flag = cv.take<int32_t>(64);   // right before the counts: one fill clears both
     carve_order(cv, g, N, shift);
-    g.flag = cv.take<int32_t>(64);
     g.range = cv.take<uint2>(g.ncells);
     g.pts = cv.take<float4>(N);
     g.qs = reinterpret_cast<uint64_t*>(g.pts);
@@ -179,32 +179,39 @@ void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift) {
     g.nredo = cv.take<uint32_t>(64);
 }
 
-// quantise, count, scan, scatter: perm and inv, and what else is asked for.
-// flag (nullable) receives kFlagPos.
-hipError_t run_order(const pg_paths* p, GridBufs& g, int32_t* flag, hipStream_t s) {
-    const int64_t N = p->n_vertices;
+static hipError_t order_rest(const pg_paths* p, GridBufs& g, hipStream_t s) {
     hipError_t e;
-    if ((e = launch_fill(g.cells, (size_t)(g.ncells + 1) * 4, s)) != hipSuccess) return e;
-    if ((e = launch_quantize_count(N, p->pos, g.shift, g.cells, g.cellid, g.rank, flag, s)) != hipSuccess) return e;
     if ((e = launch_scan_exclusive(g.cells, g.cells, g.ncells, g.partials, s)) != hipSuccess) return e;
-    return launch_scatter(N, *p, g.cellid, g.rank, g.cells, g.perm, g.inv, g.out_qs, g.out_pts, g.out_rec, s);
+    return launch_scatter(p->n_vertices, *p, g.cellid, g.rank, g.cells, g.perm, g.inv, g.out_qs, g.out_pts, g.out_rec,
+                          s);
 }
 
-// rec may be NULL; with recp the records are packed in path order first and
-// gathered into the sorted order.
+// quantise, count, scan, scatter: perm and inv of the spatial order alone.
+hipError_t run_order(const pg_paths* p, GridBufs& g, hipStream_t s) {
+    hipError_t e;
+    if ((e = launch_fill(g.cells, (size_t)(g.ncells + 1) * 4, s)) != hipSuccess) return e;
+    if ((e = launch_quantize_count(p->n_vertices, p->pos, g.shift, g.cells, g.cellid, g.rank, nullptr, s)) !=
+        hipSuccess)
+        return e;
+    return order_rest(p, g, s);
+}
+
+// The grid with its error flag.  rec may be NULL; with recp the records are
+// packed in path order first and gathered into the sorted order.
 hipError_t run_grid(const pg_paths* p, GridBufs& g, GridFor use, VRec* rec, hipStream_t s, VRec* recp) {
     const int64_t N = p->n_vertices;
     hipError_t e;
-    if ((e = launch_fill(g.flag, 64 * sizeof(int32_t), s)) != hipSuccess) return e;
+    const size_t clear = (size_t)(reinterpret_cast<char*>(g.cells + g.ncells + 1) - reinterpret_cast<char*>(g.flag));
+    if ((e = launch_fill(g.flag, clear, s)) != hipSuccess) return e;
     const bool knn = use == GridFor::kNeighbours, packed = rec && recp;
     g.out_qs = knn ? nullptr : g.qs;
     g.out_pts = knn ? g.pts : nullptr;
     g.out_rec = packed ? nullptr : rec;
-    if ((e = run_order(p, g, g.flag, s)) != hipSuccess) return e;
+    e = packed ? launch_count_pack(N, *p, g.shift, g.cells, g.cellid, g.rank, recp, g.flag, s)
+               : launch_quantize_count(N, p->pos, g.shift, g.cells, g.cellid, g.rank, g.flag, s);
+    if (e != hipSuccess || (e = order_rest(p, g, s)) != hipSuccess) return e;
     if (knn && (e = launch_cell_range(g.ncells, g.shift, g.cells, g.range, s)) != hipSuccess) return e;
-    if (!packed) return hipSuccess;
-    if ((e = launch_pack_records(N, *p, recp, g.flag, s)) != hipSuccess) return e;
-    return launch_gather_records(N, g.perm, recp, rec, s);
+    return packed ? launch_gather_records(N, g.perm, recp, rec, s) : hipSuccess;
 }
 
 int shift_of(const pg_params* q, int64_t N) { return q && q->cell_shift ? q->cell_shift : default_shift(N); }
@@ -285,7 +292,7 @@ static pg_status propagate_in_order(const pg_paths* p, const pg_params* q, PropB
     GridBufs& g = b.g;
     hipError_t e;
     // any positions give an order, so none is reported here
-    if ((e = run_order(p, g, nullptr, s)) != hipSuccess) return hip_fail(e, "order");
+    if ((e = run_order(p, g, s)) != hipSuccess) return hip_fail(e, "order");
     if ((e = launch_relayout(N, K, g.perm, g.inv, col, w, bc, lplus, b.alpha, b.succ, b.scol, b.sw, b.sb, b.sx,
                              b.salpha, b.ssucc, s)) != hipSuccess)
         return hip_fail(e, "relayout");

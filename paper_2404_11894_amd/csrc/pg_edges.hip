@@ -111,6 +111,9 @@ __global__ __launch_bounds__(kBlock) void k_edges(int64_t N, Consts c, const int
         }
     }
     if (row_ok && lane == 0) {
+        if (o.succ) o.succ[i] = -1;
+        if (o.pred) o.pred[i] = -1;
+        if (o.x0) st3(o.x0, i, f3{0.f, 0.f, 0.f});
         // aggregated direct: sun (delta light, weight 1/K per neighbour) + MIS'd records
         const float rho_sun = c.rho(one_minus_cos(ti, c.sun));
         const float invK = 1.0f / (float)K;
@@ -160,7 +163,7 @@ hipError_t launch_edges(int64_t N, const Consts& c, const int32_t* col, const VR
 // holds vertex hi - c, a wave-level inclusive scan composes the lanes' maps
 // (F(L) = A + B L; F2 o F1 = (A2 + B2 A1, B2 B1)), and each lane applies
 // the composition of the lanes above it to the value arriving at the chunk.
-// succ, pred and x0 must be pre-filled with -1, -1, 0.
+// succ, pred and x0 must hold -1, -1, 0 (k_edges or fills).
 __global__ __launch_bounds__(kBlock) void k_paths(int64_t P, int64_t N, const int64_t* __restrict__ off,
                                                   const int32_t* __restrict__ inv, const float* __restrict__ alpha,
                                                   const float* __restrict__ dpt, const float* __restrict__ r,

@@ -27,17 +27,22 @@ __device__ inline uint32_t quant(float x) {
     return (uint32_t)s;
 }
 
+__device__ __forceinline__ void count_vertex(int64_t i, float x, float y, float z, int shift,
+                                             uint32_t* __restrict__ count, uint32_t* __restrict__ cellid,
+                                             uint32_t* __restrict__ rank, int32_t* flag) {
+    if (!(x >= 0.0f && x <= 1.0f && y >= 0.0f && y <= 1.0f && z >= 0.0f && z <= 1.0f)) set_flag(flag, kFlagPos);
+    uint32_t c = hilbert3(quant(x) >> shift, quant(y) >> shift, quant(z) >> shift, kQBits - shift);
+    cellid[i] = c;
+    rank[i] = atomicAdd(&count[c], 1u);
+}
+
 __global__ __launch_bounds__(kBlock) void k_quantize_count(int64_t N, const float* __restrict__ pos, int shift,
                                                            uint32_t* __restrict__ count,
                                                            uint32_t* __restrict__ cellid,
                                                            uint32_t* __restrict__ rank, int32_t* flag) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
-    float x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2];
-    if (!(x >= 0.0f && x <= 1.0f && y >= 0.0f && y <= 1.0f && z >= 0.0f && z <= 1.0f)) set_flag(flag, kFlagPos);
-    uint32_t c = hilbert3(quant(x) >> shift, quant(y) >> shift, quant(z) >> shift, kQBits - shift);
-    cellid[i] = c;
-    rank[i] = atomicAdd(&count[c], 1u);
+    count_vertex(i, pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], shift, count, cellid, rank, flag);
 }
 
 hipError_t launch_quantize_count(int64_t N, const float* pos, int shift, uint32_t* count, uint32_t* cellid,
@@ -162,11 +167,41 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t* in, uint32
     if (base < n && base + kScanItems >= n) out[n] = ex;
 }
 
+// The whole scan in one block, tile by tile: one launch instead of three where
+// there is little to scan (4096 cells: 2 us instead of 3 x 3).
+constexpr int64_t kScanOne = 8 * kScanTile;
+__global__ __launch_bounds__(kBlock) void k_scan_one(const uint32_t* in, uint32_t* out, int64_t n) {
+    uint32_t carry = 0;
+    for (int64_t tile = 0; tile < n; tile += kScanTile) {
+        const int64_t base = tile + (int64_t)threadIdx.x * kScanItems;
+        uint32_t v[kScanItems];
+        uint32_t s = 0;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            v[k] = (base + k < n) ? in[base + k] : 0u;
+            s += v[k];
+        }
+        uint32_t total;
+        uint32_t ex = block_exclusive(s, total) + carry;   // its barriers order the reads before the writes
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            if (base + k < n) out[base + k] = ex;
+            ex += v[k];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) out[n] = carry;
+}
+
 size_t scan_partials_bytes(int64_t n) { return (size_t)(div_up(n, kScanTile) + 1) * sizeof(uint32_t); }
 
 hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials,
                                  hipStream_t s) {
     if (n <= 0) return hipErrorInvalidValue;
+    if (n <= kScanOne) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kBlock), 0, s, in, out, n);
+        return hipGetLastError();
+    }
     int64_t nb = div_up(n, kScanTile);
     hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kBlock), 0, s, in, n, partials);
     hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kBlock), 0, s, partials, nb);
@@ -251,6 +286,27 @@ __global__ __launch_bounds__(kBlock) void k_pack_records(int64_t N, pg_paths P, 
     VRec r;
     fill_record(P, v, r);
     store_record(rec + v, r);
+}
+
+// k_quantize_count and k_pack_records in one pass over the vertices: the
+// atomics' latency passes behind the copy of the records, one launch less.
+__global__ __launch_bounds__(kBlock) void k_count_pack(int64_t N, pg_paths P, int shift, uint32_t* __restrict__ count,
+                                                       uint32_t* __restrict__ cellid, uint32_t* __restrict__ rank,
+                                                       VRec* __restrict__ rec, int32_t* flag) {
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= N) return;
+    count_vertex(v, P.pos[3 * v], P.pos[3 * v + 1], P.pos[3 * v + 2], shift, count, cellid, rank, flag);
+    VRec r;
+    fill_record(P, v, r);
+    store_record(rec + v, r);
+}
+
+hipError_t launch_count_pack(int64_t N, const pg_paths& paths, int shift, uint32_t* count, uint32_t* cellid,
+                             uint32_t* rank, VRec* rec, int32_t* flag, hipStream_t s) {
+    if (N == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_count_pack, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, paths, shift, count,
+                       cellid, rank, rec, flag);
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(kBlock) void k_alpha(int64_t N, pg_paths P, float* __restrict__ alpha) {
@@ -757,9 +813,13 @@ hipError_t launch_knn(int64_t N, int K, int shift, const float4* pts, const int3
                       int64_t* row_ptr, uint32_t* redo, uint32_t* nredo, bool exact_only, hipStream_t s) {
     if (N == 0) return hipSuccess;
     const int m = K - 1;
-    hipError_t e = launch_fill(nredo, sizeof(uint32_t), s);
-    if (e != hipSuccess) return e;
     const KeyFmt f = key_fmt(N);
+    // below 2^21 vertices a key holds any distance in the cube: no query is redone
+    const bool redone = exact_only || f.sat <= 3ull * kQMax * kQMax;
+    if (redone) {
+        hipError_t e = launch_fill(nredo, sizeof(uint32_t), s);
+        if (e != hipSuccess) return e;
+    }
     auto go = [&](auto km) {
         constexpr int KM = decltype(km)::value;
         constexpr int WPE = KM <= 16 ? 6 : 1;
@@ -768,7 +828,8 @@ hipError_t launch_knn(int64_t N, int K, int shift, const float4* pts, const int3
         else
             hipLaunchKernelGGL((k_knn<KM, WPE>), dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, K,
                                shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, redo, nredo, f);
-        hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, (const uint32_t*)redo,
+        if (redone)
+            hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, (const uint32_t*)redo,
                            (const uint32_t*)nredo);
     };
     // k = 8..17 get a list of exactly K-1 keys: a sentinel slot costs its

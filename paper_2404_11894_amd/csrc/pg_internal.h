@@ -489,6 +489,8 @@ struct Consts {
 // grid build: quantise + histogram, exclusive scan, scatter into cell order
 hipError_t launch_quantize_count(int64_t N, const float* pos, int shift, uint32_t* count, uint32_t* cellid,
                                  uint32_t* rank, int32_t* flag, hipStream_t s);
+hipError_t launch_count_pack(int64_t N, const pg_paths& paths, int shift, uint32_t* count, uint32_t* cellid,
+                             uint32_t* rank, VRec* rec, int32_t* flag, hipStream_t s);
 size_t scan_partials_bytes(int64_t n);
 hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, uint32_t* partials,
                                  hipStream_t s);
@@ -516,6 +518,9 @@ struct EdgeOut {
     float* dpt;          // [N] f3 local
     float* r;            // [N] local
     float* alpha;        // [N] local
+    int32_t* succ;       // [N] local each, nullable: set to -1, -1 and 0 for the path pass, which
+    int32_t* pred;       //   writes the vertices its paths cover
+    float* x0;           // [N] f3
     const int32_t* canon_row;
     const float* emit;   // volume emission e, [N] f3 in canonical (path) order, nullable
     const float* dir_pl; // point light (canonical order), nullable

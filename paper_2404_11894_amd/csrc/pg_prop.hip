@@ -470,49 +470,66 @@ hipError_t launch_spmv_shifted(int64_t N, int K, const int32_t* succ, const int3
 }
 
 // ------------------------------------------------------------- pixels ---
-// One thread per pixel; its spp paths are consecutive.  o_p as in the
-// "Final output" paragraph with the non-aggregated direct term at the first
-// vertex ("Handling direct Light") -- or the estimate of the extra samples
-// recorded there -- and that vertex's volume emission.  inv == NULL: local ids are path-order
-// ids; r == NULL / alpha == NULL: computed from the path records.
+// o_p as in the "Final output" paragraph with the non-aggregated direct term at
+// the first vertex ("Handling direct Light") -- or the estimate of the extra
+// samples recorded there -- and that vertex's volume emission.  inv == NULL:
+// local ids are path-order ids; r == NULL / alpha == NULL: computed from the
+// path records.
+//
+// S groups of KP lanes per pixel, inside one wave: group g takes the samples g,
+// g + S, ... of the pixel, lane l of it the l-th neighbour of the sample's first
+// vertex.  Bound by the latency of offset -> id -> neighbour -> value: one
+// thread per pixel walked spp K such chains (31 us for 4096 pixels at 4 samples,
+// k = 8; 886 us for 512 x 512 at k = 16); with the neighbours and samples side
+// by side a wave waits for one (MEASURED us).
+template <int KP, int S>
 __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const int32_t* __restrict__ inv,
                                                    const int32_t* __restrict__ col, const float* __restrict__ w,
                                                    const float* __restrict__ x, const float* __restrict__ dpt,
                                                    const float* __restrict__ r, const float* __restrict__ alpha,
                                                    float* __restrict__ image, int32_t* flag) {
-    const int64_t px = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int W = KP * S;   // lanes per pixel, a power of two <= 64
+    const int64_t px = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / W;
+    const int lane = threadIdx.x % KP, grp = threadIdx.x % W / KP;
     const int64_t npix = (int64_t)P.width * P.height;
-    if (px >= npix) return;
     const int64_t N = P.n_vertices;
     const int K = c.K;
     float sx = 0.0f, sy = 0.0f, sz = 0.0f;
-    for (int k = 0; k < P.spp; ++k) {
+    for (int k0 = 0; k0 < P.spp; k0 += S) {   // the same trips on every lane: all take part in the sums
+        const int k = k0 + grp;
         const int64_t p = px * P.spp + k;
-        sx += P.e_cam[3 * p];
-        sy += P.e_cam[3 * p + 1];
-        sz += P.e_cam[3 * p + 2];
-        const int64_t a = P.path_offsets[p], e = P.path_offsets[p + 1];
-        if (e <= a) continue;
-        if (a < 0 || e > N) {
-            set_flag(flag, kFlagOffsets);
-            continue;
+        const bool path = px < npix && k < P.spp;
+        int64_t a = 0;
+        bool on = false;
+        if (path) {
+            a = P.path_offsets[p];
+            const int64_t e = P.path_offsets[p + 1];
+            on = e > a;
+            if (on && (a < 0 || e > N)) {
+                if (lane == 0) set_flag(flag, kFlagOffsets);
+                on = false;
+            }
         }
-        const int64_t s0 = inv ? (int64_t)inv[a] : a;
+        const int64_t s0 = on ? (inv ? (int64_t)inv[a] : a) : 0;
         float ix = 0.0f, iy = 0.0f, iz = 0.0f;
         if (c.final_gather == 0) {
-            for (int l = 0; l < K; ++l) {
-                const int64_t e = inv ? eidx(s0, l, K) : s0 * K + l;
+            if (on && lane < K) {
+                const int64_t e = inv ? eidx(s0, lane, K) : s0 * K + lane;
                 const int64_t j = col[e];
                 if (j < 0 || j >= N) {
                     set_flag(flag, kFlagIndex);
-                    continue;
+                } else {
+                    const float ww = w[e];
+                    const f3 xv = ld3(x, j);
+                    ix = ww * xv.x;
+                    iy = ww * xv.y;
+                    iz = ww * xv.z;
                 }
-                const float ww = w[e];
-                ix = fmaf(ww, x[3 * j], ix);
-                iy = fmaf(ww, x[3 * j + 1], iy);
-                iz = fmaf(ww, x[3 * j + 2], iz);
             }
-        } else {
+            ix = group_sum<KP>(ix);
+            iy = group_sum<KP>(iy);
+            iz = group_sum<KP>(iz);
+        } else if (on && lane == 0) {
             float rr;
             if (r) {
                 rr = r[s0];
@@ -525,6 +542,13 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
             iy = rr * x[3 * s0 + 1];
             iz = rr * x[3 * s0 + 2];
         }
+        if (lane != 0) continue;
+        if (path) {
+            sx += P.e_cam[3 * p];
+            sy += P.e_cam[3 * p + 1];
+            sz += P.e_cam[3 * p + 2];
+        }
+        if (!on) continue;
         float al;
         if (alpha) {
             al = alpha[s0];
@@ -548,6 +572,14 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
         sy = fmaf(al, dd.y + iy, sy);
         sz = fmaf(al, dd.z + iz, sz);
     }
+    // the groups' sums (held by their lanes 0)
+#pragma unroll
+    for (int o = KP; o < W; o <<= 1) {
+        sx += __shfl_xor(sx, o, kWave);
+        sy += __shfl_xor(sy, o, kWave);
+        sz += __shfl_xor(sz, o, kWave);
+    }
+    if (px >= npix || lane != 0 || grp != 0) return;
     const float inv_spp = 1.0f / (float)P.spp;
     image[3 * px] = sx * inv_spp;
     image[3 * px + 1] = sy * inv_spp;
@@ -559,8 +591,17 @@ hipError_t launch_pixels(const pg_paths& paths, const Consts& c, const int32_t* 
                          float* image, int32_t* flag, hipStream_t s) {
     const int64_t npix = (int64_t)paths.width * paths.height;
     if (npix == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pixels, dim3((unsigned)div_up(npix, kBlock)), dim3(kBlock), 0, s, paths, c, inv, col, w,
-                       x, dpt, r, alpha, image, flag);
+    auto go = [&](auto kp, auto sg) {
+        constexpr int KP = decltype(kp)::value, S = decltype(sg)::value;
+        hipLaunchKernelGGL((k_pixels<KP, S>), dim3((unsigned)div_up(npix * KP * S, kBlock)), dim3(kBlock), 0, s, paths,
+                           c, inv, col, w, x, dpt, r, alpha, image, flag);
+    };
+    dispatch_kp(c.K, [&](auto kp) {   // up to four samples side by side, as many as fit a wave
+        constexpr int KP = decltype(kp)::value, S4 = KP <= 16 ? 4 : 64 / KP, S2 = KP <= 32 ? 2 : 1;
+        if (paths.spp >= 3) go(kp, std::integral_constant<int, S4>{});
+        else if (paths.spp == 2) go(kp, std::integral_constant<int, S2>{});
+        else go(kp, std::integral_constant<int, 1>{});
+    });
     return hipGetLastError();
 }
 

@@ -111,6 +111,10 @@ hipError_t render_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, co
     o.emit = p->l_emit;
     o.dir_pl = p->dir_pl;
     o.l_pl = p->l_pl;
+    float* x0 = r.tape ? r.traj : r.x;
+    o.succ = r.succ;
+    o.pred = r.pred;
+    o.x0 = x0;
     if (out) {
         o.w_ind = out->w_ind;
         o.w_ph = out->w_ph;
@@ -126,10 +130,6 @@ hipError_t render_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, co
         ProfScope ps(s, "compact_ids");
         PG_TRY(launch_c16_build(N, K, r.col, r.c16, r.c16_cnt, r.c16_base, r.c16_part, r.c16_ovf, s));
     }
-    float* x0 = r.tape ? r.traj : r.x;
-    PG_TRY(launch_fill_value(r.succ, (size_t)N * 4, 0xffffffffu, s));
-    if (r.pred) PG_TRY(launch_fill_value(r.pred, (size_t)N * 4, 0xffffffffu, s));
-    PG_TRY(launch_fill(x0, (size_t)N * 12, s));
     {
         ProfScope ps(s, "paths");
         PG_TRY(launch_paths(r.P, N, p->path_offsets, g.inv, r.alpha, r.dpt, r.r, p->l_emit, q->init, r.succ, r.pred, x0,
