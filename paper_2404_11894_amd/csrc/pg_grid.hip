@@ -563,8 +563,14 @@ struct KnnScratch {
 // nothing that could enter the list is dropped.
 // Neighbour lists with the grid build, before and after: 20M vertices (k = 16)
 // 17.0 -> 13.1 ms; 64M vertices at the default cells 103 -> 60 ms; 29 thousand
-// (k = 8) 0.190 -> 0.119 ms.
-template <int KM>
+// (k = 8) 0.190 -> 0.070 ms, with four lanes a query (one: 0.115).
+//
+// SUB > 1 (few queries): a launch that leaves the chip half idle lasts as long as
+// one wave's walk, so SUB neighbouring lanes share a query.  All test the same
+// cells; each reads every SUB-th candidate of a range into a list of its own.
+// After the seeds and after each pass over cells the lists are merged for the
+// bound that the group goes on with, and in the end for the result.
+template <int KM, int SUB>
 struct KnnSearch {
     const float4* __restrict__ pts;
     const uint2* __restrict__ cells;
@@ -573,8 +579,49 @@ struct KnnSearch {
     uint32_t lo, nwin;      // seeded index range: [lo, lo + nwin]
     float bound;            // not below the worst kept squared distance; inf until the list is full
     int nr, np;             // queued ranges, pending candidates
+    int m, sub;             // keys wanted, lane of the query's group
     uint64_t k[KM];
     KnnScratch* sc;
+
+    __device__ __forceinline__ float reach(uint64_t worst) const {
+        return worst == ~0ull ? INFINITY : (float)(worst >> f.idb) * (1.0f + 0x1p-20f);
+    }
+
+    // g = the KM smallest keys of the group's lists (every lane the same).  Of two
+    // ascending lists the smaller of g[p] and o[KM - 1 - p] are the KM smallest, up
+    // and then down; half-cleaners of a power of two sort them, as if smaller keys
+    // that never move stood before them.
+    __device__ __forceinline__ void merge_group(uint64_t (&g)[KM]) const {
+        constexpr int P = KM <= 1 ? 1 : KM <= 2 ? 2 : KM <= 4 ? 4 : KM <= 8 ? 8 : KM <= 16 ? 16 : KM <= 32 ? 32 : 64;
+#pragma unroll
+        for (int p = 0; p < KM; ++p) g[p] = k[p];
+#pragma unroll
+        for (int step = 1; step < SUB; step <<= 1) {
+            uint64_t o[KM];
+#pragma unroll
+            for (int p = 0; p < KM; ++p) o[p] = __shfl_xor((unsigned long long)g[p], step, kWave);
+            for (int i = m; i < KM; ++i) {   // without the other's leading zeros
+#pragma unroll
+                for (int p = 0; p + 1 < KM; ++p) o[p] = o[p + 1];
+                o[KM - 1] = ~0ull;
+            }
+#pragma unroll
+            for (int p = 0; p < KM; ++p) g[p] = g[p] < o[KM - 1 - p] ? g[p] : o[KM - 1 - p];
+#pragma unroll
+            for (int h = P / 2; h > 0; h >>= 1) {
+#pragma unroll
+                for (int i = P - KM; i + h < P; ++i) {
+                    if ((i & h) == 0) {
+                        const int a = i - (P - KM), b = a + h;
+                        const bool swap = g[b] < g[a];
+                        const uint64_t lower = swap ? g[b] : g[a], upper = swap ? g[a] : g[b];
+                        g[a] = lower;
+                        g[b] = upper;
+                    }
+                }
+            }
+        }
+    }
 
     // Reads the queued ranges, one candidate per lane and step, and lets those
     // within the bound into the list.  The one place where the list grows: it is
@@ -594,7 +641,7 @@ struct KnnSearch {
             const bool take = d2 <= bound && r.x - lo > nwin;
             if (take) sc->pend[np][tid] = r.x;
             np += take ? 1 : 0;
-            if (++r.x >= r.y) {
+            if ((r.x += SUB) >= r.y) {
                 p.x = NAN;
                 r.y = ~0u;
                 if (++i < nr) r = sc->range[i][tid];
@@ -612,7 +659,7 @@ struct KnnSearch {
                     const uint64_t key = make_key(c.x - qx, c.y - qy, c.z - qz, __float_as_uint(c.w), f);
                     key_insert<KM>(k, has ? key : ~0ull);
                 } while (__any(np > keep));
-                bound = k[KM - 1] == ~0ull ? INFINITY : (float)(k[KM - 1] >> f.idb) * (1.0f + 0x1p-20f);
+                bound = fminf(bound, reach(k[KM - 1]));
             }
             if (!more) break;
         }
@@ -620,6 +667,7 @@ struct KnnSearch {
     }
 
     __device__ __forceinline__ void queue(uint32_t a, uint32_t e) {
+        a += (uint32_t)sub;   // 0 without groups
         if (a < e) sc->range[nr++][threadIdx.x] = make_uint2(a, e);
     }
 
@@ -655,6 +703,11 @@ struct KnnSearch {
         bool pass_end = true;
         for (;;) {
             drain(pass_end);
+            if (SUB > 1 && pass_end && stage > 0) {
+                uint64_t g[KM];
+                merge_group(g);
+                bound = fminf(bound, reach(g[KM - 1]));
+            }
             if (pass_end) {
                 if (stage == 0) {
                     queue(a2, a1);
@@ -725,22 +778,25 @@ struct KnnSearch {
     static __device__ __forceinline__ int zigzag(int i) { return (i & 1) ? -((i + 1) >> 1) : (i >> 1); }
 };
 
+// SUB: lanes a query, a power of two.
 // WPE: the minimum waves per SIMD the compiler must fit the search in: 6 for
 // lists of up to 16 keys (80 registers, nothing spilled; 7 and 8 spill and are
 // 2% and 13% slower at k = 16, 5 is 4% slower); longer lists take no bound.
-template <int KM, int WPE>
+template <int KM, int WPE, int SUB>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) void k_knn(
     int64_t N, int K, int shift, const float4* __restrict__ pts, const int32_t* __restrict__ inv,
     const uint2* __restrict__ cell_range, int32_t* __restrict__ col_sorted, int32_t* __restrict__ col_canon,
     int64_t* __restrict__ row_ptr, uint32_t* __restrict__ redo, uint32_t* __restrict__ nredo, const KeyFmt f) {
     __shared__ KnnScratch scratch;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t s = tile * blockDim.x + threadIdx.x;
+    const int64_t s = (tile * kBlock + threadIdx.x) / SUB;
     if (s >= N) return;
     const int m = K - 1;
     const float4 q = pts[s];
     const uint32_t self = __float_as_uint(q.w);
-    KnnSearch<KM> ks;
+    KnnSearch<KM, SUB> ks;
+    ks.m = m;
+    ks.sub = SUB > 1 ? (int)(threadIdx.x % SUB) : 0;
     ks.pts = pts;
     ks.cells = cell_range;
     ks.f = f;
@@ -751,6 +807,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
 #pragma unroll
     for (int p = 0; p < KM; ++p) ks.k[p] = p < KM - m ? 0ull : ~0ull;
     if (m > 0) ks.run((uint32_t)N, (uint32_t)s, shift);
+    if (SUB > 1) {
+        uint64_t g[KM];
+        ks.merge_group(g);
+#pragma unroll
+        for (int p = 0; p < KM; ++p) ks.k[p] = g[p];
+        if (ks.sub != 0) return;   // the lists are all the same: the group's first lane writes
+    }
     const bool sat = m > 0 && (ks.k[KM - 1] >> f.idb) >= f.sat;   // a kept distance saturated: redo exactly
     const uint32_t slot = wave_append(nredo, sat);
     if (sat) {
@@ -820,17 +883,38 @@ hipError_t launch_knn(int64_t N, int K, int shift, const float4* pts, const int3
         hipError_t e = launch_fill(nredo, sizeof(uint32_t), s);
         if (e != hipSuccess) return e;
     }
-    auto go = [&](auto km) {
-        constexpr int KM = decltype(km)::value;
-        constexpr int WPE = KM <= 16 ? 6 : 1;
+    auto launch = [&](auto km, auto sub) {
+        constexpr int KM = decltype(km)::value, SUB = decltype(sub)::value;
+        constexpr int WPE = KM <= 16 && SUB == 1 ? 6 : 1;
         if (exact_only)
             hipLaunchKernelGGL(k_redo_all, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, redo, nredo);
         else
-            hipLaunchKernelGGL((k_knn<KM, WPE>), dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, K,
+            hipLaunchKernelGGL((k_knn<KM, WPE, SUB>), dim3((unsigned)div_up(N * SUB, kBlock)), dim3(kBlock), 0, s, N, K,
                                shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, redo, nredo, f);
         if (redone)
             hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, (const uint32_t*)redo,
                            (const uint32_t*)nredo);
+    };
+    // The fewer queries, the more lanes to each: a small launch lasts as long as its
+    // slowest wave, a large one as long as its instructions, of which groups take
+    // more.  Lists with the grid build, 1 / 2 / 4 / 8 lanes a query:
+    //   N = 3 thousand, k = 16    0.229  0.145  0.098  0.073 ms   (N K = 2^15.6)
+    //       10 thousand, 8        0.155  0.104  0.094  0.093      (2^16.3)
+    //       29 thousand, 16       0.146  0.113  0.106  0.127      (2^18.8)
+    //       60 thousand, 16       0.243  0.224  0.252  0.283      (2^19.9)
+    //       120 thousand, 16      0.273  0.247  0.310  0.370      (2^20.9)
+    //       240 thousand, 16      0.514  0.503  0.633  0.749      (2^21.9)
+    //       480 thousand, 8       0.438  0.457  0.538  0.741      (2^21.9)
+    // Lists longer than 16 keys stay with one lane: merging needs two in registers.
+    auto go = [&](auto km) {
+        constexpr int KM = decltype(km)::value;
+        const int64_t work = N * K;
+        if constexpr (KM <= 16) {
+            if (work <= int64_t(1) << 16) return launch(km, std::integral_constant<int, 8>{});
+            if (work <= int64_t(1) << 19) return launch(km, std::integral_constant<int, 4>{});
+            if (work <= int64_t(1) << 21) return launch(km, std::integral_constant<int, 2>{});
+        }
+        return launch(km, std::integral_constant<int, 1>{});
     };
     // k = 8..17 get a list of exactly K-1 keys: a sentinel slot costs its
     // compare and selects in every insertion
