@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 
 #include "pg_api_common.h"
 
@@ -264,7 +265,7 @@ static void carve_propagate(Carver& cv, PropBufs& b, const pg_paths* p, const pg
 
 // Whether the iterations run in the sorted order.  The move costs about 300 ns a
 // row at K = 16 and an iteration there saves 160 ns a row once L is far larger
-// than the caches (5M vertices: path order 1034 us an iteration, sorted 188 us,
+// than the caches (5M vertices: path order 987 us an iteration, sorted 188 us,
 // the move 1.6 ms), less below: both orders took the same time at D = 16 with
 // 270 thousand vertices, D = 7 with 540 thousand and D = 4 with 1.1M, all about
 // kSortedMinWork edge updates (K = 8 and 24 likewise).  Fewer vertices than
@@ -287,13 +288,14 @@ static size_t propagate_bytes(const pg_paths* p, const pg_params* q, bool sorted
 size_t propagate_size(const pg_paths* p, const pg_params* q) { return propagate_bytes(p, q, false); }
 
 static pg_status propagate_in_order(const pg_paths* p, const pg_params* q, PropBufs& b, int K, const int32_t* col,
-                                    const float* w, const float* bc, float* lplus, float* traj, hipStream_t s) {
+                                    const float* w, const float* bc, const float* alpha, float* lplus, float* traj,
+                                    hipStream_t s) {
     const int64_t N = p->n_vertices;
     GridBufs& g = b.g;
     hipError_t e;
     // any positions give an order, so none is reported here
     if ((e = run_order(p, g, s)) != hipSuccess) return hip_fail(e, "order");
-    if ((e = launch_relayout(N, K, g.perm, g.inv, col, w, bc, lplus, b.alpha, b.succ, b.scol, b.sw, b.sb, b.sx,
+    if ((e = launch_relayout(N, K, g.perm, g.inv, col, w, bc, lplus, alpha, b.succ, b.scol, b.sw, b.sb, b.sx,
                              b.salpha, b.ssucc, s)) != hipSuccess)
         return hip_fail(e, "relayout");
     if ((e = launch_c16_build(N, K, b.scol, b.c16, b.c16_cnt, b.c16_base, b.c16_part, b.c16_ovf, s, b.start)) !=
@@ -328,24 +330,37 @@ pg_status propagate_run(const pg_paths* paths, const pg_params* params, const in
     PropBufs pb;
     carve_propagate(cv, pb, paths, params, sorted);
     int32_t *flag = pb.flag, *succ = pb.succ;
-    float *alpha = pb.alpha, *y = pb.y;
     hipError_t e;
-    if ((e = launch_fill(flag, 64 * 4, s)) != hipSuccess) return hip_fail(e, "fill");
+    if ((params->flags & PG_FLAG_CHECK) && (e = launch_fill(flag, 64 * 4, s)) != hipSuccess)
+        return hip_fail(e, "fill");   // read back only with the check
     if ((st = check_knn_layout(params, N, K, row_ptr, flag, s))) return st;
     if (N == 0) return finish(s, params, flag, params->flags);
     if ((e = launch_fill_value(succ, (size_t)N * 4, 0xffffffffu, s)) != hipSuccess) return hip_fail(e, "fill");
     if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, nullptr, nullptr, nullptr, nullptr, PG_INIT_ZERO,
                           succ, nullptr, nullptr, flag, s)) != hipSuccess)
         return hip_fail(e, "paths");
-    if ((e = launch_alpha(N, *paths, alpha, s)) != hipSuccess) return hip_fail(e, "alpha");
+    const float* alpha = paths->albedo;
+    if (paths->albedo_grid) {
+        if ((e = launch_alpha(N, *paths, pb.alpha, s)) != hipSuccess) return hip_fail(e, "alpha");
+        alpha = pb.alpha;
+    }
     if (sorted) {
-        if ((st = propagate_in_order(paths, params, pb, K, col, w_ind, b, lplus, traj, s))) return st;
+        if ((st = propagate_in_order(paths, params, pb, K, col, w_ind, b, alpha, lplus, traj, s))) return st;
         return finish(s, params, flag, params->flags);
     }
+    // lplus and y in turn, so that the last iteration ends in lplus: of an odd
+    // number the first one is a product into y and a shift back
+    float *x = lplus, *next = pb.y;
     for (int t = 1; t <= params->D; ++t) {
-        if ((e = launch_spmv(N, K, col, w_ind, lplus, b, alpha, y, s)) != hipSuccess) return hip_fail(e, "spmv");
-        if ((e = launch_shift(N, succ, y, lplus, s)) != hipSuccess) return hip_fail(e, "shift");
-        if (traj && (e = hipMemcpyAsync(traj + (size_t)(t - 1) * N * 3, lplus, (size_t)N * 12,
+        const bool two_pass = t == 1 && params->D % 2 == 1;
+        if ((e = launch_spmv(N, K, col, w_ind, x, b, alpha, two_pass ? nullptr : succ, next, s)) != hipSuccess)
+            return hip_fail(e, "spmv");
+        if (two_pass) {
+            if ((e = launch_shift(N, succ, next, x, s)) != hipSuccess) return hip_fail(e, "shift");
+        } else {
+            std::swap(x, next);
+        }
+        if (traj && (e = hipMemcpyAsync(traj + (size_t)(t - 1) * N * 3, x, (size_t)N * 12,
                                         hipMemcpyDeviceToDevice, s)) != hipSuccess)
             return hip_fail(e, "hipMemcpyAsync");
     }

@@ -542,7 +542,7 @@ hipError_t launch_paths(int64_t P, int64_t N, const int64_t* off, const int32_t*
 
 // propagation
 hipError_t launch_spmv(int64_t N, int K, const int32_t* col, const float* w, const float* x, const float* b,
-                       const float* alpha, float* y, hipStream_t s);
+                       const float* alpha, const int32_t* succ, float* y, hipStream_t s);
 // the same product over the sliced-ELL layout, one thread per row
 // (tile: workgroup size, tile_group: consecutive tiles per XCD; 0 = defaults)
 hipError_t launch_spmv_ell(int64_t N, int K, const int32_t* col, const float* w, const float* x, const float* b,
