@@ -183,8 +183,7 @@ void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift) {
 static hipError_t order_rest(const pg_paths* p, GridBufs& g, hipStream_t s) {
     hipError_t e;
     if ((e = launch_scan_exclusive(g.cells, g.cells, g.ncells, g.partials, s)) != hipSuccess) return e;
-    return launch_scatter(p->n_vertices, *p, g.cellid, g.rank, g.cells, g.perm, g.inv, g.out_qs, g.out_pts, g.out_rec,
-                          s);
+    return launch_scatter(p->n_vertices, *p, g.cellid, g.rank, g.cells, g.perm, g.inv, g.out_qs, g.out_pts, s);
 }
 
 // quantise, count, scan, scatter: perm and inv of the spatial order alone.
@@ -197,22 +196,21 @@ hipError_t run_order(const pg_paths* p, GridBufs& g, hipStream_t s) {
     return order_rest(p, g, s);
 }
 
-// The grid with its error flag.  rec may be NULL; with recp the records are
-// packed in path order first and gathered into the sorted order.
+// The grid with its error flag; with recp also the records packed in path order,
+// with rec too these gathered into the sorted order.
 hipError_t run_grid(const pg_paths* p, GridBufs& g, GridFor use, VRec* rec, hipStream_t s, VRec* recp) {
     const int64_t N = p->n_vertices;
     hipError_t e;
     const size_t clear = (size_t)(reinterpret_cast<char*>(g.cells + g.ncells + 1) - reinterpret_cast<char*>(g.flag));
     if ((e = launch_fill(g.flag, clear, s)) != hipSuccess) return e;
-    const bool knn = use == GridFor::kNeighbours, packed = rec && recp;
+    const bool knn = use == GridFor::kNeighbours;
     g.out_qs = knn ? nullptr : g.qs;
     g.out_pts = knn ? g.pts : nullptr;
-    g.out_rec = packed ? nullptr : rec;
-    e = packed ? launch_count_pack(N, *p, g.shift, g.cells, g.cellid, g.rank, recp, g.flag, s)
-               : launch_quantize_count(N, p->pos, g.shift, g.cells, g.cellid, g.rank, g.flag, s);
+    e = recp ? launch_count_pack(N, *p, g.shift, g.cells, g.cellid, g.rank, recp, g.flag, s)
+             : launch_quantize_count(N, p->pos, g.shift, g.cells, g.cellid, g.rank, g.flag, s);
     if (e != hipSuccess || (e = order_rest(p, g, s)) != hipSuccess) return e;
     if (knn && (e = launch_cell_range(g.ncells, g.shift, g.cells, g.range, s)) != hipSuccess) return e;
-    return packed ? launch_gather_records(N, g.perm, recp, rec, s) : hipSuccess;
+    return rec ? launch_gather_records(N, g.perm, recp, rec, s) : hipSuccess;
 }
 
 int shift_of(const pg_params* q, int64_t N) { return q && q->cell_shift ? q->cell_shift : default_shift(N); }

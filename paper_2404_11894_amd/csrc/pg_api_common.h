@@ -90,7 +90,6 @@ struct GridBufs {
     // what the scatter writes besides perm and inv (each nullable)
     uint64_t* out_qs = nullptr;
     float4* out_pts = nullptr;
-    VRec* out_rec = nullptr;
 };
 
 void carve_order(Carver& cv, GridBufs& g, int64_t N, int shift);
@@ -116,9 +115,7 @@ struct ClusterBufs {
     uint32_t* gpart = nullptr;
     uint32_t* gcell = nullptr;       // by sorted id (centres only): grid cell, rank in it
     uint32_t* grank = nullptr;
-    uint64_t* gq = nullptr;          // centres in grid order: packed position,
-    int32_t* gs = nullptr;           //   sorted id
-    int32_t* gpid = nullptr;         //   path id
+    float4* gpts = nullptr;        // the centres by grid cell: quantised position, sorted id in w (its bits)
     int32_t* cid = nullptr;          // sorted id of the vertex's centre
     uint32_t* ccount = nullptr;      // members per centre [N+1]
     uint32_t* cstart = nullptr;      // first member of each centre's group [N+1]
@@ -136,6 +133,7 @@ struct ClusterBufs {
     uint64_t* stage_q = nullptr;
     int32_t* cperm = nullptr;        // position -> sorted id
     int32_t* cinv = nullptr;         // path id -> position
+    uint64_t* heads = nullptr;     // [N / 64] bit i % 64 of word i / 64: a cluster begins at position i
     uint2* crange = nullptr;         // position -> [first, end) position of its cluster
 };
 void carve_clusters(Carver& cv, ClusterBufs& cb, int64_t N, int K);

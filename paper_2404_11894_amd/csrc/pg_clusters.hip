@@ -138,82 +138,99 @@ __global__ __launch_bounds__(kBlock) void k_cg_scatter(int64_t N, const int32_t*
                                                        const uint64_t* __restrict__ qs,
                                                        const uint32_t* __restrict__ gcell,
                                                        const uint32_t* __restrict__ grank,
-                                                       const uint32_t* __restrict__ gstart, uint64_t* __restrict__ gq,
-                                                       int32_t* __restrict__ gs, int32_t* __restrict__ gpid) {
+                                                       const uint32_t* __restrict__ gstart,
+                                                       float4* __restrict__ gpts) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= N) return;
-    const int32_t pid = perm[s];
-    if (!is_centre(pid, key, thr, kmin)) return;
-    const uint32_t pos = gstart[gcell[s]] + grank[s];
-    gq[pos] = qs[s];
-    gs[pos] = (int32_t)s;
-    gpid[pos] = pid;
+    if (!is_centre(perm[s], key, thr, kmin)) return;
+    int32_t x, y, z;
+    qunpack(qs[s], x, y, z);
+    gpts[gstart[gcell[s]] + grank[s]] = make_float4((float)x, (float)y, (float)z, __int_as_float((int32_t)s));
 }
 
-// Nearest centre of every vertex: rings of cells at Chebyshev distance r
-// around the vertex's cell, r = 0, 1, ....  A cell whose box is farther than
-// the best distance so far is skipped (one at exactly that distance is read:
-// a tie may win on its path id).  After ring r every unvisited centre is at
-// least `gap` quantisation steps away on some axis, so the search ends once
-// the best squared distance is below gap^2.
+// Nearest centre of every vertex: the 27 cells around the vertex's cell, then
+// rings of cells at Chebyshev distance r = 2, 3, ....  A row of cells along x is one
+// contiguous range of centres.  Rows whose box is farther than the best distance
+// so far are skipped, and the cells at the ends of the first ones (one at
+// exactly that distance is read: a tie may win on its path id).  After ring r
+// every unvisited centre is at least `gap` quantisation steps away on some axis,
+// so the search ends once the best squared distance is below gap^2.
+//
+// Bound by the latency of its short loops: by rows, nearest first, a vertex takes
+// 9 lookups at most instead of 27.  Steps are whole numbers below 2^21, so
+// differences are exact in single precision; squares there are rounded by less
+// than 2^-21 and only decide, against a bound raised by 2^-20, what is looked at
+// in double precision, where every sum of squares is exact.  20M vertices: 2.39 ->
+// 1.40 ms (cell by cell in 64-bit integers before; cell by cell as here 2.09).
 __global__ __launch_bounds__(kBlock) void k_nearest_centre(int64_t N, const uint64_t* __restrict__ qs, int b,
                                                            const uint32_t* __restrict__ gstart,
-                                                           const uint64_t* __restrict__ gq,
-                                                           const int32_t* __restrict__ gs,
-                                                           const int32_t* __restrict__ gpid,
+                                                           const float4* __restrict__ gpts,
+                                                           const int32_t* __restrict__ perm,
                                                            int32_t* __restrict__ cid, int32_t* flag) {
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= N) return;
-    const uint64_t q = qs[s];
-    int32_t qx, qy, qz;
-    qunpack(q, qx, qy, qz);
-    const int sh = kQBits - b;
-    const int side = 1 << b;
-    const int cx = qx >> sh, cy = qy >> sh, cz = qz >> sh;
-    int64_t bd = INT64_MAX;
-    int32_t bp = INT32_MAX, bs = -1;
-    const int64_t cw = (int64_t)1 << sh;   // cell width in quantisation steps
-    for (int r = 0; r < side; ++r) {
-        for (int dz = -r; dz <= r; ++dz) {
-            const int z = cz + dz;
-            if (z < 0 || z >= side) continue;
-            const int64_t gz = dz < 0 ? (int64_t)qz - ((int64_t)(z + 1) * cw - 1) : (dz > 0 ? (int64_t)z * cw - qz : 0);
-            for (int dy = -r; dy <= r; ++dy) {
-                const int y = cy + dy;
-                if (y < 0 || y >= side) continue;
-                const int64_t gy = dy < 0 ? (int64_t)qy - ((int64_t)(y + 1) * cw - 1) : (dy > 0 ? (int64_t)y * cw - qy : 0);
-                const bool face = dz == -r || dz == r || dy == -r || dy == r;
-                const int step = face ? 1 : 2 * r;
-                for (int dx = -r; dx <= r; dx += step) {
-                    const int x = cx + dx;
-                    if (x < 0 || x >= side) continue;
-                    const int64_t gx = dx < 0 ? (int64_t)qx - ((int64_t)(x + 1) * cw - 1) : (dx > 0 ? (int64_t)x * cw - qx : 0);
-                    if (gx * gx + gy * gy + gz * gz > bd) continue;   // the whole cell is farther
-                    const uint32_t cell = ((uint32_t)z << (2 * b)) | ((uint32_t)y << b) | (uint32_t)x;
-                    const uint32_t e1 = gstart[cell + 1];
-                    for (uint32_t e = gstart[cell]; e < e1; ++e) {
-                        const int64_t d2 = qdist2(q, gq[e]);
-                        const int32_t p = gpid[e];
-                        if (near_less(d2, p, bd, bp)) {
+    int32_t ix, iy, iz;
+    qunpack(qs[s], ix, iy, iz);
+    const float qx = (float)ix, qy = (float)iy, qz = (float)iz;
+    const int sh = kQBits - b, side = 1 << b;
+    const int cx = ix >> sh, cy = iy >> sh, cz = iz >> sh;
+    const float cw = (float)(1 << sh);   // cell width in quantisation steps
+    // steps to the neighbouring cells on either side of each axis, and to those at offset d
+    const float lx = (float)(ix - (cx << sh) + 1), ly = (float)(iy - (cy << sh) + 1), lz = (float)(iz - (cz << sh) + 1);
+    const float hx = cw + 1.0f - lx, hy = cw + 1.0f - ly, hz = cw + 1.0f - lz;
+    auto gap1 = [&](int d, float l, float h) {
+        return d == 0 ? 0.0f : (d < 0 ? l + (float)(-d - 1) * cw : h + (float)(d - 1) * cw);
+    };
+    double bd = INFINITY;
+    float bound = INFINITY;   // not below bd
+    int32_t bs = -1;
+    for (int r = 1;; ++r) {
+        const int rin = r > 1 ? r - 1 : -1;   // the cube already searched
+        for (int kz = 0; kz <= 2 * r; ++kz) {
+            const int dz = (kz & 1) ? -((kz + 1) >> 1) : kz >> 1, z = cz + dz;   // 0, -1, 1, ...
+            if ((uint32_t)z >= (uint32_t)side) continue;
+            const float gz = gap1(dz, lz, hz), gzz = gz * gz;
+            if (gzz > bound) continue;
+            for (int ky = 0; ky <= 2 * r; ++ky) {
+                const int dy = (ky & 1) ? -((ky + 1) >> 1) : ky >> 1, y = cy + dy;
+                if ((uint32_t)y >= (uint32_t)side) continue;
+                const float gy = gap1(dy, ly, hy), gyz = fmaf(gy, gy, gzz);
+                if (gyz > bound) continue;
+                const bool holed = abs(dz) <= rin && abs(dy) <= rin;
+                const bool left = fmaf(gap1(-r, lx, hx), gap1(-r, lx, hx), gyz) <= bound && cx - r >= 0;
+                const bool right = fmaf(gap1(r, lx, hx), gap1(r, lx, hx), gyz) <= bound && cx + r < side;
+                const uint32_t* row = gstart + ((z << (2 * b)) | (y << b));
+                for (int part = 0; part <= (int)holed; ++part) {   // the whole row, or its two ends
+                    const int x0 = holed ? (part ? cx + r : cx - r) : max(left ? cx - r : cx - r + 1, 0);
+                    const int x1 = holed ? x0 : min(right ? cx + r : cx + r - 1, side - 1);
+                    if (holed && !(part ? right : left)) continue;
+                    const uint32_t e1 = row[x1 + 1];
+                    for (uint32_t e = row[x0]; e < e1; ++e) {
+                        const float4 c = gpts[e];
+                        const float ex = c.x - qx, ey = c.y - qy, ez = c.z - qz;
+                        if (fmaf(ex, ex, fmaf(ey, ey, ez * ez)) > bound) continue;
+                        const double d2 = fma((double)ex, (double)ex, fma((double)ey, (double)ey, (double)ez * (double)ez));
+                        const int32_t cs = __float_as_int(c.w);
+                        if (d2 < bd || (d2 == bd && perm[cs] < perm[bs])) {
                             bd = d2;
-                            bp = p;
-                            bs = gs[e];
+                            bound = (float)d2 * (1.0f + 0x1p-20f);
+                            bs = cs;
                         }
                     }
                 }
             }
         }
         // smallest per-axis distance from q to a cell outside the searched cube
-        int64_t gap = INT64_MAX;
-        const int c3[3] = {cx, cy, cz};
-        const int64_t q3[3] = {qx, qy, qz};
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            if (c3[a] - r > 0) gap = min(gap, q3[a] - (int64_t)(c3[a] - r) * cw + 1);
-            if (c3[a] + r < side - 1) gap = min(gap, (int64_t)(c3[a] + r + 1) * cw - q3[a]);
-        }
-        if (gap == INT64_MAX) break;                // the whole grid was searched
-        if (bs >= 0 && bd < gap * gap) break;       // provably final
+        float gap = INFINITY;
+        const float rc = (float)r * cw;
+        if (cx - r > 0) gap = fminf(gap, lx + rc);
+        if (cx + r < side - 1) gap = fminf(gap, hx + rc);
+        if (cy - r > 0) gap = fminf(gap, ly + rc);
+        if (cy + r < side - 1) gap = fminf(gap, hy + rc);
+        if (cz - r > 0) gap = fminf(gap, lz + rc);
+        if (cz + r < side - 1) gap = fminf(gap, hz + rc);
+        if (gap == INFINITY) break;                                  // the whole grid was searched
+        if (bs >= 0 && bd < (double)gap * (double)gap) break;        // provably final
     }
     if (bs < 0) set_flag(flag, kFlagCluster);
     cid[s] = bs < 0 ? (int32_t)s : bs;
@@ -461,13 +478,16 @@ __global__ __launch_bounds__(kBlock) void k_corder(int64_t N, const int32_t* __r
     }
 }
 
-// Records in cluster order, plus (t, alpha) packed for the iteration.
+// Records gathered from path order into cluster order, plus (t, alpha) packed for
+// the iteration.  Moving a record once, by an 80-byte read, took 20M vertices
+// 3.4 ms with the packing; scattered into the sorted order first, 4.3 ms.
 __global__ __launch_bounds__(kBlock) void k_crec(int64_t N, const int32_t* __restrict__ cperm,
-                                                 const VRec* __restrict__ rec, VRec* __restrict__ crec,
-                                                 float4* __restrict__ tq, float* __restrict__ alpha) {
+                                                 const int32_t* __restrict__ perm, const VRec* __restrict__ rec,
+                                                 VRec* __restrict__ crec, float4* __restrict__ tq,
+                                                 float* __restrict__ alpha) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
-    const float4* src = reinterpret_cast<const float4*>(rec + cperm[i]);
+    const float4* src = reinterpret_cast<const float4*>(rec + perm[cperm[i]]);
     float4* dst = reinterpret_cast<float4*>(crec + i);
     float4 a0 = src[0], a1 = src[1], a2 = src[2], a3 = src[3], a4 = src[4];
     dst[0] = a0;
@@ -479,19 +499,90 @@ __global__ __launch_bounds__(kBlock) void k_crec(int64_t N, const int32_t* __res
     alpha[i] = a4.z;
 }
 
+// ----------------------------------------------- the members of a block ---
+
+// The kernels over the members of clusters run one thread per row.  The clusters of a block's
+// rows cover one contiguous span of positions (its rows plus the parts of the
+// first and last cluster outside the block); when the span fits kSpan, what the
+// rows read of their members is staged in LDS once, with coalesced loads, and
+// every row sums from there.
+//
+// The iteration is bound by memory (20M vertices: 1.5 GB an iteration in order, 310 us at
+// the rate of a copy, and a gather), so a row's range comes from the bits of the heads,
+// one word a wave, instead of 8 bytes a row, and what a row reads of its own is
+// requested before the staging's barrier: 401 -> 361 us.
+constexpr int kSpan = 512;
+
+struct Span {
+    uint32_t lo, n;   // the block's
+    uint2 rg;         // the row's (undefined past the last row)
+};
+
+// The last head in the words up to w, the first in those from w on; N past the
+// end.  h: word w, requested before (a cluster rarely reaches further).
+__device__ __forceinline__ uint32_t last_head(const uint64_t* __restrict__ heads, uint64_t h, int64_t w) {
+    while (h == 0 && w > 0) h = heads[--w];
+    return h ? (uint32_t)w * kWave + (63u - (uint32_t)__clzll((long long)h)) : 0u;
+}
+__device__ __forceinline__ uint32_t next_head(const uint64_t* __restrict__ heads, uint64_t h, int64_t w, int64_t N) {
+    const int64_t nw = div_up(N, kWave);
+    while (h == 0 && ++w < nw) h = heads[w];
+    return h ? (uint32_t)w * kWave + (uint32_t)__ffsll((unsigned long long)h) - 1u : (uint32_t)N;
+}
+
+__device__ __forceinline__ Span block_span(const uint64_t* __restrict__ heads, int64_t i0, int64_t N) {
+    constexpr int W = kBlock / kWave;
+    const int64_t w0 = i0 / kWave, nw = div_up(N, kWave);
+    uint64_t h[W + 2];   // the block's words and one on either side, at once; 0 outside
+#pragma unroll
+    for (int u = 0; u < W + 2; ++u) h[u] = w0 + u > 0 && w0 + u - 1 < nw ? heads[w0 + u - 1] : 0ull;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+    uint64_t prev = h[0], cur = h[1], next = h[2];
+#pragma unroll
+    for (int u = 1; u < W; ++u) {
+        prev = wave == u ? h[u] : prev;
+        cur = wave == u ? h[u + 1] : cur;
+        next = wave == u ? h[u + 2] : next;
+    }
+    const int64_t w = w0 + wave;
+    const uint32_t lane = threadIdx.x % kWave, i = (uint32_t)i0 + threadIdx.x;
+    Span sp;
+    sp.lo = (h[1] & 1) ? (uint32_t)i0 : last_head(heads, h[0], w0 - 1);
+    sp.n = next_head(heads, h[W + 1], w0 + W, N) - sp.lo;
+    const uint32_t before = (cur & 1) ? (uint32_t)(w * kWave) : last_head(heads, prev, w - 1);
+    const uint32_t after = next_head(heads, next, w + 1, N);
+    const uint64_t at = cur & (~0ull >> (63u - lane)), past = lane == 63u ? 0ull : cur >> (lane + 1u);
+    sp.rg = bounded(make_uint2(at ? i - (lane + (uint32_t)__clzll((long long)at) - 63u) : before,
+                               past ? i + (uint32_t)__ffsll((unsigned long long)past) : after));
+    return sp;
+}
+
+// HG_g(t, w) / c_g = ((1-g)^2 + g |t - w|^2)^(-3/2), the receiver's phase
+// without its constant (which the member's wq.w carries).
+__device__ __forceinline__ float hg_shape(const HG& rho, f3 t, float wx, float wy, float wz) {
+    const float dx = t.x - wx, dy = t.y - wy, dz = t.z - wz;
+    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    const float r = __frsqrt_rn(fmaf(0.5f * rho.two_g, d2, rho.a));
+    return r * r * r;
+}
+
 // --------------------------------------------------------- the weights ---
 
 // First pass: the marginals of every vertex's own samples over its cluster,
 //   M+(w_i) = sum_l p_l(w_i),  Me(we_i) = sum_l p_l(we_i) + C p_e,
 // stored as wq = (w_i, c_g / M+) with c_g = (1 - g^2) / (4 pi) the HG
-// constant, mp = M+ + C p_e, me = Me.
+// constant, mp = M+ + C p_e, me = Me.  heads gets the bits of the positions where
+// a cluster begins (and of those past the end).
 __global__ __launch_bounds__(kBlock) void k_cmarg(int64_t N, Consts c, const uint2* __restrict__ crange,
                                                   const VRec* __restrict__ crec, const float4* __restrict__ tq,
                                                   float4* __restrict__ wq, float* __restrict__ mp,
-                                                  float* __restrict__ me) {
+                                                  float* __restrict__ me, uint64_t* __restrict__ heads) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint2 all = i < N ? crange[i] : make_uint2((uint32_t)i, (uint32_t)i);
+    const uint64_t head = __ballot(all.x == (uint32_t)i);
     if (i >= N) return;
-    const uint2 rg = bounded(crange[i]);
+    if (__lane_id() == 0) heads[i / kWave] = head;
+    const uint2 rg = bounded(all);
     const VRec& ri = crec[i];
     const f3 w{ri.w[0], ri.w[1], ri.w[2]}, we{ri.we[0], ri.we[1], ri.we[2]};
     float mplus = 0.0f, menv = 0.0f;
@@ -507,34 +598,61 @@ __global__ __launch_bounds__(kBlock) void k_cmarg(int64_t N, Consts c, const uin
     me[i] = menv + Cpe;
 }
 
+// What a receiver reads of a member in the second pass: its samples, the
+// radiances over their marginals.
+struct Member {
+    float4 w, we, le, lp;   // ls in the last parts of the first three
+    __device__ __forceinline__ static Member of(const VRec& r, float mp, float me) {
+        return {make_float4(r.w[0], r.w[1], r.w[2], r.ls[0]), make_float4(r.we[0], r.we[1], r.we[2], r.ls[1]),
+                make_float4(r.le[0] / me, r.le[1] / me, r.le[2] / me, r.ls[2]),
+                make_float4(r.lp[0] / mp, r.lp[1] / mp, r.lp[2] / mp, 0.f)};
+    }
+};
+
 // Second pass, per receiver i over its cluster's samples j:
 //   d_agg_i = rho_i(sun)/C sum_j Ls_j + sum_j rho_i(we_j) Le_j / Me_j + rho_i(w_j) Lp_j / (M+_j + C p_e)
 //   b_i = e_i + alpha_i d_agg_i,  and the own (path-traced) direct term and ratio.
-__global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const uint2* __restrict__ crange,
+// Bound by the instructions of the pairs, so what depends on the member alone is
+// done once, as the members are staged: 20M vertices 1.67 -> 0.71 ms.
+__global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const uint64_t* __restrict__ heads,
                                                    const VRec* __restrict__ crec, const float4* __restrict__ tq,
                                                    const float* __restrict__ mp, const float* __restrict__ me,
                                                    const float* __restrict__ emit, const int32_t* __restrict__ cperm,
                                                    const int32_t* __restrict__ perm, const float* __restrict__ dir_pl,
                                                    const float* __restrict__ l_pl, float* __restrict__ b,
                                                    float* __restrict__ dpt, float* __restrict__ r) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ Member sm[kSpan];
+    const int64_t i0 = (int64_t)blockIdx.x * kBlock, i = i0 + threadIdx.x;
+    const Span sp = block_span(heads, i0, N);
+    const uint2 rg = sp.rg;
+    const uint32_t lo = sp.lo;
+    const bool staged = sp.n <= (uint32_t)kSpan;
+    if (staged) {
+        for (uint32_t t = threadIdx.x; t < sp.n; t += kBlock) sm[t] = Member::of(crec[lo + t], mp[lo + t], me[lo + t]);
+        __syncthreads();
+    }
     if (i >= N) return;
-    const uint2 rg = bounded(crange[i]);
     const float4 t4 = tq[i];
     const f3 ti{t4.x, t4.y, t4.z};
     float cx = 0.f, cy = 0.f, cz = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, qx = 0.f, qy = 0.f, qz = 0.f;
-    for (uint32_t j = rg.x; j < rg.y; ++j) {
-        const VRec& rj = crec[j];
-        const f3 wj{rj.w[0], rj.w[1], rj.w[2]}, wej{rj.we[0], rj.we[1], rj.we[2]};
-        const float fp = c.rho(one_minus_cos(ti, wj)) / mp[j];
-        const float fe = c.rho(one_minus_cos(ti, wej)) / me[j];
-        cx += fe * rj.le[0] + fp * rj.lp[0];
-        cy += fe * rj.le[1] + fp * rj.lp[1];
-        cz += fe * rj.le[2] + fp * rj.lp[2];
-        sx += rj.ls[0];
-        sy += rj.ls[1];
-        sz += rj.ls[2];
-        if (dir_pl) {   // point light: a delta light per member sample, weight 1/C
+    auto add = [&](const Member& m) {
+        const float fp = hg_shape(c.rho, ti, m.w.x, m.w.y, m.w.z), fe = hg_shape(c.rho, ti, m.we.x, m.we.y, m.we.z);
+        cx = fmaf(fe, m.le.x, fmaf(fp, m.lp.x, cx));
+        cy = fmaf(fe, m.le.y, fmaf(fp, m.lp.y, cy));
+        cz = fmaf(fe, m.le.z, fmaf(fp, m.lp.z, cz));
+        sx += m.w.w;
+        sy += m.we.w;
+        sz += m.le.w;
+    };
+    if (staged)
+        for (uint32_t j = rg.x; j < rg.y; ++j) add(sm[j - lo]);
+    else
+        for (uint32_t j = rg.x; j < rg.y; ++j) add(Member::of(crec[j], mp[j], me[j]));
+    cx *= c.rho.c;
+    cy *= c.rho.c;
+    cz *= c.rho.c;
+    if (dir_pl) {   // point light: a delta light per member sample, weight 1/C
+        for (uint32_t j = rg.x; j < rg.y; ++j) {
             const int64_t pj = perm[cperm[j]];
             const float rp = c.rho(one_minus_cos(ti, ld3(dir_pl, pj)));
             const f3 lq = ld3(l_pl, pj);
@@ -572,15 +690,6 @@ __global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const ui
 
 // ------------------------------------------------------- the iteration ---
 
-// HG_g(t, w) / c_g = ((1-g)^2 + g |t - w|^2)^(-3/2), the receiver's phase
-// without its constant (which the member's wq.w carries).
-__device__ __forceinline__ float hg_shape(const HG& rho, f3 t, float wx, float wy, float wz) {
-    const float dx = t.x - wx, dy = t.y - wy, dz = t.z - wz;
-    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    const float r = __frsqrt_rn(fmaf(0.5f * rho.two_g, d2, rho.a));
-    return r * r * r;
-}
-
 // The shape r^3 of hg_shape (r = 1/sqrt(den), den = (1-g)^2 + 2 g u) and,
 // from the same denominator, d ln HG / d g = c0 - 3 (g - 1 + u) / den with
 // c0 = -2g / (1 - g^2) and 1/den = r^2 (rho built from g; gm1 = g - 1).
@@ -609,18 +718,54 @@ __device__ __forceinline__ f3 cluster_gather(const HG& rho, f3 ti, uint2 rg, con
     return f3{zx, zy, zz};
 }
 
-// y_i = b_i + alpha_i sum_j w+_ij x_j, the weights recomputed; one thread
-// per row.  The clusters of a block's rows cover one contiguous span of
-// positions (its rows plus the parts of the first and last cluster outside
-// the block); when the span fits kSpan, the members' (w, 1/M+) and x are
-// staged in LDS once, with coalesced loads, and every row sums from there.
+// a and x of the span into LDS; with SHIFTED x_j = x(succ j), 0 at a path's end.
+// The block's own rows are requested before the span is known (own), then the
+// parts of the first and last cluster outside the block.
+template <bool SHIFTED, bool NT>
+struct Stage {
+    float4 a;
+    f3 x;
+
+    __device__ __forceinline__ void load(int64_t j, const float4* __restrict__ aq, const float* __restrict__ xq,
+                                         const int32_t* __restrict__ succ) {
+        a = NT ? ld4_nt(aq + j) : aq[j];
+        const int64_t from = SHIFTED ? __builtin_nontemporal_load(succ + j) : j;
+        x = from >= 0 ? ld3(xq, from) : f3{0.f, 0.f, 0.f};
+    }
+    __device__ __forceinline__ void store(uint32_t t, float4* sa, float* sx) const {
+        sa[t] = a;
+        sx[3 * t] = x.x;
+        sx[3 * t + 1] = x.y;
+        sx[3 * t + 2] = x.z;
+    }
+};
+
+template <bool SHIFTED, bool NT>
+__device__ __forceinline__ void stage_span(const Span& sp, int64_t i0, int64_t N, const Stage<SHIFTED, NT>& own,
+                                           const float4* __restrict__ aq, const float* __restrict__ xq,
+                                           const int32_t* __restrict__ succ, float4* sa, float* sx) {
+    const uint32_t rows = (uint32_t)(N - i0 < kBlock ? N - i0 : kBlock), first = (uint32_t)i0 - sp.lo;
+    static_assert(kSpan <= 2 * kBlock, "one turn over the margins");
+    if (threadIdx.x < sp.n - rows) {
+        const uint32_t t = threadIdx.x < first ? threadIdx.x : threadIdx.x + rows;
+        Stage<SHIFTED, NT> margin;
+        margin.load((int64_t)sp.lo + t, aq, xq, succ);
+        margin.store(t, sa, sx);
+    }
+    if (threadIdx.x < rows) own.store(first + threadIdx.x, sa, sx);
+}
+
+// y_i = b_i + alpha_i sum_j w+_ij x_j, the weights recomputed.
 //
 // With SHIFTED the propagation is folded in: x is not stored, the members'
 // values are gathered as x_j = y_prev(succ j) (0 at a path's end), so one
 // launch per iteration replaces the aggregation and the shift.
-constexpr int kSpan = 512;
-template <bool SHIFTED>
-__global__ __launch_bounds__(kBlock) void k_cagg(int64_t N, HG rho, const uint2* __restrict__ crange,
+//
+// NT: what is read once an iteration, and what is stored, past the caches
+// (cagg_nt says when).
+enum class Nt { kNone, kLoads, kBoth };
+template <bool SHIFTED, Nt NT>
+__global__ __launch_bounds__(kBlock) void k_cagg(int64_t N, HG rho, const uint64_t* __restrict__ heads,
                                                  const float4* __restrict__ tq, const float4* __restrict__ wq,
                                                  const float* __restrict__ b, const float* __restrict__ x,
                                                  const int32_t* __restrict__ succ, float* __restrict__ y) {
@@ -628,29 +773,22 @@ __global__ __launch_bounds__(kBlock) void k_cagg(int64_t N, HG rho, const uint2*
     __shared__ float sx[3 * kSpan];
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);   // the path neighbours' lines on one L2
     const int64_t i0 = tile * kBlock;
-    const int64_t i = i0 + threadIdx.x;
-    const int64_t ilast = i0 + kBlock - 1 < N ? i0 + kBlock - 1 : N - 1;
-    const uint32_t lo = crange[i0].x, hi = crange[ilast].y;
-    const bool staged = hi - lo <= (uint32_t)kSpan;   // uniform over the block
+    const int64_t i = i0 + threadIdx.x, own = i < N ? i : N - 1;
+    constexpr bool ntl = NT != Nt::kNone;
+    Stage<SHIFTED, ntl> st;
+    st.load(own, wq, x, succ);
+    const float4 t4 = ntl ? ld4_nt(tq + own) : tq[own];
+    const f3 bb = ntl ? ld3_nt(b, own) : ld3(b, own);
+    const Span sp = block_span(heads, i0, N);
+    const uint2 rg = sp.rg;
+    const uint32_t lo = sp.lo;
+    const bool staged = sp.n <= (uint32_t)kSpan;   // uniform over the block
     if (staged) {
-        for (uint32_t t = threadIdx.x; t < hi - lo; t += kBlock) {
-            sw[t] = wq[lo + t];
-            if (SHIFTED) {
-                const int32_t sj = __builtin_nontemporal_load(succ + lo + t);
-                const f3 v = sj >= 0 ? ld3(x, sj) : f3{0.f, 0.f, 0.f};
-                sx[3 * t] = v.x;
-                sx[3 * t + 1] = v.y;
-                sx[3 * t + 2] = v.z;
-            }
-        }
-        if (!SHIFTED)
-            for (uint32_t t = threadIdx.x; t < 3 * (hi - lo); t += kBlock) sx[t] = x[3 * (int64_t)lo + t];
+        stage_span(sp, i0, N, st, wq, x, succ, sw, sx);
         __syncthreads();
     }
     if (i >= N) return;
-    const float4 t4 = tq[i];
     const f3 ti{t4.x, t4.y, t4.z};
-    const uint2 rg = bounded(crange[i]);
     f3 z;
     if (staged) {
         float zx = 0.f, zy = 0.f, zz = 0.f;
@@ -677,8 +815,33 @@ __global__ __launch_bounds__(kBlock) void k_cagg(int64_t N, HG rho, const uint2*
     } else {
         z = cluster_gather(rho, ti, rg, wq, x);
     }
-    const f3 bb = ld3(b, i);
-    st3_nt(y, i, f3{fmaf(t4.w, z.x, bb.x), fmaf(t4.w, z.y, bb.y), fmaf(t4.w, z.z, bb.z)});
+    const f3 yv{fmaf(t4.w, z.x, bb.x), fmaf(t4.w, z.y, bb.y), fmaf(t4.w, z.z, bb.z)};
+    if (NT == Nt::kBoth)
+        st3_nt(y, i, yv);
+    else
+        st3(y, i, yv);
+}
+
+// An iteration reads 48 bytes a vertex in order and gathers from y_prev while it
+// stores y.  While all of it fits the 256 MB cache behind the L2s nothing is
+// sent past it; beyond, the reads in order are, which leaves it to the two y;
+// where these outgrow it too, so are the stores.  Whole renders (D = 64), nothing /
+// the reads / both:  1M vertices 2.06, 2.18, 2.18 ms;  2.5M 4.31, 4.62, 4.76;  5M 9.02,
+// 8.87, 9.14;  10M 18.6, 17.7, 18.3;  20M 36.8, 35.9, 35.5.
+Nt cagg_nt(int64_t N) {
+    constexpr int64_t kCache = int64_t(256) << 20;
+    if (N * (48 + 24) <= kCache) return Nt::kNone;
+    return N * 24 <= kCache ? Nt::kLoads : Nt::kBoth;
+}
+
+template <bool SHIFTED, typename... Args>
+void launch_cagg(int64_t N, hipStream_t s, Args... args) {
+    const dim3 grid((unsigned)div_up(N, kBlock)), block(kBlock);
+    switch (cagg_nt(N)) {
+        case Nt::kNone: hipLaunchKernelGGL((k_cagg<SHIFTED, Nt::kNone>), grid, block, 0, s, N, args...); break;
+        case Nt::kLoads: hipLaunchKernelGGL((k_cagg<SHIFTED, Nt::kLoads>), grid, block, 0, s, N, args...); break;
+        case Nt::kBoth: hipLaunchKernelGGL((k_cagg<SHIFTED, Nt::kBoth>), grid, block, 0, s, N, args...); break;
+    }
 }
 
 // One thread per pixel, as the sliced-ELL output but gathering over the
@@ -886,7 +1049,7 @@ __global__ __launch_bounds__(kBlock) void k_cout_adjoint(pg_paths P, Consts c, c
 // L_{t-1}(j)> (dW/dg = W h) to the block's dL/dg slot.  The block's member
 // span is staged in LDS as in the forward product.
 template <bool SHIFTED>
-__global__ __launch_bounds__(kBlock) void k_crev_rows(int64_t N, HG rho, float g, const uint2* __restrict__ crange,
+__global__ __launch_bounds__(kBlock) void k_crev_rows(int64_t N, HG rho, float g, const uint64_t* __restrict__ heads,
                                                       const float4* __restrict__ tq, const float4* __restrict__ wq,
                                                       const float* __restrict__ x, const int32_t* __restrict__ succ,
                                                       const float* __restrict__ lam, const int32_t* __restrict__ pred,
@@ -896,25 +1059,22 @@ __global__ __launch_bounds__(kBlock) void k_crev_rows(int64_t N, HG rho, float g
     __shared__ float sx[3 * kSpan];
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);   // the path neighbours' lines on one L2
     const int64_t i0 = tile * kBlock;
-    const int64_t i = i0 + threadIdx.x;
-    const int64_t ilast = i0 + kBlock - 1 < N ? i0 + kBlock - 1 : N - 1;
-    const uint32_t lo = crange[i0].x, hi = crange[ilast].y;
-    const bool staged = hi - lo <= (uint32_t)kSpan;
+    const int64_t i = i0 + threadIdx.x, own = i < N ? i : N - 1;
+    Stage<SHIFTED, false> st;
+    st.load(own, wq, x, succ);
+    const float4 t4 = tq[own];
+    const int32_t pv = pred[own];
+    const Span sp = block_span(heads, i0, N);
+    const uint2 rg = sp.rg;
+    const uint32_t lo = sp.lo;
+    const bool staged = sp.n <= (uint32_t)kSpan;
     if (staged) {
-        for (uint32_t t = threadIdx.x; t < hi - lo; t += kBlock) {
-            sw[t] = wq[lo + t];
-            const f3 v = tape_x<SHIFTED>(x, succ, lo + t);
-            sx[3 * t] = v.x;
-            sx[3 * t + 1] = v.y;
-            sx[3 * t + 2] = v.z;
-        }
+        stage_span(sp, i0, N, st, wq, x, succ, sw, sx);
         __syncthreads();
     }
     double gl = 0.0;
     if (i < N) {
-        const float4 t4 = tq[i];
         const f3 ti{t4.x, t4.y, t4.z};
-        const uint2 rg = bounded(crange[i]);
         const float c0 = -2.0f * g / (1.0f - g * g), gm1 = g - 1.0f;
         f3 z{0.f, 0.f, 0.f}, zg{0.f, 0.f, 0.f};
         for (uint32_t j = rg.x; j < rg.y; ++j) {
@@ -927,7 +1087,6 @@ __global__ __launch_bounds__(kBlock) void k_crev_rows(int64_t N, HG rho, float g
             z = f3{fmaf(f, xv.x, z.x), fmaf(f, xv.y, z.y), fmaf(f, xv.z, z.z)};
             zg = f3{fmaf(fh, xv.x, zg.x), fmaf(fh, xv.y, zg.y), fmaf(fh, xv.z, zg.z)};
         }
-        const int32_t pv = pred[i];
         const f3 yb = pv >= 0 ? ld3(lam, pv) : f3{0.f, 0.f, 0.f};
         abar[i] += dot3(yb, z);
         bbar[3 * i] += yb.x;
@@ -943,24 +1102,26 @@ __global__ __launch_bounds__(kBlock) void k_crev_rows(int64_t N, HG rho, float g
 
 // lam_{t-1}(j) = sum_{i in cluster(j)} W_ij zbar_i = (c_g / M+_j) sum_i
 // rho_i(w_j) zbar_i: the receivers' (t_i, zbar_i) of the span in LDS.
-__global__ __launch_bounds__(kBlock) void k_crev_cols(int64_t N, HG rho, const uint2* __restrict__ crange,
+__global__ __launch_bounds__(kBlock) void k_crev_cols(int64_t N, HG rho, const uint64_t* __restrict__ heads,
                                                       const float4* __restrict__ tq, const float4* __restrict__ wq,
                                                       const float* __restrict__ zbar, float* __restrict__ lam) {
     __shared__ float4 st[kSpan];
     __shared__ float sz[3 * kSpan];
     const int64_t j0 = (int64_t)blockIdx.x * kBlock;
     const int64_t j = j0 + threadIdx.x;
-    const int64_t jlast = j0 + kBlock - 1 < N ? j0 + kBlock - 1 : N - 1;
-    const uint32_t lo = crange[j0].x, hi = crange[jlast].y;
-    const bool staged = hi - lo <= (uint32_t)kSpan;
+    const int64_t own = j < N ? j : N - 1;
+    Stage<false, false> sg;
+    sg.load(own, tq, zbar, nullptr);
+    const float4 w4 = wq[own];
+    const Span sp = block_span(heads, j0, N);
+    const uint2 rg = sp.rg;
+    const uint32_t lo = sp.lo;
+    const bool staged = sp.n <= (uint32_t)kSpan;
     if (staged) {
-        for (uint32_t t = threadIdx.x; t < hi - lo; t += kBlock) st[t] = tq[lo + t];
-        for (uint32_t t = threadIdx.x; t < 3 * (hi - lo); t += kBlock) sz[t] = zbar[3 * (int64_t)lo + t];
+        stage_span(sp, j0, N, sg, tq, zbar, nullptr, st, sz);
         __syncthreads();
     }
     if (j >= N) return;
-    const float4 w4 = wq[j];
-    const uint2 rg = bounded(crange[j]);
     float ax = 0.f, ay = 0.f, az = 0.f;
     for (uint32_t i = rg.x; i < rg.y; ++i) {
         const float4 t4 = staged ? st[i - lo] : tq[i];
@@ -1079,9 +1240,7 @@ void carve_clusters(Carver& cv, ClusterBufs& cb, int64_t N, int K) {
     cb.gpart = cv.take<uint32_t>(scan_partials_bytes(cb.ncells + 1) / 4);
     cb.gcell = cv.take<uint32_t>(N);
     cb.grank = cv.take<uint32_t>(N);
-    cb.gq = cv.take<uint64_t>(N);
-    cb.gs = cv.take<int32_t>(N);
-    cb.gpid = cv.take<int32_t>(N);
+    cb.gpts = cv.take<float4>(N);
     cb.cid = cv.take<int32_t>(N);
     cb.ccount = cv.take<uint32_t>(N + 1);
     cb.cstart = cv.take<uint32_t>(N + 1);
@@ -1100,6 +1259,7 @@ void carve_clusters(Carver& cv, ClusterBufs& cb, int64_t N, int K) {
     cb.cperm = cv.take<int32_t>(N);
     cb.cinv = cv.take<int32_t>(N);
     cb.crange = cv.take<uint2>(N);
+    cb.heads = reinterpret_cast<uint64_t*>(cb.gcell);   // gcell is done with when the clusters stand
 }
 
 #define PG_TRY(x)                              \
@@ -1144,12 +1304,12 @@ hipError_t run_clusters(const pg_paths* p, GridBufs& g, ClusterBufs& cb, hipStre
     PG_TRY(hipGetLastError());
     PG_TRY(launch_scan_exclusive(cb.gcount, cb.gcount, cb.ncells + 1, cb.gpart, s));
     hipLaunchKernelGGL(k_cg_scatter, grid_of(N), dim3(kBlock), 0, s, N, g.perm, p->cluster_key, thr, cb.kmin, g.qs,
-                       cb.gcell, cb.grank, cb.gcount, cb.gq, cb.gs, cb.gpid);
+                       cb.gcell, cb.grank, cb.gcount, cb.gpts);
     PG_TRY(hipGetLastError());
     {
         ProfScope ps(s, "nearest_centre");
-        hipLaunchKernelGGL(k_nearest_centre, grid_of(N), dim3(kBlock), 0, s, N, g.qs, cb.bits, cb.gcount, cb.gq,
-                           cb.gs, cb.gpid, cb.cid, g.flag);
+        hipLaunchKernelGGL(k_nearest_centre, grid_of(N), dim3(kBlock), 0, s, N, g.qs, cb.bits, cb.gcount, cb.gpts,
+                           g.perm, cb.cid, g.flag);
         PG_TRY(hipGetLastError());
     }
     // split rounds; round r runs only if round r-1 split something.  The
@@ -1215,18 +1375,19 @@ hipError_t cluster_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, c
     ClusterRender& cr = r.cr;
     {
         ProfScope ps(s, "grid");
-        PG_TRY(run_grid(p, g, GridFor::kClusters, r.rec, s));
+        PG_TRY(run_grid(p, g, GridFor::kClusters, nullptr, s, r.rec));
     }
     PG_TRY(run_clusters(p, g, cb, s));
     const Consts c = make_consts(q, r.K);
     if (N > 0) {
         ProfScope ps(s, "edges");
-        hipLaunchKernelGGL(k_crec, grid_of(N), dim3(kBlock), 0, s, N, cb.cperm, r.rec, cr.crec, cr.tq, r.alpha);
+        hipLaunchKernelGGL(k_crec, grid_of(N), dim3(kBlock), 0, s, N, cb.cperm, g.perm, r.rec, cr.crec, cr.tq,
+                           r.alpha);
         PG_TRY(hipGetLastError());
         hipLaunchKernelGGL(k_cmarg, grid_of(N), dim3(kBlock), 0, s, N, c, cb.crange, cr.crec, cr.tq, cr.wq, cr.mp,
-                           cr.me);
+                           cr.me, cb.heads);
         PG_TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_cedges, grid_of(N), dim3(kBlock), 0, s, N, c, cb.crange, cr.crec, cr.tq, cr.mp, cr.me,
+        hipLaunchKernelGGL(k_cedges, grid_of(N), dim3(kBlock), 0, s, N, c, cb.heads, cr.crec, cr.tq, cr.mp, cr.me,
                            p->l_emit, cb.cperm, g.perm, p->dir_pl, p->l_pl, r.b, r.dpt, r.r);
         PG_TRY(hipGetLastError());
     }
@@ -1274,12 +1435,10 @@ hipError_t cluster_iterate(RenderBufs& r, const pg_params* q, float* x0, hipStre
     for (int t = 1; t <= r.D; ++t) {
         ProfScope ps(s, "spmv");
         if (t == 1) {
-            hipLaunchKernelGGL(k_cagg<false>, grid_of(N), dim3(kBlock), 0, s, N, rho, r.cl.crange, r.cr.tq, r.cr.wq,
-                               r.b, x0, r.succ, yp);
+            launch_cagg<false>(N, s, rho, r.cl.heads, r.cr.tq, r.cr.wq, r.b, x0, r.succ, yp);
         } else {
             if (r.tape) yq = r.traj + (size_t)t * N * 3;
-            hipLaunchKernelGGL(k_cagg<true>, grid_of(N), dim3(kBlock), 0, s, N, rho, r.cl.crange, r.cr.tq, r.cr.wq,
-                               r.b, yp, r.succ, yq);
+            launch_cagg<true>(N, s, rho, r.cl.heads, r.cr.tq, r.cr.wq, r.b, yp, r.succ, yq);
         }
         PG_TRY(hipGetLastError());
         if (t > 1) std::swap(yp, yq);
@@ -1333,15 +1492,15 @@ hipError_t launch_cluster_reverse_step(const RenderBufs& r, const pg_params* q, 
     {
         ProfScope ps(s, "rev_rows");
         if (t == 1)
-            hipLaunchKernelGGL(k_crev_rows<false>, grid_of(N), dim3(kBlock), 0, s, N, rho, q->g, r.cl.crange,
+            hipLaunchKernelGGL(k_crev_rows<false>, grid_of(N), dim3(kBlock), 0, s, N, rho, q->g, r.cl.heads,
                                r.cr.tq, r.cr.wq, x, r.succ, lam, r.pred, abar, bbar, zbar, gpart);
         else
-            hipLaunchKernelGGL(k_crev_rows<true>, grid_of(N), dim3(kBlock), 0, s, N, rho, q->g, r.cl.crange,
+            hipLaunchKernelGGL(k_crev_rows<true>, grid_of(N), dim3(kBlock), 0, s, N, rho, q->g, r.cl.heads,
                                r.cr.tq, r.cr.wq, x, r.succ, lam, r.pred, abar, bbar, zbar, gpart);
         PG_TRY(hipGetLastError());
     }
     ProfScope ps(s, "rev_cols");
-    hipLaunchKernelGGL(k_crev_cols, grid_of(N), dim3(kBlock), 0, s, N, rho, r.cl.crange, r.cr.tq, r.cr.wq, zbar,
+    hipLaunchKernelGGL(k_crev_cols, grid_of(N), dim3(kBlock), 0, s, N, rho, r.cl.heads, r.cr.tq, r.cr.wq, zbar,
                        lam_prev);
     return hipGetLastError();
 }

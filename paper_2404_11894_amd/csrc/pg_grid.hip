@@ -250,8 +250,7 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P,
                                                     const uint32_t* __restrict__ rank,
                                                     const uint32_t* __restrict__ cell_start,
                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv,
-                                                    uint64_t* __restrict__ qsorted, float4* __restrict__ pts,
-                                                    VRec* __restrict__ rec) {
+                                                    uint64_t* __restrict__ qsorted, float4* __restrict__ pts) {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= N) return;
     int64_t s = (int64_t)cell_start[cellid[v]] + rank[v];
@@ -261,19 +260,14 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P,
     const uint32_t qx = quant(P.pos[3 * v]), qy = quant(P.pos[3 * v + 1]), qz = quant(P.pos[3 * v + 2]);
     if (qsorted) qsorted[s] = qpack(qx, qy, qz);
     if (pts) pts[s] = make_float4((float)qx, (float)qy, (float)qz, __int_as_float((int32_t)v));   // exact: below 2^24
-    if (rec) {
-        VRec r;
-        fill_record(P, v, r);
-        store_record(rec + s, r);
-    }
 }
 
 hipError_t launch_scatter(int64_t N, const pg_paths& paths, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
-                          uint64_t* qsorted, float4* pts, VRec* rec, hipStream_t s) {
+                          uint64_t* qsorted, float4* pts, hipStream_t s) {
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, paths, cellid,
-                       rank, cell_start, perm, inv, qsorted, pts, rec);
+                       rank, cell_start, perm, inv, qsorted, pts);
     return hipGetLastError();
 }
 

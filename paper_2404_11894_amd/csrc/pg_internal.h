@@ -169,6 +169,15 @@ __device__ inline void st3(float* p, int64_t i, f3 v) { p[3 * i] = v.x; p[3 * i 
 // Store with the non-temporal hint: the propagation's output vectors are
 // consumed by the next kernel's gathers, which measured faster when these
 // stores do not allocate in the caches on the way out.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ inline float4 ld4_nt(const float4* p) {
+    const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ inline f3 ld3_nt(const float* p, int64_t i) {
+    return f3{__builtin_nontemporal_load(p + 3 * i), __builtin_nontemporal_load(p + 3 * i + 1),
+              __builtin_nontemporal_load(p + 3 * i + 2)};
+}
 __device__ inline void st3_nt(float* p, int64_t i, f3 v) {
     __builtin_nontemporal_store(v.x, p + 3 * i);
     __builtin_nontemporal_store(v.y, p + 3 * i + 1);
@@ -496,7 +505,7 @@ hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, u
                                  hipStream_t s);
 hipError_t launch_scatter(int64_t N, const pg_paths& paths, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
-                          uint64_t* qsorted, float4* pts, VRec* rec, hipStream_t s);
+                          uint64_t* qsorted, float4* pts, hipStream_t s);
 // redo: [N] scratch list, nredo: one counter (queries the fast 64-bit-key
 // search hands to the exact one)
 hipError_t launch_cell_range(int64_t ncells, int shift, const uint32_t* start, uint2* range, hipStream_t s);
