@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kBlock) void k_out_adjoint(pg_paths P, Consts c, co
 // zg_i = sum_l dw_il/dg x(j_l) (z then zg, six floats) for the reverse
 // sweep.  z takes the same slots and FMAs as k_spmv_c16, so y is the same bit
 // for bit; zg the same as the recomputing k_rev_rows.
-template <int KT, int BS>
+template <int KT, int BS, bool NT>
 __global__ __launch_bounds__(BS) void k_spmv_c16_tape(int64_t N, int K, const int16_t* __restrict__ c16,
                                                       const uint32_t* __restrict__ c16_base,
                                                       const int32_t* __restrict__ ovf, const float* __restrict__ w,
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(BS) void k_spmv_c16_tape(int64_t N, int K, const in
     }
     const f3 bb = ld3(b, i);
     const float a = alpha[i];
-    st3_nt(y, i, f3{fmaf(a, ax, bb.x), fmaf(a, ay, bb.y), fmaf(a, az, bb.z)});
+    st3_iter<NT>(y, i, f3{fmaf(a, ax, bb.x), fmaf(a, ay, bb.y), fmaf(a, az, bb.z)});
     st3_nt(zt, 2 * i, f3{ax, ay, az});
     st3_nt(zt, 2 * i + 1, f3{gx, gy, gz});
 }
@@ -424,12 +424,19 @@ hipError_t launch_spmv_c16_tape(int64_t N, int K, const int16_t* c16, const uint
     if (N == 0) return hipSuccess;
     dispatch_tile(tile, [&](auto bs) {
         constexpr int BS = decltype(bs)::value;
-        switch (ell_k4(K)) {
-        case 8: hipLaunchKernelGGL((k_spmv_c16_tape<8, BS>), dim3((unsigned)div_up(N, BS)), dim3(BS), 0, s, N, K, c16, c16_base, ovf, w, gw, x, b, alpha, y, zt, tile_group); break;
-        case 12: hipLaunchKernelGGL((k_spmv_c16_tape<12, BS>), dim3((unsigned)div_up(N, BS)), dim3(BS), 0, s, N, K, c16, c16_base, ovf, w, gw, x, b, alpha, y, zt, tile_group); break;
-        case 16: hipLaunchKernelGGL((k_spmv_c16_tape<16, BS>), dim3((unsigned)div_up(N, BS)), dim3(BS), 0, s, N, K, c16, c16_base, ovf, w, gw, x, b, alpha, y, zt, tile_group); break;
-        default: break;   // not carved for other K4 (see sums_taped)
-        }
+        dispatch_nt(N, [&](auto nt) {
+            constexpr bool NT = decltype(nt)::value;
+            auto go = [&](auto kt) {
+                hipLaunchKernelGGL((k_spmv_c16_tape<decltype(kt)::value, BS, NT>), dim3((unsigned)div_up(N, BS)),
+                                   dim3(BS), 0, s, N, K, c16, c16_base, ovf, w, gw, x, b, alpha, y, zt, tile_group);
+            };
+            switch (ell_k4(K)) {
+            case 8: go(std::integral_constant<int, 8>{}); break;
+            case 12: go(std::integral_constant<int, 12>{}); break;
+            case 16: go(std::integral_constant<int, 16>{}); break;
+            default: break;   // not carved for other K4 (see sums_taped)
+            }
+        });
     });
     return hipGetLastError();
 }
@@ -442,7 +449,7 @@ hipError_t launch_spmv_c16_tape(int64_t N, int K, const int16_t* c16, const uint
 // <zbar_i, sum_l dw_il/dg L_{t-1}(j_l)> to the block's dL/dg slot.  One thread
 // per row over the sliced-ELL edges (all K loads issued before the gathers),
 // as in the forward product.  KT = ell_k4(K) at compile time, 0: runtime.
-template <int KT, bool C16>
+template <int KT, bool C16, bool NT>
 __global__ __launch_bounds__(kBlock) void k_rev_rows(int64_t N, int Kr, const int32_t* __restrict__ col,
                                                      const int16_t* __restrict__ c16,
                                                      const uint32_t* __restrict__ c16_base,
@@ -513,7 +520,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_rows(int64_t N, int Kr, const in
         bbar[3 * i + 2] += yb.z;
         const float al = alpha[i];
         const f3 zb{al * yb.x, al * yb.y, al * yb.z};
-        st3_nt(zbar, i, zb);
+        st3_iter<NT>(zbar, i, zb);
         gl = (double)dot3(zb, f3{gx, gy, gz});
     }
     const double t = block_sum_d(gl);
@@ -523,6 +530,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_rows(int64_t N, int Kr, const in
 // k_rev_rows with z_i and zg_i read from the forward's tape (zt: six floats
 // per row) instead of gathered again: the same values, the same updates and
 // the same block partials, so the same results bit for bit.
+template <bool NT>
 __global__ __launch_bounds__(kBlock) void k_rev_rows_taped(int64_t N, const float* __restrict__ zt,
                                                            const float* __restrict__ lam,
                                                            const int32_t* __restrict__ ppred,
@@ -542,7 +550,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_rows_taped(int64_t N, const floa
         bbar[3 * i + 2] += yb.z;
         const float al = alpha[i];
         const f3 zb{al * yb.x, al * yb.y, al * yb.z};
-        st3_nt(zbar, i, zb);
+        st3_iter<NT>(zbar, i, zb);
         gl = (double)dot3(zb, zg);
     }
     const double t = block_sum_d(gl);
@@ -553,6 +561,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_rows_taped(int64_t N, const floa
 // position r: one thread per position over the sliced-ELL transpose (every
 // lane of a wave runs its slice's length, the zero-weight padding included: a
 // per-lane bound measured slower), eight entries loaded ahead (four: 7% slower).
+template <bool NT>
 __global__ __launch_bounds__(kBlock) void k_rev_cols(int64_t N, const uint32_t* __restrict__ soff,
                                                      const uint2* __restrict__ tent,
                                                      const float* __restrict__ zbar, float* __restrict__ lam) {
@@ -592,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void k_rev_cols(int64_t N, const uint32_t* 
         ay = fmaf(ww, zb.y, ay);
         az = fmaf(ww, zb.z, az);
     }
-    st3_nt(lam, r, f3{ax, ay, az});
+    st3_iter<NT>(lam, r, f3{ax, ay, az});
 }
 
 __global__ __launch_bounds__(kBlock) void k_rev_overflow(const int32_t* __restrict__ ovf, const float* __restrict__ ovw,
@@ -1049,21 +1058,25 @@ hipError_t run_backward(const pg_paths* p, const pg_params* q, RenderBufs& r, Ba
         const float* xprev = r.traj + (size_t)(t - 1) * N * 3;
         if (r.zt) {
             ProfScope ps(s, "rev_rows");
-            hipLaunchKernelGGL(k_rev_rows_taped, dim3((unsigned)bb.n_rows), dim3(kBlock), 0, s, N,
-                               (const float*)(r.zt + (size_t)(t - 1) * N * 6), (const float*)lam,
-                               (const int32_t*)bb.ppred, (const float*)r.alpha, bb.abar, bb.bbar, bb.zbar, g_rows);
+            dispatch_nt(N, [&](auto nt) {
+                hipLaunchKernelGGL(k_rev_rows_taped<decltype(nt)::value>, dim3((unsigned)bb.n_rows), dim3(kBlock), 0, s,
+                                   N, (const float*)(r.zt + (size_t)(t - 1) * N * 6), (const float*)lam,
+                                   (const int32_t*)bb.ppred, (const float*)r.alpha, bb.abar, bb.bbar, bb.zbar, g_rows);
+            });
         } else {
             ProfScope ps(s, "rev_rows");
             auto go = [&](auto kt) {
                 constexpr int KT = decltype(kt)::value;
-                if (KT > 0 && r.c16)
-                    hipLaunchKernelGGL((k_rev_rows<KT, true>), dim3((unsigned)bb.n_rows), dim3(kBlock), 0, s, N, K,
-                                       r.col, r.c16, r.c16_base, r.c16_ovf, r.w, r.gw, xprev, lam, bb.ppred, r.alpha,
-                                       bb.abar, bb.bbar, bb.zbar, g_rows);
-                else
-                    hipLaunchKernelGGL((k_rev_rows<KT, false>), dim3((unsigned)bb.n_rows), dim3(kBlock), 0, s, N, K,
-                                       r.col, r.c16, r.c16_base, r.c16_ovf, r.w, r.gw, xprev, lam, bb.ppred, r.alpha,
-                                       bb.abar, bb.bbar, bb.zbar, g_rows);
+                dispatch_nt(N, [&](auto nt) {
+                    constexpr bool NT = decltype(nt)::value;
+                    auto launch = [&](auto c16) {
+                        hipLaunchKernelGGL((k_rev_rows<KT, decltype(c16)::value, NT>), dim3((unsigned)bb.n_rows),
+                                           dim3(kBlock), 0, s, N, K, r.col, r.c16, r.c16_base, r.c16_ovf, r.w, r.gw,
+                                           xprev, lam, bb.ppred, r.alpha, bb.abar, bb.bbar, bb.zbar, g_rows);
+                    };
+                    if (KT > 0 && r.c16) launch(std::true_type{});
+                    else launch(std::false_type{});
+                });
             };
             switch (ell_k4(K)) {
             case 8: go(std::integral_constant<int, 8>{}); break;
@@ -1074,8 +1087,10 @@ hipError_t run_backward(const pg_paths* p, const pg_params* q, RenderBufs& r, Ba
         }
         {
             ProfScope ps(s, "rev_cols");
-            hipLaunchKernelGGL(k_rev_cols, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, bb.soff,
-                               (const uint2*)bb.tent, bb.zbar, lam_next);
+            dispatch_nt(N, [&](auto nt) {
+                hipLaunchKernelGGL(k_rev_cols<decltype(nt)::value>, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0,
+                                   s, N, bb.soff, (const uint2*)bb.tent, bb.zbar, lam_next);
+            });
             hipLaunchKernelGGL(k_rev_overflow, dim3(64), dim3(kBlock), 0, s, bb.ovf, bb.ovw, bb.novf, bb.tpos,
                                bb.zbar, lam_next);
         }

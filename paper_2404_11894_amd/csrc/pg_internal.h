@@ -166,10 +166,6 @@ struct f3 { float x, y, z; };
 
 __device__ inline f3 ld3(const float* p, int64_t i) { return f3{p[3 * i], p[3 * i + 1], p[3 * i + 2]}; }
 __device__ inline void st3(float* p, int64_t i, f3 v) { p[3 * i] = v.x; p[3 * i + 1] = v.y; p[3 * i + 2] = v.z; }
-// Store with the non-temporal hint: the propagation's output vectors are
-// consumed by the next kernel's gathers, which measured faster when these
-// stores do not allocate in the caches on the way out.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ inline float4 ld4_nt(const float4* p) {
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
     return make_float4(v.x, v.y, v.z, v.w);
@@ -182,6 +178,33 @@ __device__ inline void st3_nt(float* p, int64_t i, f3 v) {
     __builtin_nontemporal_store(v.x, p + 3 * i);
     __builtin_nontemporal_store(v.y, p + 3 * i + 1);
     __builtin_nontemporal_store(v.z, p + 3 * i + 2);
+}
+
+// Whether the two vectors that an iteration over n rows stores in turn, and gathers
+// from in the next kernel, go past the caches on their way out.  Kept, they are
+// found again where they fit one XCD's L2 (4 MB) or else the cache behind all of
+// them (256 MB); in between, and beyond, the stores only displace what is being
+// read.  Renders of 64 iterations, past the caches / kept (K = 16):
+//   29 thousand rows  0.671 / 0.641 ms   100 thousand  0.930 / 0.892
+//   200 thousand  1.358 / 1.382          300 thousand  1.900 / 1.972
+//   500 thousand  2.467 / 2.481          700 thousand  3.10 / 3.06
+//   1M  4.08 / 3.90   2.5M  9.80 / 9.40   5M  17.5 / 16.8
+//   8.5M  31.1 / 31.1                    20M  71.4 / 73.0
+inline bool iter_past_caches(int64_t n) {
+    const int64_t bytes = n * 24;
+    return bytes > (int64_t(200) << 20) || (bytes > (int64_t(4) << 20) && bytes <= (int64_t(12) << 20));
+}
+// The choice is a template parameter NT of the kernels: of two stores in one
+// kernel that differ in nothing but the hint the compiler makes one without it.
+template <typename F>
+inline void dispatch_nt(int64_t n, F&& go) {
+    if (iter_past_caches(n)) go(std::true_type{});
+    else go(std::false_type{});
+}
+template <bool NT>
+__device__ inline void st3_iter(float* p, int64_t i, f3 v) {
+    if constexpr (NT) st3_nt(p, i, v);
+    else st3(p, i, v);
 }
 
 // sum_l w_il x(j_l) for row i of the sliced ELL, over all K4 = ell_k4(K)

@@ -222,7 +222,7 @@ hipError_t launch_c16_build(int64_t N, int K, const int32_t* col, int16_t* c16, 
 // The two-pass aggregation over the compact ids: the same rows, slots and
 // arithmetic as k_spmv_ell, so the same results bit for bit, with 2 bytes per
 // id streamed instead of 4 (plus the few escaped ids).
-template <int KT, int BS>
+template <int KT, int BS, bool NT>
 __global__ __launch_bounds__(BS) void k_spmv_c16(int64_t N, int K, const int16_t* __restrict__ c16,
                                                  const uint32_t* __restrict__ c16_base,
                                                  const int32_t* __restrict__ ovf, const float* __restrict__ w,
@@ -234,7 +234,7 @@ __global__ __launch_bounds__(BS) void k_spmv_c16(int64_t N, int K, const int16_t
     const f3 z = c16_row_sum<KT>(i, K, c16, c16_base, ovf, w, x);
     const f3 bb = ld3(b, i);
     const float a = alpha ? alpha[i] : 1.0f;
-    st3_nt(y, i, f3{fmaf(a, z.x, bb.x), fmaf(a, z.y, bb.y), fmaf(a, z.z, bb.z)});
+    st3_iter<NT>(y, i, f3{fmaf(a, z.x, bb.x), fmaf(a, z.y, bb.y), fmaf(a, z.z, bb.z)});
 }
 
 hipError_t launch_spmv_c16(int64_t N, int K, const int16_t* c16, const uint32_t* c16_base, const int32_t* ovf,
@@ -248,8 +248,10 @@ hipError_t launch_spmv_c16(int64_t N, int K, const int16_t* c16, const uint32_t*
         dispatch_k4(K, [&](auto kt) {
             constexpr int KT = decltype(kt)::value;
             if constexpr (KT > 0)
-                hipLaunchKernelGGL((k_spmv_c16<KT, BS>), grid, block, 0, s, N, K, c16, c16_base, ovf, w, x, b, alpha,
-                                   y, tile_group);
+                dispatch_nt(N, [&](auto nt) {
+                    hipLaunchKernelGGL((k_spmv_c16<KT, BS, decltype(nt)::value>), grid, block, 0, s, N, K, c16,
+                                       c16_base, ovf, w, x, b, alpha, y, tile_group);
+                });
         });
     });
     return hipGetLastError();
@@ -337,7 +339,7 @@ hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t*
 // give the same results bit for bit.  Left to itself the compiler interleaves
 // gathers and products (73 registers at K = 16, 210 us on 5M vertices); with all
 // gathers issued first (86 registers) it takes 141 us.
-template <int KT, int BS>
+template <int KT, int BS, bool NT>
 __global__ __launch_bounds__(BS) void k_spmv_sorted(int64_t N, int K, const int16_t* __restrict__ c16,
                                                     const uint16_t* __restrict__ start,
                                                     const uint32_t* __restrict__ c16_base,
@@ -369,7 +371,7 @@ __global__ __launch_bounds__(BS) void k_spmv_sorted(int64_t N, int K, const int1
         for (int l = 0; l < o; ++l) a[l] = f3{a[l].x + a[l + o].x, a[l].y + a[l + o].y, a[l].z + a[l + o].z};
     const f3 bb = ld3(b, i);
     const float al = alpha[i];
-    st3_nt(y, i, f3{fmaf(al, a[0].x, bb.x), fmaf(al, a[0].y, bb.y), fmaf(al, a[0].z, bb.z)});
+    st3_iter<NT>(y, i, f3{fmaf(al, a[0].x, bb.x), fmaf(al, a[0].y, bb.y), fmaf(al, a[0].z, bb.z)});
 }
 
 hipError_t launch_spmv_sorted(int64_t N, int K, const int16_t* c16, const uint16_t* start, const uint32_t* c16_base,
@@ -380,20 +382,22 @@ hipError_t launch_spmv_sorted(int64_t N, int K, const int16_t* c16, const uint16
     dispatch_k4(K, [&](auto kt) {
         constexpr int KT = decltype(kt)::value;
         if constexpr (KT > 0)
-            hipLaunchKernelGGL((k_spmv_sorted<KT, BS>), dim3((unsigned)div_up(N, BS)), dim3(BS), 0, s, N, K, c16, start,
-                               c16_base, ovf, w, x, b, alpha, y);
+            dispatch_nt(N, [&](auto nt) {
+                hipLaunchKernelGGL((k_spmv_sorted<KT, BS, decltype(nt)::value>), dim3((unsigned)div_up(N, BS)),
+                                   dim3(BS), 0, s, N, K, c16, start, c16_base, ovf, w, x, b, alpha, y);
+            });
     });
     return hipGetLastError();
 }
 
 // L(v) = y(succ v), 0 at a path's end.  Two vertices per thread, strided by
 // the grid so every access stays coalesced, for two independent gathers; the
-// successor ids (read once) are streamed and L is stored non-temporally.
+// successor ids (read once) are streamed.
 // Every load is unconditional (indices clamped to a valid element, the value
 // masked afterwards), so both successor ids and then both gathers are in
 // flight together instead of each waiting at a branch.
 constexpr int kShiftPer = 2;
-template <int BS>
+template <int BS, bool NT>
 __global__ __launch_bounds__(BS) void k_shift(int64_t N, const int32_t* __restrict__ succ,
                                               const float* __restrict__ y, float* __restrict__ x) {
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -416,7 +420,7 @@ __global__ __launch_bounds__(BS) void k_shift(int64_t N, const int32_t* __restri
     for (int k = 0; k < kShiftPer; ++k) {
         const int64_t v = v0 + (int64_t)k * BS;
         if (u[k] < 0) val[k] = f3{0.f, 0.f, 0.f};
-        if (v < N) st3_nt(x, v, val[k]);
+        if (v < N) st3_iter<NT>(x, v, val[k]);
     }
 }
 
@@ -424,8 +428,10 @@ hipError_t launch_shift(int64_t N, const int32_t* succ, const float* y, float* x
     if (N == 0) return hipSuccess;
     dispatch_tile(tile, [&](auto bs) {
         constexpr int BS = decltype(bs)::value;
-        hipLaunchKernelGGL(k_shift<BS>, dim3((unsigned)div_up(N, (int64_t)BS * kShiftPer)), dim3(BS), 0, s, N,
-                           succ, y, x);
+        dispatch_nt(N, [&](auto nt) {
+            hipLaunchKernelGGL((k_shift<BS, decltype(nt)::value>), dim3((unsigned)div_up(N, (int64_t)BS * kShiftPer)),
+                               dim3(BS), 0, s, N, succ, y, x);
+        });
     });
     return hipGetLastError();
 }
