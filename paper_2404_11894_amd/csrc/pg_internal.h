@@ -320,10 +320,16 @@ __device__ __forceinline__ f3 c16_row_sum(int64_t i, int K, const int16_t* __res
     for (int q = 0; q < NQ; ++q) ww[q] = ld_quad_nt(w + base + q * kQuadStride);
     int32_t j[KT];
     c16_row_ids<KT>(i, K, c16, c16_base, ovf, j);
+    f3 xs[KT];
+#pragma unroll
+    for (int l = 0; l < KT; ++l) xs[l] = ld3(x, j[l]);
+    // every gather in flight before the first product: in 128 registers at K = 24,
+    // left to the compiler 132, a wave a SIMD less (5M rows, D = 64: 26.9 -> 25.6 ms)
+    __builtin_amdgcn_sched_barrier(0);
     float ax = 0.f, ay = 0.f, az = 0.f;
 #pragma unroll
     for (int l = 0; l < KT; ++l) {
-        const f3 xv = ld3(x, j[l]);
+        const f3 xv = xs[l];
         const float wl = ww[l >> 2][l & 3];
         ax = fmaf(wl, xv.x, ax);
         ay = fmaf(wl, xv.y, ay);
