@@ -297,7 +297,7 @@ __global__ __launch_bounds__(kBlock) void k_tppred(int64_t N, const int32_t* __r
 // seeds the adjoint of L_D (lam), of alpha, d_pt, r, and dL/dg through the extra
 // samples.  KP lanes per path, lane l its first vertex's l-th neighbour, so the
 // K chains of loads and atomics run side by side (one thread per path: 654 us
-// for 262 thousand paths at k = 16, now 589 us, bound by its atomics).
+// for 262 thousand paths at k = 16, now 571 us, bound by its atomics).
 template <int KP>
 __global__ __launch_bounds__(kBlock) void k_out_adjoint(pg_paths P, Consts c, const int32_t* __restrict__ inv,
                                                         const int32_t* __restrict__ col, const float* __restrict__ w,
@@ -320,6 +320,7 @@ __global__ __launch_bounds__(kBlock) void k_out_adjoint(pg_paths P, Consts c, co
         on = e > a && a >= 0 && e <= N;
     }
     f3 ob{0.f, 0.f, 0.f}, zb{0.f, 0.f, 0.f}, in{0.f, 0.f, 0.f}, ing{0.f, 0.f, 0.f};
+    double ix = 0.0, iy = 0.0, iz = 0.0, gx = 0.0, gy = 0.0, gz = 0.0;
     int64_t s0 = 0;
     if (on) {
         const int64_t px = p / P.spp;
@@ -332,8 +333,13 @@ __global__ __launch_bounds__(kBlock) void k_out_adjoint(pg_paths P, Consts c, co
             const int64_t j = col[e];
             const float ww = w[e], gg = gw[e];
             const f3 xv = ld3(xD, j);
-            in = f3{ww * xv.x, ww * xv.y, ww * xv.z};
-            ing = f3{gg * xv.x, gg * xv.y, gg * xv.z};
+            const double wd = ww, gd = gg;   // split over lanes, the sums keep the chain's accuracy in double precision
+            ix = wd * xv.x;
+            iy = wd * xv.y;
+            iz = wd * xv.z;
+            gx = gd * xv.x;
+            gy = gd * xv.y;
+            gz = gd * xv.z;
             const int64_t pj = tpos[j];
             atomicAdd(&lam[3 * pj], ww * zb.x);
             atomicAdd(&lam[3 * pj + 1], ww * zb.y);
@@ -341,8 +347,8 @@ __global__ __launch_bounds__(kBlock) void k_out_adjoint(pg_paths P, Consts c, co
         }
     }
     if (c.final_gather == 0) {
-        in = f3{group_sum<KP>(in.x), group_sum<KP>(in.y), group_sum<KP>(in.z)};
-        ing = f3{group_sum<KP>(ing.x), group_sum<KP>(ing.y), group_sum<KP>(ing.z)};
+        in = f3{(float)group_sum<KP>(ix), (float)group_sum<KP>(iy), (float)group_sum<KP>(iz)};
+        ing = f3{(float)group_sum<KP>(gx), (float)group_sum<KP>(gy), (float)group_sum<KP>(gz)};
     }
     if (on && lane == 0) {
         const bool extra = P.n_extra > 0;

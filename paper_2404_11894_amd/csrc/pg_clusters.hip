@@ -589,8 +589,8 @@ __global__ __launch_bounds__(kBlock) void k_cmarg(int64_t N, Consts c, const uin
     for (uint32_t l = rg.x; l < rg.y; ++l) {
         const float4 t4 = tq[l];
         const f3 tl{t4.x, t4.y, t4.z};
-        mplus += c.pdf(one_minus_cos(tl, w));
-        menv += c.pdf(one_minus_cos(tl, we));
+        mplus += c.pdf.between(tl, w);
+        menv += c.pdf.between(tl, we);
     }
     const float Cpe = (float)(rg.y - rg.x) * c.env_pdf;
     wq[i] = make_float4(w.x, w.y, w.z, c.rho.c / mplus);
@@ -598,22 +598,21 @@ __global__ __launch_bounds__(kBlock) void k_cmarg(int64_t N, Consts c, const uin
     me[i] = menv + Cpe;
 }
 
-// What a receiver reads of a member in the second pass: its samples, the
-// radiances over their marginals.
+// What a receiver reads of a member in the second pass.
 struct Member {
-    float4 w, we, le, lp;   // ls in the last parts of the first three
+    float4 w, we, le, lp;   // ls in the last parts of the first three, M+ + C p_e in that of lp
+    float me;
     __device__ __forceinline__ static Member of(const VRec& r, float mp, float me) {
         return {make_float4(r.w[0], r.w[1], r.w[2], r.ls[0]), make_float4(r.we[0], r.we[1], r.we[2], r.ls[1]),
-                make_float4(r.le[0] / me, r.le[1] / me, r.le[2] / me, r.ls[2]),
-                make_float4(r.lp[0] / mp, r.lp[1] / mp, r.lp[2] / mp, 0.f)};
+                make_float4(r.le[0], r.le[1], r.le[2], r.ls[2]), make_float4(r.lp[0], r.lp[1], r.lp[2], mp), me};
     }
 };
 
 // Second pass, per receiver i over its cluster's samples j:
 //   d_agg_i = rho_i(sun)/C sum_j Ls_j + sum_j rho_i(we_j) Le_j / Me_j + rho_i(w_j) Lp_j / (M+_j + C p_e)
 //   b_i = e_i + alpha_i d_agg_i,  and the own (path-traced) direct term and ratio.
-// Bound by the instructions of the pairs, so what depends on the member alone is
-// done once, as the members are staged: 20M vertices 1.67 -> 0.71 ms.
+// Members come from LDS, where one read of 16 bytes serves the rows of a cluster
+// that a wave holds: 20M vertices 1.67 ms from global memory, 0.91 ms so.
 __global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const uint64_t* __restrict__ heads,
                                                    const VRec* __restrict__ crec, const float4* __restrict__ tq,
                                                    const float* __restrict__ mp, const float* __restrict__ me,
@@ -621,14 +620,22 @@ __global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const ui
                                                    const int32_t* __restrict__ perm, const float* __restrict__ dir_pl,
                                                    const float* __restrict__ l_pl, float* __restrict__ b,
                                                    float* __restrict__ dpt, float* __restrict__ r) {
-    __shared__ Member sm[kSpan];
+    __shared__ float4 sm[4 * kSpan];
+    __shared__ float sme[kSpan];
     const int64_t i0 = (int64_t)blockIdx.x * kBlock, i = i0 + threadIdx.x;
     const Span sp = block_span(heads, i0, N);
     const uint2 rg = sp.rg;
     const uint32_t lo = sp.lo;
     const bool staged = sp.n <= (uint32_t)kSpan;
     if (staged) {
-        for (uint32_t t = threadIdx.x; t < sp.n; t += kBlock) sm[t] = Member::of(crec[lo + t], mp[lo + t], me[lo + t]);
+        for (uint32_t t = threadIdx.x; t < sp.n; t += kBlock) {
+            const Member m = Member::of(crec[lo + t], mp[lo + t], me[lo + t]);
+            sm[4 * t] = m.w;
+            sm[4 * t + 1] = m.we;
+            sm[4 * t + 2] = m.le;
+            sm[4 * t + 3] = m.lp;
+            sme[t] = m.me;
+        }
         __syncthreads();
     }
     if (i >= N) return;
@@ -636,21 +643,20 @@ __global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const ui
     const f3 ti{t4.x, t4.y, t4.z};
     float cx = 0.f, cy = 0.f, cz = 0.f, sx = 0.f, sy = 0.f, sz = 0.f, qx = 0.f, qy = 0.f, qz = 0.f;
     auto add = [&](const Member& m) {
-        const float fp = hg_shape(c.rho, ti, m.w.x, m.w.y, m.w.z), fe = hg_shape(c.rho, ti, m.we.x, m.we.y, m.we.z);
-        cx = fmaf(fe, m.le.x, fmaf(fp, m.lp.x, cx));
-        cy = fmaf(fe, m.le.y, fmaf(fp, m.lp.y, cy));
-        cz = fmaf(fe, m.le.z, fmaf(fp, m.lp.z, cz));
+        const float fp = c.rho.between(ti, f3{m.w.x, m.w.y, m.w.z}) / m.lp.w;
+        const float fe = c.rho.between(ti, f3{m.we.x, m.we.y, m.we.z}) / m.me;
+        cx += fe * m.le.x + fp * m.lp.x;
+        cy += fe * m.le.y + fp * m.lp.y;
+        cz += fe * m.le.z + fp * m.lp.z;
         sx += m.w.w;
         sy += m.we.w;
         sz += m.le.w;
     };
     if (staged)
-        for (uint32_t j = rg.x; j < rg.y; ++j) add(sm[j - lo]);
+        for (uint32_t t = rg.x - lo; t < rg.y - lo; ++t)
+            add(Member{sm[4 * t], sm[4 * t + 1], sm[4 * t + 2], sm[4 * t + 3], sme[t]});
     else
         for (uint32_t j = rg.x; j < rg.y; ++j) add(Member::of(crec[j], mp[j], me[j]));
-    cx *= c.rho.c;
-    cy *= c.rho.c;
-    cz *= c.rho.c;
     if (dir_pl) {   // point light: a delta light per member sample, weight 1/C
         for (uint32_t j = rg.x; j < rg.y; ++j) {
             const int64_t pj = perm[cperm[j]];

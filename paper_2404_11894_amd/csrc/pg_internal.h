@@ -372,6 +372,12 @@ struct HG {
         float r = __frsqrt_rn(den);
         return c * r * r * r;
     }
+    // the same of u = |p - q|^2 / 2, bit for bit, without the halving
+    __device__ float between(f3 p, f3 q) const {
+        const float dx = p.x - q.x, dy = p.y - q.y, dz = p.z - q.z;
+        const float r = __frsqrt_rn(fmaf(0.5f * two_g, fmaf(dx, dx, fmaf(dy, dy, dz * dz)), a));
+        return c * r * r * r;
+    }
 };
 
 __device__ inline float one_minus_cos(f3 a, f3 b) {
@@ -487,11 +493,35 @@ inline void dispatch_kp(int K, F&& go) {
     else go(std::integral_constant<int, 64>{});
 }
 
-// Sum over aligned groups of KP lanes (KP a power of two <= 64).
-template <int KP>
-__device__ inline float group_sum(float v) {
-#pragma unroll
-    for (int o = KP / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+// v of lane ^ O.  Up to 8 the exchange stays within a row of 16 lanes and is part of
+// the vector instruction (DPP) instead of a round through the LDS unit.
+template <int O>
+__device__ inline float lane_xor(float v) {
+    const int x = __float_as_int(v);
+    if constexpr (O == 1) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0xB1, 0xf, 0xf, true));   // quad 1 0 3 2
+    if constexpr (O == 2) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0x4E, 0xf, 0xf, true));   // quad 2 3 0 1
+    if constexpr (O == 4) {   // banks of four lanes: the odd ones from below, the even ones from above
+        const int up = __builtin_amdgcn_update_dpp(x, x, 0x114, 0xf, 0xa, true);
+        return __int_as_float(__builtin_amdgcn_update_dpp(up, x, 0x104, 0xf, 0x5, true));
+    }
+    if constexpr (O == 8) return __int_as_float(__builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true));  // row turned by 8
+    return __shfl_xor(v, O, kWave);
+}
+
+template <int O>
+__device__ inline double lane_xor(double v) {
+    const float lo = lane_xor<O>(__int_as_float(__double2loint(v))), hi = lane_xor<O>(__int_as_float(__double2hiint(v)));
+    return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+}
+
+// Sum over aligned groups of KP lanes (KP a power of two <= 64); every lane
+// of a group takes part.
+template <int KP, typename T>
+__device__ inline T group_sum(T v) {
+    if constexpr (KP > 1) {
+        v += lane_xor<KP / 2>(v);
+        return group_sum<KP / 2>(v);
+    }
     return v;
 }
 
@@ -548,6 +578,34 @@ hipError_t launch_pack_records(int64_t N, const pg_paths& paths, VRec* rec, int3
 // space, into the sliced-ELL layout (ell = 1, the internal render) or a
 // row-major CSR (ell = 0, the pg_edges entry point).  canon_row (nullable)
 // maps local row -> path-order row for the optional path-order outputs.
+// A record in registers (zeros by default).
+struct RecRegs {
+    f3 t{0.f, 0.f, 0.f}, w{0.f, 0.f, 0.f}, we{0.f, 0.f, 0.f}, ls{0.f, 0.f, 0.f}, le{0.f, 0.f, 0.f},
+        lp{0.f, 0.f, 0.f};
+    float alpha = 0.0f;
+    __device__ void load(const VRec* r) {
+        const float4* r4 = reinterpret_cast<const float4*>(r);
+        const float4 a0 = r4[0], a1 = r4[1], a2 = r4[2], a3 = r4[3], a4 = r4[4];
+        t = f3{a0.x, a0.y, a0.z};
+        w = f3{a0.w, a1.x, a1.y};
+        we = f3{a1.z, a1.w, a2.x};
+        ls = f3{a2.y, a2.z, a2.w};
+        le = f3{a3.x, a3.y, a3.z};
+        lp = f3{a3.w, a4.x, a4.y};
+        alpha = a4.z;
+    }
+};
+
+// Which of a block's GR rows this thread finishes (the last part of k_edges and
+// k_edges_adjoint), -1: none.  One thread a row: in the row's own group the
+// instructions for one lane would take the wave's time.  Fewer than a wave of
+// rows go to one wave, a different one from block to block.
+template <int GR>
+__device__ inline int finished_row() {
+    const int r = GR >= kWave ? (int)threadIdx.x : (int)threadIdx.x - (int)(blockIdx.x % (kBlock / kWave)) * kWave;
+    return r >= 0 && r < GR ? r : -1;
+}
+
 struct EdgeOut {
     int ell;             // 1: col / w / gw in the sliced-ELL layout, 0: row-major
     float* w;            // local order (required): ell_size(N, K) or N*K elements

@@ -489,7 +489,9 @@ hipError_t launch_spmv_shifted(int64_t N, int K, const int32_t* succ, const int3
 // vertex.  Bound by the latency of offset -> id -> neighbour -> value: one
 // thread per pixel walked spp K such chains (31 us for 4096 pixels at 4 samples,
 // k = 8; 886 us for 512 x 512 at k = 16); with the neighbours and samples side
-// by side a wave waits for one (5 and 225 us).
+// by side a wave waits for one (5 and 225 us).  Products and sums are in double
+// precision, hidden behind the loads: in single precision, split over lanes, the
+// image was 4% further off than by one thread's chain of fused operations.
 template <int KP, int S>
 __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const int32_t* __restrict__ inv,
                                                    const int32_t* __restrict__ col, const float* __restrict__ w,
@@ -502,7 +504,7 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
     const int64_t npix = (int64_t)P.width * P.height;
     const int64_t N = P.n_vertices;
     const int K = c.K;
-    float sx = 0.0f, sy = 0.0f, sz = 0.0f;
+    double sx = 0.0, sy = 0.0, sz = 0.0;
     for (int k0 = 0; k0 < P.spp; k0 += S) {   // the same trips on every lane: all take part in the sums
         const int k = k0 + grp;
         const int64_t p = px * P.spp + k;
@@ -519,7 +521,7 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
             }
         }
         const int64_t s0 = on ? (inv ? (int64_t)inv[a] : a) : 0;
-        float ix = 0.0f, iy = 0.0f, iz = 0.0f;
+        double ix = 0.0, iy = 0.0, iz = 0.0;
         if (c.final_gather == 0) {
             if (on && lane < K) {
                 const int64_t e = inv ? eidx(s0, lane, K) : s0 * K + lane;
@@ -527,7 +529,7 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
                 if (j < 0 || j >= N) {
                     set_flag(flag, kFlagIndex);
                 } else {
-                    const float ww = w[e];
+                    const double ww = w[e];
                     const f3 xv = ld3(x, j);
                     ix = ww * xv.x;
                     iy = ww * xv.y;
@@ -538,7 +540,7 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
             iy = group_sum<KP>(iy);
             iz = group_sum<KP>(iz);
         } else if (on && lane == 0) {
-            float rr;
+            double rr;
             if (r) {
                 rr = r[s0];
             } else {
@@ -576,9 +578,9 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
         }
         f3 dd = ld3(dpt, s0);
         if (P.n_extra > 0) dd = extra_direct(P, p, a, ld3(P.dir_in, a), c.rho, c.g, c.sun, c.env_pdf, nullptr);
-        sx = fmaf(al, dd.x + ix, sx);
-        sy = fmaf(al, dd.y + iy, sy);
-        sz = fmaf(al, dd.z + iz, sz);
+        sx = fma((double)al, (double)dd.x + ix, sx);
+        sy = fma((double)al, (double)dd.y + iy, sy);
+        sz = fma((double)al, (double)dd.z + iz, sz);
     }
     // the groups' sums (held by their lanes 0)
 #pragma unroll
@@ -588,10 +590,10 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
         sz += __shfl_xor(sz, o, kWave);
     }
     if (px >= npix || lane != 0 || grp != 0) return;
-    const float inv_spp = 1.0f / (float)P.spp;
-    image[3 * px] = sx * inv_spp;
-    image[3 * px + 1] = sy * inv_spp;
-    image[3 * px + 2] = sz * inv_spp;
+    const double inv_spp = 1.0 / (double)P.spp;
+    image[3 * px] = (float)(sx * inv_spp);
+    image[3 * px + 1] = (float)(sy * inv_spp);
+    image[3 * px + 2] = (float)(sz * inv_spp);
 }
 
 hipError_t launch_pixels(const pg_paths& paths, const Consts& c, const int32_t* inv, const int32_t* col,
