@@ -717,14 +717,13 @@ __global__ __launch_bounds__(kBlock) void k_edges_adjoint(int64_t N, Consts c, c
                                                           const float* __restrict__ l_pl) {
     constexpr int GR = kBlock / KP;
     __shared__ f3 tsh[GR][KP];
+    __shared__ f3 csum[GR], hsum[GR], ssum[GR], qsum[GR], gsum[GR];
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int lane = threadIdx.x % KP, grp = threadIdx.x / KP;
     const int64_t i = tile * GR + grp;
     const int K = c.K;
     const bool act = i < N && lane < K;
-    f3 t{0.f, 0.f, 0.f}, w{0.f, 0.f, 0.f}, we{0.f, 0.f, 0.f}, ls{0.f, 0.f, 0.f}, le{0.f, 0.f, 0.f},
-        lp{0.f, 0.f, 0.f};
-    float alpha = 0.0f;
+    RecRegs n;   // of the neighbour
     f3 dpl{0.f, 0.f, 0.f}, lpl{0.f, 0.f, 0.f};
     if (act) {
         const int32_t jn = col[eidx(i, lane, K)];
@@ -732,36 +731,28 @@ __global__ __launch_bounds__(kBlock) void k_edges_adjoint(int64_t N, Consts c, c
             dpl = ld3(dir_pl, perm[jn]);
             lpl = ld3(l_pl, perm[jn]);
         }
-        const float4* r4 = reinterpret_cast<const float4*>(rec + jn);
-        float4 a0 = r4[0], a1 = r4[1], a2 = r4[2], a3 = r4[3], a4 = r4[4];
-        t = f3{a0.x, a0.y, a0.z};
-        w = f3{a0.w, a1.x, a1.y};
-        we = f3{a1.z, a1.w, a2.x};
-        ls = f3{a2.y, a2.z, a2.w};
-        le = f3{a3.x, a3.y, a3.z};
-        lp = f3{a3.w, a4.x, a4.y};
-        alpha = a4.z;
+        n.load(rec + jn);
     }
-    tsh[grp][lane] = t;
+    tsh[grp][lane] = n.t;
     __syncthreads();
     const f3 ti = tsh[grp][0];
     float mplus = 0.0f, menv = 0.0f;
     for (int l = 0; l < K; ++l) {
         const f3 tl = tsh[grp][l];
-        mplus += c.pdf(one_minus_cos(tl, w));
-        menv += c.pdf(one_minus_cos(tl, we));
+        mplus += c.pdf.between(tl, n.w);
+        menv += c.pdf.between(tl, n.we);
     }
     const float Kpe = (float)K * c.env_pdf;
-    const float u_w = one_minus_cos(ti, w), u_e = one_minus_cos(ti, we);
+    const float u_w = one_minus_cos(ti, n.w), u_e = one_minus_cos(ti, n.we);
     const float rho = c.rho(u_w), rho_e = c.rho(u_e);
     const float wp = rho / (mplus + Kpe), wev = rho_e / (menv + Kpe);
     const float hw = hg_dlog(c.g, u_w), he = hg_dlog(c.g, u_e);
     // value and g-derivative of each record's contribution
-    float cx = act ? wev * le.x + wp * lp.x : 0.f, cy = act ? wev * le.y + wp * lp.y : 0.f,
-          cz = act ? wev * le.z + wp * lp.z : 0.f;
-    float hx = act ? wev * he * le.x + wp * hw * lp.x : 0.f, hy = act ? wev * he * le.y + wp * hw * lp.y : 0.f,
-          hz = act ? wev * he * le.z + wp * hw * lp.z : 0.f;
-    float sx = act ? ls.x : 0.f, sy = act ? ls.y : 0.f, sz = act ? ls.z : 0.f;
+    float cx = act ? wev * n.le.x + wp * n.lp.x : 0.f, cy = act ? wev * n.le.y + wp * n.lp.y : 0.f,
+          cz = act ? wev * n.le.z + wp * n.lp.z : 0.f;
+    float hx = act ? wev * he * n.le.x + wp * hw * n.lp.x : 0.f, hy = act ? wev * he * n.le.y + wp * hw * n.lp.y : 0.f,
+          hz = act ? wev * he * n.le.z + wp * hw * n.lp.z : 0.f;
+    float sx = act ? n.ls.x : 0.f, sy = act ? n.ls.y : 0.f, sz = act ? n.ls.z : 0.f;
     cx = group_sum<KP>(cx);
     cy = group_sum<KP>(cy);
     cz = group_sum<KP>(cz);
@@ -788,29 +779,52 @@ __global__ __launch_bounds__(kBlock) void k_edges_adjoint(int64_t N, Consts c, c
         gy = group_sum<KP>(gy);
         gz = group_sum<KP>(gz);
     }
+    if (lane == 0) {
+        csum[grp] = f3{cx, cy, cz};
+        hsum[grp] = f3{hx, hy, hz};
+        ssum[grp] = f3{sx, sy, sz};
+        if (dir_pl) {
+            qsum[grp] = f3{qx, qy, qz};
+            gsum[grp] = f3{gx, gy, gz};
+        }
+    }
+    __syncthreads();
     double gl = 0.0;
-    if (i < N && lane == 0) {
-        const float u_s = one_minus_cos(ti, c.sun);
+    const int f = finished_row<GR>();
+    const int64_t v = tile * GR + f;
+    if (f >= 0 && v < N) {
+        const f3 tv = tsh[f][0], cs = csum[f], hsm = hsum[f], ss = ssum[f];
+        RecRegs m;   // the vertex's own
+        m.load(rec + v);
+        const float u_s = one_minus_cos(tv, c.sun);
         const float rho_sun = c.rho(u_s), hs = hg_dlog(c.g, u_s);
         const float invK = 1.0f / (float)K;
-        f3 dagg{fmaf(rho_sun * invK, sx, cx), fmaf(rho_sun * invK, sy, cy), fmaf(rho_sun * invK, sz, cz)};
-        if (dir_pl) dagg = f3{fmaf(invK, qx, dagg.x), fmaf(invK, qy, dagg.y), fmaf(invK, qz, dagg.z)};
-        const f3 bb = ld3(bbar, i);
-        abar[i] += dot3(bb, dagg);
-        const f3 db{alpha * bb.x, alpha * bb.y, alpha * bb.z};
+        f3 dagg{fmaf(rho_sun * invK, ss.x, cs.x), fmaf(rho_sun * invK, ss.y, cs.y), fmaf(rho_sun * invK, ss.z, cs.z)};
+        if (dir_pl) {
+            const f3 qs = qsum[f];
+            dagg = f3{fmaf(invK, qs.x, dagg.x), fmaf(invK, qs.y, dagg.y), fmaf(invK, qs.z, dagg.z)};
+        }
+        const f3 bb = ld3(bbar, v);
+        abar[v] += dot3(bb, dagg);
+        const f3 db{m.alpha * bb.x, m.alpha * bb.y, m.alpha * bb.z};
         const float ks = rho_sun * hs * invK;
-        gl += (double)dot3(db, f3{fmaf(ks, sx, hx), fmaf(ks, sy, hy), fmaf(ks, sz, hz)});
-        if (dir_pl) gl += (double)(invK * dot3(db, f3{gx, gy, gz}));
+        gl += (double)dot3(db, f3{fmaf(ks, ss.x, hsm.x), fmaf(ks, ss.y, hsm.y), fmaf(ks, ss.z, hsm.z)});
+        if (dir_pl) gl += (double)(invK * dot3(db, gsum[f]));
         // own direct term and continuation ratio
-        const float p_w = c.pdf(u_w), p_e = c.pdf(u_e);
-        const float f_env = rho_e / (p_e + c.env_pdf), f_out = rho / (p_w + c.env_pdf);
-        const f3 pb = ld3(dptbar, i);
-        const f3 dd{rho_sun * hs * ls.x + f_env * he * le.x + f_out * hw * lp.x,
-                    rho_sun * hs * ls.y + f_env * he * le.y + f_out * hw * lp.y,
-                    rho_sun * hs * ls.z + f_env * he * le.z + f_out * hw * lp.z};
+        const float o_w = one_minus_cos(tv, m.w), o_e = one_minus_cos(tv, m.we);
+        const float h_w = hg_dlog(c.g, o_w), h_e = hg_dlog(c.g, o_e);
+        const float rho_w = c.rho(o_w), p_w = c.pdf(o_w), p_e = c.pdf(o_e);
+        const float f_env = c.rho(o_e) / (p_e + c.env_pdf), f_out = rho_w / (p_w + c.env_pdf);
+        const f3 pb = ld3(dptbar, v);
+        const f3 dd{rho_sun * hs * m.ls.x + f_env * h_e * m.le.x + f_out * h_w * m.lp.x,
+                    rho_sun * hs * m.ls.y + f_env * h_e * m.le.y + f_out * h_w * m.lp.y,
+                    rho_sun * hs * m.ls.z + f_env * h_e * m.le.z + f_out * h_w * m.lp.z};
         gl += (double)dot3(pb, dd);
-        if (dir_pl) gl += (double)(hpl * dot3(pb, lpl));   // lane 0: the receiver's own sample
-        gl += (double)(rbar[i] * (rho / p_w) * hw);
+        if (dir_pl) {   // the receiver's own sample
+            const float u = one_minus_cos(tv, ld3(dir_pl, perm[v]));
+            gl += (double)(c.rho(u) * hg_dlog(c.g, u) * dot3(pb, ld3(l_pl, perm[v])));
+        }
+        gl += (double)(rbar[v] * (rho_w / p_w) * h_w);
     }
     const double tsum = block_sum_d(gl);
     if (threadIdx.x == 0) gpart[tile] = tsum;

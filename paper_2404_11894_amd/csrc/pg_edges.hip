@@ -12,18 +12,24 @@
 
 namespace pg {
 
-__device__ inline f3 rec_f3(const float* p) { return f3{p[0], p[1], p[2]}; }
-
 // One group of KP lanes per receiver, lane j = j-th neighbour.  The
 // neighbours' arriving directions (the techniques) are staged in LDS; every
 // lane sums the K technique pdfs at its own two samples (continuation and
 // environment) to get the marginals, then forms its three weights; the
-// direct term is a group reduction.
+// direct term is a group reduction, which one thread a row turns into the
+// vertex's terms.
+//
+// Bound by the vector instructions: K pairs of densities a lane and what is done
+// once a row.  With the row's terms in its group (instructions for one lane of
+// 16) and sums by way of the LDS, 20M rows (K = 16) took 5.45 ms, now 4.60; 3.8M in
+// path order (K = 13), where the gathers come in between, 1.18 and 1.12 ms.
 template <int KP>
 __global__ __launch_bounds__(kBlock) void k_edges(int64_t N, Consts c, const int32_t* __restrict__ col,
                                                   const VRec* __restrict__ rec, EdgeOut o, int32_t* flag) {
     constexpr int GR = kBlock / KP;
     __shared__ f3 tsh[GR][KP];
+    __shared__ f3 csum[GR], ssum[GR], qsum[GR];
+    __shared__ int own[GR];
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int lane = threadIdx.x % KP, grp = threadIdx.x / KP;
     const int64_t i = tile * GR + grp;
@@ -31,9 +37,7 @@ __global__ __launch_bounds__(kBlock) void k_edges(int64_t N, Consts c, const int
     const bool row_ok = i < N;
     bool act = row_ok && lane < K;
 
-    f3 t{0.f, 0.f, 0.f}, w{0.f, 0.f, 0.f}, we{0.f, 0.f, 0.f}, ls{0.f, 0.f, 0.f}, le{0.f, 0.f, 0.f},
-        lp{0.f, 0.f, 0.f};
-    float alpha = 0.0f;
+    RecRegs n;   // of the neighbour
     f3 dpl{0.f, 0.f, 0.f}, lpl{0.f, 0.f, 0.f};   // point light sample of the neighbour
     const int64_t e = o.ell ? eidx(i, lane, K) : i * K + lane;
     if (act) {
@@ -42,15 +46,7 @@ __global__ __launch_bounds__(kBlock) void k_edges(int64_t N, Consts c, const int
             set_flag(flag, kFlagIndex);
             act = false;
         } else {
-            const float4* r4 = reinterpret_cast<const float4*>(rec + j);
-            float4 a0 = r4[0], a1 = r4[1], a2 = r4[2], a3 = r4[3], a4 = r4[4];
-            t = f3{a0.x, a0.y, a0.z};
-            w = f3{a0.w, a1.x, a1.y};
-            we = f3{a1.z, a1.w, a2.x};
-            ls = f3{a2.y, a2.z, a2.w};
-            le = f3{a3.x, a3.y, a3.z};
-            lp = f3{a3.w, a4.x, a4.y};
-            alpha = a4.z;
+            n.load(rec + j);
             if (o.dir_pl) {
                 const int64_t cj = o.canon_row ? (int64_t)o.canon_row[j] : j;
                 dpl = ld3(o.dir_pl, cj);
@@ -58,27 +54,27 @@ __global__ __launch_bounds__(kBlock) void k_edges(int64_t N, Consts c, const int
             }
         }
     }
-    tsh[grp][lane] = t;
+    tsh[grp][lane] = n.t;
     __syncthreads();
     const f3 ti = tsh[grp][0];
 
     float mplus = 0.0f, menv = 0.0f;
     for (int l = 0; l < K; ++l) {
         const f3 tl = tsh[grp][l];
-        mplus += c.pdf(one_minus_cos(tl, w));
-        menv += c.pdf(one_minus_cos(tl, we));
+        mplus += c.pdf.between(tl, n.w);
+        menv += c.pdf.between(tl, n.we);
     }
     const float Kpe = (float)K * c.env_pdf;
-    const float u_w = one_minus_cos(ti, w), u_e = one_minus_cos(ti, we);
+    const float u_w = one_minus_cos(ti, n.w), u_e = one_minus_cos(ti, n.we);
     const float rho = c.rho(u_w), rho_e = c.rho(u_e);
     const float wi = rho / mplus;
     const float wp = rho / (mplus + Kpe);
     const float wev = rho_e / (menv + Kpe);
 
-    float cx = act ? wev * le.x + wp * lp.x : 0.0f;
-    float cy = act ? wev * le.y + wp * lp.y : 0.0f;
-    float cz = act ? wev * le.z + wp * lp.z : 0.0f;
-    float sx = act ? ls.x : 0.0f, sy = act ? ls.y : 0.0f, sz = act ? ls.z : 0.0f;
+    float cx = act ? wev * n.le.x + wp * n.lp.x : 0.0f;
+    float cy = act ? wev * n.le.y + wp * n.lp.y : 0.0f;
+    float cz = act ? wev * n.le.z + wp * n.lp.z : 0.0f;
+    float sx = act ? n.ls.x : 0.0f, sy = act ? n.ls.y : 0.0f, sz = act ? n.ls.z : 0.0f;
     cx = group_sum<KP>(cx);
     cy = group_sum<KP>(cy);
     cz = group_sum<KP>(cz);
@@ -110,36 +106,52 @@ __global__ __launch_bounds__(kBlock) void k_edges(int64_t N, Consts c, const int
             if (o.w_env) o.w_env[ce] = wev;
         }
     }
-    if (row_ok && lane == 0) {
-        if (o.succ) o.succ[i] = -1;
-        if (o.pred) o.pred[i] = -1;
-        if (o.x0) st3(o.x0, i, f3{0.f, 0.f, 0.f});
-        // aggregated direct: sun (delta light, weight 1/K per neighbour) + MIS'd records
-        const float rho_sun = c.rho(one_minus_cos(ti, c.sun));
-        const float invK = 1.0f / (float)K;
-        f3 dagg{fmaf(rho_sun * invK, sx, cx), fmaf(rho_sun * invK, sy, cy), fmaf(rho_sun * invK, sz, cz)};
-        if (o.dir_pl) dagg = f3{fmaf(invK, qx, dagg.x), fmaf(invK, qy, dagg.y), fmaf(invK, qz, dagg.z)};
-        // constant of the row: the vertex's own volume emission (not scattered) + alpha d_agg
-        f3 em{0.f, 0.f, 0.f};
-        if (o.emit) em = ld3(o.emit, o.canon_row ? (int64_t)o.canon_row[i] : i);
-        const f3 b{fmaf(alpha, dagg.x, em.x), fmaf(alpha, dagg.y, em.y), fmaf(alpha, dagg.z, em.z)};
-        // own (path-traced) direct: one sun sample, environment and phase samples by the balance heuristic
-        const float p_w = c.pdf(u_w), p_e = c.pdf(u_e);
-        const float f_env = rho_e / (p_e + c.env_pdf), f_out = rho / (p_w + c.env_pdf);
-        f3 dpt{rho_sun * ls.x + f_env * le.x + f_out * lp.x, rho_sun * ls.y + f_env * le.y + f_out * lp.y,
-               rho_sun * ls.z + f_env * le.z + f_out * lp.z};
-        if (o.dir_pl)   // lane 0 holds the receiver's own sample
-            dpt = f3{fmaf(rho_pl, lpl.x, dpt.x), fmaf(rho_pl, lpl.y, dpt.y), fmaf(rho_pl, lpl.z, dpt.z)};
-        st3(o.b, i, b);
-        st3(o.dpt, i, dpt);
-        o.r[i] = rho / p_w;
-        o.alpha[i] = alpha;
-        if (o.b_canon || o.dpt_canon) {
-            const int64_t ci = o.canon_row ? (int64_t)o.canon_row[i] : i;
-            if (o.b_canon) st3(o.b_canon, ci, b);
-            if (o.dpt_canon) st3(o.dpt_canon, ci, dpt);
-        }
+    if (lane == 0) {
+        csum[grp] = f3{cx, cy, cz};
+        ssum[grp] = f3{sx, sy, sz};
+        if (o.dir_pl) qsum[grp] = f3{qx, qy, qz};
+        own[grp] = act;
     }
+    __syncthreads();
+    const int f = finished_row<GR>();
+    const int64_t v = tile * GR + f;
+    if (f < 0 || v >= N) return;
+    const f3 tv = tsh[f][0], cs = csum[f], ss = ssum[f];
+    RecRegs m;   // the vertex's own
+    if (own[f]) m.load(rec + v);
+    if (o.succ) o.succ[v] = -1;
+    if (o.pred) o.pred[v] = -1;
+    if (o.x0) st3(o.x0, v, f3{0.f, 0.f, 0.f});
+    const int64_t cv = o.canon_row ? (int64_t)o.canon_row[v] : v;
+    // aggregated direct: sun (delta light, weight 1/K per neighbour) + MIS'd records
+    const float rho_sun = c.rho(one_minus_cos(tv, c.sun));
+    const float invK = 1.0f / (float)K;
+    f3 dagg{fmaf(rho_sun * invK, ss.x, cs.x), fmaf(rho_sun * invK, ss.y, cs.y), fmaf(rho_sun * invK, ss.z, cs.z)};
+    if (o.dir_pl) {
+        const f3 qs = qsum[f];
+        dagg = f3{fmaf(invK, qs.x, dagg.x), fmaf(invK, qs.y, dagg.y), fmaf(invK, qs.z, dagg.z)};
+    }
+    // constant of the row: the vertex's own volume emission (not scattered) + alpha d_agg
+    f3 em{0.f, 0.f, 0.f};
+    if (o.emit) em = ld3(o.emit, cv);
+    const f3 b{fmaf(m.alpha, dagg.x, em.x), fmaf(m.alpha, dagg.y, em.y), fmaf(m.alpha, dagg.z, em.z)};
+    // own (path-traced) direct: one sun sample, environment and phase samples by the balance heuristic
+    const float o_w = one_minus_cos(tv, m.w), o_e = one_minus_cos(tv, m.we);
+    const float rho_w = c.rho(o_w), p_w = c.pdf(o_w), p_e = c.pdf(o_e);
+    const float f_env = c.rho(o_e) / (p_e + c.env_pdf), f_out = rho_w / (p_w + c.env_pdf);
+    f3 dpt{rho_sun * m.ls.x + f_env * m.le.x + f_out * m.lp.x, rho_sun * m.ls.y + f_env * m.le.y + f_out * m.lp.y,
+           rho_sun * m.ls.z + f_env * m.le.z + f_out * m.lp.z};
+    if (o.dir_pl && own[f]) {   // the receiver's own sample
+        const float rp = c.rho(one_minus_cos(tv, ld3(o.dir_pl, cv)));
+        const f3 lq = ld3(o.l_pl, cv);
+        dpt = f3{fmaf(rp, lq.x, dpt.x), fmaf(rp, lq.y, dpt.y), fmaf(rp, lq.z, dpt.z)};
+    }
+    st3(o.b, v, b);
+    st3(o.dpt, v, dpt);
+    o.r[v] = rho_w / p_w;
+    o.alpha[v] = m.alpha;
+    if (o.b_canon) st3(o.b_canon, cv, b);
+    if (o.dpt_canon) st3(o.dpt_canon, cv, dpt);
 }
 
 hipError_t launch_edges(int64_t N, const Consts& c, const int32_t* col, const VRec* rec, const EdgeOut& o,
