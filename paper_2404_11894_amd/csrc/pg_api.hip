@@ -588,28 +588,27 @@ pg_status pg_edges(const pg_paths* paths, const pg_params* params, const int64_t
     float* rl = cv.take<float>(N);
     float* al = cv.take<float>(N);
     hipError_t e;
-    if ((e = launch_fill(flag, 64 * 4, s)) != hipSuccess) return hip_fail(e, "fill");
+    if ((params->flags & PG_FLAG_CHECK) && (e = launch_fill(flag, 64 * 4, s)) != hipSuccess)
+        return hip_fail(e, "fill");   // read back only with the check
     if ((st = check_knn_layout(params, N, K, row_ptr, flag, s))) return st;
     if (N == 0) return finish(s, params, flag, params->flags);
     if ((e = launch_pack_records(N, *paths, rec, flag, s)) != hipSuccess) return hip_fail(e, "pack");
     EdgeOut o{};
     o.w = w_ind ? w_ind : wtmp;
-    o.b = bl;
-    o.dpt = dl;
+    o.b = b ? b : bl;   // the rows are in path order: no copies
+    o.dpt = d_pt ? d_pt : dl;
     o.r = rl;
     o.alpha = al;
     o.w_ph = w_ph;
     o.w_env = w_env;
-    o.b_canon = b;
-    o.dpt_canon = d_pt;
+    o.x0 = lplus0;
     o.emit = paths->l_emit;
     o.dir_pl = paths->dir_pl;
     o.l_pl = paths->l_pl;
     Consts c = make_consts(params, K);
     if ((e = launch_edges(N, c, col, rec, o, flag, s)) != hipSuccess) return hip_fail(e, "edges");
     if (lplus0) {
-        if ((e = launch_fill(lplus0, (size_t)N * 12, s)) != hipSuccess) return hip_fail(e, "fill");
-        if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, al, dl, rl, paths->l_emit, params->init, nullptr,
+        if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, al, o.dpt, rl, paths->l_emit, params->init, nullptr,
                               nullptr, lplus0, flag, s)) != hipSuccess)
             return hip_fail(e, "paths");
     }
