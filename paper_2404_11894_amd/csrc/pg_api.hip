@@ -334,8 +334,8 @@ pg_status propagate_run(const pg_paths* paths, const pg_params* params, const in
     if ((st = check_knn_layout(params, N, K, row_ptr, flag, s))) return st;
     if (N == 0) return finish(s, params, flag, params->flags);
     if ((e = launch_fill_value(succ, (size_t)N * 4, 0xffffffffu, s)) != hipSuccess) return hip_fail(e, "fill");
-    if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, nullptr, nullptr, nullptr, nullptr, PG_INIT_ZERO,
-                          succ, nullptr, nullptr, flag, s)) != hipSuccess)
+    if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, nullptr, nullptr, PG_INIT_ZERO, succ,
+                           nullptr, nullptr, flag, s)) != hipSuccess)
         return hip_fail(e, "paths");
     const float* alpha = paths->albedo;
     if (paths->albedo_grid) {
@@ -548,10 +548,7 @@ static size_t edges_size(const pg_paths* p, const pg_params* q, bool* ok) {
     cv.take<int32_t>(64);
     cv.take<VRec>(N);
     cv.take<float>(N * K);    // w if the caller does not want it
-    cv.take<float>(3 * N);    // b
-    cv.take<float>(3 * N);    // dpt
-    cv.take<float>(N);        // r
-    cv.take<float>(N);        // alpha
+    cv.take<float4>(N);       // the path pass's maps
     *ok = true;
     return cv.size();
 }
@@ -583,10 +580,7 @@ pg_status pg_edges(const pg_paths* paths, const pg_params* params, const int64_t
     int32_t* flag = cv.take<int32_t>(64);
     VRec* rec = cv.take<VRec>(N);
     float* wtmp = cv.take<float>(N * K);
-    float* bl = cv.take<float>(3 * N);
-    float* dl = cv.take<float>(3 * N);
-    float* rl = cv.take<float>(N);
-    float* al = cv.take<float>(N);
+    float4* step = cv.take<float4>(N);
     hipError_t e;
     if ((params->flags & PG_FLAG_CHECK) && (e = launch_fill(flag, 64 * 4, s)) != hipSuccess)
         return hip_fail(e, "fill");   // read back only with the check
@@ -595,10 +589,9 @@ pg_status pg_edges(const pg_paths* paths, const pg_params* params, const int64_t
     if ((e = launch_pack_records(N, *paths, rec, flag, s)) != hipSuccess) return hip_fail(e, "pack");
     EdgeOut o{};
     o.w = w_ind ? w_ind : wtmp;
-    o.b = b ? b : bl;   // the rows are in path order: no copies
-    o.dpt = d_pt ? d_pt : dl;
-    o.r = rl;
-    o.alpha = al;
+    o.b = b;   // the rows are in path order: no copies
+    o.dpt = d_pt;
+    if (lplus0 && params->init == PG_INIT_PT) o.step = step;
     o.w_ph = w_ph;
     o.w_env = w_env;
     o.x0 = lplus0;
@@ -608,7 +601,7 @@ pg_status pg_edges(const pg_paths* paths, const pg_params* params, const int64_t
     Consts c = make_consts(params, K);
     if ((e = launch_edges(N, c, col, rec, o, flag, s)) != hipSuccess) return hip_fail(e, "edges");
     if (lplus0) {
-        if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, al, o.dpt, rl, paths->l_emit, params->init, nullptr,
+        if ((e = launch_paths(paths->n_paths, N, paths->path_offsets, nullptr, o.step, paths->l_emit, params->init, nullptr,
                               nullptr, lplus0, flag, s)) != hipSuccess)
             return hip_fail(e, "paths");
     }

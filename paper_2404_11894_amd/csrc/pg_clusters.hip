@@ -619,7 +619,8 @@ __global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const ui
                                                    const float* __restrict__ emit, const int32_t* __restrict__ cperm,
                                                    const int32_t* __restrict__ perm, const float* __restrict__ dir_pl,
                                                    const float* __restrict__ l_pl, float* __restrict__ b,
-                                                   float* __restrict__ dpt, float* __restrict__ r) {
+                                                   float* __restrict__ dpt, float* __restrict__ r,
+                                                   float4* __restrict__ step) {
     __shared__ float4 sm[4 * kSpan];
     __shared__ float sme[kSpan];
     const int64_t i0 = (int64_t)blockIdx.x * kBlock, i = i0 + threadIdx.x;
@@ -691,7 +692,9 @@ __global__ __launch_bounds__(kBlock) void k_cedges(int64_t N, Consts c, const ui
         dp = f3{fmaf(rp, lq.x, dp.x), fmaf(rp, lq.y, dp.y), fmaf(rp, lq.z, dp.z)};
     }
     st3(dpt, i, dp);
-    r[i] = rho / p_w;
+    const float rr = rho / p_w;
+    r[i] = rr;
+    if (step) step[i] = make_float4(fmaf(al, dp.x, em.x), fmaf(al, dp.y, em.y), fmaf(al, dp.z, em.z), al * rr);
 }
 
 // ------------------------------------------------------- the iteration ---
@@ -1385,6 +1388,8 @@ hipError_t cluster_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, c
     }
     PG_TRY(run_clusters(p, g, cb, s));
     const Consts c = make_consts(q, r.K);
+    // in place of the packed records, once they are gathered
+    float4* step = q->init == PG_INIT_PT ? reinterpret_cast<float4*>(r.rec) : nullptr;
     if (N > 0) {
         ProfScope ps(s, "edges");
         hipLaunchKernelGGL(k_crec, grid_of(N), dim3(kBlock), 0, s, N, cb.cperm, g.perm, r.rec, cr.crec, cr.tq,
@@ -1394,7 +1399,7 @@ hipError_t cluster_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, c
                            cr.me, cb.heads);
         PG_TRY(hipGetLastError());
         hipLaunchKernelGGL(k_cedges, grid_of(N), dim3(kBlock), 0, s, N, c, cb.heads, cr.crec, cr.tq, cr.mp, cr.me,
-                           p->l_emit, cb.cperm, g.perm, p->dir_pl, p->l_pl, r.b, r.dpt, r.r);
+                           p->l_emit, cb.cperm, g.perm, p->dir_pl, p->l_pl, r.b, r.dpt, r.r, step);
         PG_TRY(hipGetLastError());
     }
     if (out && (out->row_ptr || out->col)) {
@@ -1419,8 +1424,8 @@ hipError_t cluster_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, c
     PG_TRY(launch_fill(x0, (size_t)N * 12, s));
     {
         ProfScope ps(s, "paths");
-        PG_TRY(launch_paths(r.P, N, p->path_offsets, cb.cinv, r.alpha, r.dpt, r.r, p->l_emit, q->init, r.succ,
-                            r.pred, x0, g.flag, s));
+        PG_TRY(launch_paths(r.P, N, p->path_offsets, cb.cinv, step, p->l_emit, q->init, r.succ, r.pred, x0,
+                            g.flag, s));
     }
     *x0_out = x0;
     return hipSuccess;

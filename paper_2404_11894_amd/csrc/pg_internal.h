@@ -610,13 +610,14 @@ struct EdgeOut {
     int ell;             // 1: col / w / gw in the sliced-ELL layout, 0: row-major
     float* w;            // local order (required): ell_size(N, K) or N*K elements
     float* gw;           // dw/dg in the same layout, or NULL
-    float* b;            // [N] f3 local
+    float* b;            // [N] f3 local, this and the next three nullable
     float* dpt;          // [N] f3 local
     float* r;            // [N] local
     float* alpha;        // [N] local
     int32_t* succ;       // [N] local each, nullable: set to -1, -1 and 0 for the path pass, which
     int32_t* pred;       //   writes the vertices its paths cover
     float* x0;           // [N] f3
+    float4* step;        // nullable: (e + albedo d_pt, albedo r), the path pass's map of the vertex, in one piece
     const int32_t* canon_row;
     const float* emit;   // volume emission e, [N] f3 in canonical (path) order, nullable
     const float* dir_pl; // point light (canonical order), nullable
@@ -631,10 +632,9 @@ hipError_t launch_edges(int64_t N, const Consts& c, const int32_t* col, const VR
                         int32_t* flag, hipStream_t s);
 
 // per-path pass: successor / predecessor in local ids and the initial L
-hipError_t launch_paths(int64_t P, int64_t N, const int64_t* off, const int32_t* inv, const float* alpha,
-                        const float* dpt, const float* r, const float* emit, int init, int32_t* succ, int32_t* pred,
-                        float* x0,
-                        int32_t* flag, hipStream_t s);
+hipError_t launch_paths(int64_t P, int64_t N, const int64_t* off, const int32_t* inv, const float4* step,
+                        const float* emit, int init, int32_t* succ, int32_t* pred, float* x0, int32_t* flag,
+                        hipStream_t s);
 
 // propagation
 hipError_t launch_spmv(int64_t N, int K, const int32_t* col, const float* w, const float* x, const float* b,

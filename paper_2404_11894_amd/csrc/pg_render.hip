@@ -115,6 +115,7 @@ hipError_t render_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, co
     o.succ = r.succ;
     o.pred = r.pred;
     o.x0 = x0;
+    if (q->init == PG_INIT_PT) o.step = reinterpret_cast<float4*>(r.recp);   // the packed records are gathered by now
     if (out) {
         o.w_ind = out->w_ind;
         o.w_ph = out->w_ph;
@@ -132,8 +133,8 @@ hipError_t render_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, co
     }
     {
         ProfScope ps(s, "paths");
-        PG_TRY(launch_paths(r.P, N, p->path_offsets, g.inv, r.alpha, r.dpt, r.r, p->l_emit, q->init, r.succ, r.pred, x0,
-                            g.flag, s));
+        PG_TRY(launch_paths(r.P, N, p->path_offsets, g.inv, o.step, p->l_emit, q->init, r.succ, r.pred, x0, g.flag,
+                            s));
     }
     if (r.schedule == PG_SCHED_SCATTER) {
         // path ends are never written by the scatter: they stay 0 in every buffer
