@@ -292,9 +292,9 @@ def time_clusters(pg, torch, sc, w, steps, warmup, knn_ms):
     adj_ms = (time.perf_counter() - t0) * 1e3 / n_adj
     adj_ok = bool(torch.isfinite(g_out["grad_grid"]).all().item())
     del rt
-    # per row: (t, albedo) 16, range 8, b 12, y 12; each member's (w, 1/M+) 16 once, and its x: 12 read
-    # (first iteration) or successor id 4 + gathered y 12 (the others, propagation folded in)
-    ab = N * (76 + 80 * (w.D - 1)) / w.D
+    # per row: (t, albedo) 16, one bit of range, b 12, y 12; each member's (w, 1/M+) 16 once, and its x: 12
+    # read (first iteration) or successor id 4 + gathered y 12 (the others, propagation folded in)
+    ab = N * ((68 + 72 * (w.D - 1)) / w.D + 0.125)
     flops = 22 * E  # per edge: 1 - cos 9, HG 7 (one rsqrt), 1/M+ 1, accumulate 6 (FMA = 2)
     del paths
     torch.cuda.empty_cache()
