@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
         sz += __shfl_xor(sz, o, kWave);
     }
     if (px >= npix || lane != 0 || grp != 0) return;
-    const double inv_spp = 1.0 / (double)P.spp;
+    const double inv_spp = (double)(1.0f / (float)P.spp);   // the factor of the output's adjoint
     image[3 * px] = (float)(sx * inv_spp);
     image[3 * px + 1] = (float)(sy * inv_spp);
     image[3 * px + 2] = (float)(sz * inv_spp);
