@@ -754,9 +754,9 @@ __device__ __forceinline__ void stage_span(const Span& sp, int64_t i0, int64_t N
                                            const float4* __restrict__ aq, const float* __restrict__ xq,
                                            const int32_t* __restrict__ succ, float4* sa, float* sx) {
     const uint32_t rows = (uint32_t)(N - i0 < kBlock ? N - i0 : kBlock), first = (uint32_t)i0 - sp.lo;
-    static_assert(kSpan <= 2 * kBlock, "one turn over the margins");
-    if (threadIdx.x < sp.n - rows) {
-        const uint32_t t = threadIdx.x < first ? threadIdx.x : threadIdx.x + rows;
+    // one turn, but for the last block, which has fewer rows and so up to kSpan - 1 others
+    for (uint32_t u = threadIdx.x; u < sp.n - rows; u += kBlock) {
+        const uint32_t t = u < first ? u : u + rows;
         Stage<SHIFTED, NT> margin;
         margin.load((int64_t)sp.lo + t, aq, xq, succ);
         margin.store(t, sa, sx);
