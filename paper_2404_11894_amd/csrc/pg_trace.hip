@@ -25,6 +25,7 @@
 #include <cmath>
 
 #include "pg_api_common.h"
+#include "pg_quotient.h"
 
 #pragma clang fp contract(off)
 
@@ -64,16 +65,6 @@ struct D3 {
 __device__ inline D3 d3(double x, double y, double z) { return D3{x, y, z}; }
 __device__ inline double comp(const D3& v, int a) { return a == 0 ? v.x : (a == 1 ? v.y : v.z); }
 
-// a / b, correctly rounded, with y = 1 / b correctly rounded: two Newton
-// corrections of a y, each from an exact remainder (Markstein, "IA-64 and
-// elementary functions", 2000, ch. 8).  Five operations instead of a division
-// of its own; a and the quotient are normal numbers or 0 here.
-__device__ __forceinline__ double div_by(double a, double b, double y) {
-    double q = a * y;
-    q = fma(fma(-b, q, a), y, q);
-    return fma(fma(-b, q, a), y, q);
-}
-
 __device__ inline D3 normalized(D3 v) {
     const double l = sqrt(v.x * v.x + v.y * v.y + v.z * v.z);
     return d3(v.x / l, v.y / l, v.z / l);
@@ -86,7 +77,7 @@ struct Tracer {
     // camera frame
     D3 f, r, up;
     double th, aspect;
-    double inv_maj;   // 1 / majorant, correctly rounded
+    double inv_maj;   // 1 / t.majorant, correctly rounded
 };
 
 __device__ inline size_t voxel_of(const pg_tracer& t, const D3& p) {
@@ -561,7 +552,8 @@ static Tracer make_tracer(const pg_tracer* t) {
     tr.up = D3{up[0], up[1], up[2]};
     tr.th = std::tan(0.5 * t->vfov_deg * M_PI / 180.0);
     tr.aspect = (double)t->width / (double)t->height;
-    tr.inv_maj = t->majorant > 0.0 ? 1.0 / t->majorant : 0.0;
+    tr.t.majorant = walked_majorant(t->majorant);
+    tr.inv_maj = tr.t.majorant > 0.0 ? 1.0 / tr.t.majorant : 0.0;
     return tr;
 }
 
