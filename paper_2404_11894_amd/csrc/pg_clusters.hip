@@ -519,15 +519,20 @@ struct Span {
 };
 
 // The last head in the words up to w, the first in those from w on; N past the
-// end.  h: word w, requested before (a cluster rarely reaches further).
+// end.  h: word w, requested before (a cluster rarely reaches further).  Each load
+// waits for the one before, so the walk ends where the cluster is known to be above
+// kClusterMax, at a position that leaves it so (bounded, and no block stages it).
+constexpr int kHeadWords = kClusterMax / kWave + 1;
 __device__ __forceinline__ uint32_t last_head(const uint64_t* __restrict__ heads, uint64_t h, int64_t w) {
-    while (h == 0 && w > 0) h = heads[--w];
-    return h ? (uint32_t)w * kWave + (63u - (uint32_t)__clzll((long long)h)) : 0u;
+    const int64_t end = w > kHeadWords ? w - kHeadWords : 0;
+    while (h == 0 && w > end) h = heads[--w];
+    return h ? (uint32_t)w * kWave + (63u - (uint32_t)__clzll((long long)h)) : (uint32_t)end * kWave;
 }
 __device__ __forceinline__ uint32_t next_head(const uint64_t* __restrict__ heads, uint64_t h, int64_t w, int64_t N) {
-    const int64_t nw = div_up(N, kWave);
-    while (h == 0 && ++w < nw) h = heads[w];
-    return h ? (uint32_t)w * kWave + (uint32_t)__ffsll((unsigned long long)h) - 1u : (uint32_t)N;
+    const int64_t nw = div_up(N, kWave), end = w + kHeadWords + 1 < nw ? w + kHeadWords + 1 : nw;
+    while (h == 0 && ++w < end) h = heads[w];
+    return h ? (uint32_t)w * kWave + (uint32_t)__ffsll((unsigned long long)h) - 1u
+             : (uint32_t)(end < nw ? end * kWave : N);
 }
 
 __device__ __forceinline__ Span block_span(const uint64_t* __restrict__ heads, int64_t i0, int64_t N) {
@@ -549,6 +554,8 @@ __device__ __forceinline__ Span block_span(const uint64_t* __restrict__ heads, i
     Span sp;
     sp.lo = (h[1] & 1) ? (uint32_t)i0 : last_head(heads, h[0], w0 - 1);
     sp.n = next_head(heads, h[W + 1], w0 + W, N) - sp.lo;
+    sp.rg = make_uint2(0u, 0u);
+    if (w >= nw) return sp;   // no rows: nothing was written of its words
     const uint32_t before = (cur & 1) ? (uint32_t)(w * kWave) : last_head(heads, prev, w - 1);
     const uint32_t after = next_head(heads, next, w + 1, N);
     const uint64_t at = cur & (~0ull >> (63u - lane)), past = lane == 63u ? 0ull : cur >> (lane + 1u);
