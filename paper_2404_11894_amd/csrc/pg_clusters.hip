@@ -1253,7 +1253,7 @@ void carve_clusters(Carver& cv, ClusterBufs& cb, int64_t N, int K) {
     cb.part = cv.take<unsigned long long>(div_up(N, kBlock) + 1);
     cb.live = cv.take<int32_t>(64);   // [0] = 1, [1 + r] = a cluster was split in round r
     cb.gcount = cv.take<uint32_t>(cb.ncells + 1);
-    cb.gpart = cv.take<uint32_t>(scan_partials_bytes(cb.ncells + 1) / 4);
+    cb.gpart = cv.take<uint32_t>(scan_partials_bytes(cb.ncells) / 4);
     cb.gcell = cv.take<uint32_t>(N);
     cb.grank = cv.take<uint32_t>(N);
     cb.gpts = cv.take<float4>(N);
@@ -1289,11 +1289,11 @@ static dim3 grid_of(int64_t n) { return dim3((unsigned)div_up(n > 0 ? n : 1, kBl
 // Groups the vertices by cluster (counts, starts, members): once, after the
 // nearest-centre assignment; the split rounds then regroup in place.
 static hipError_t group(const pg_paths* p, const GridBufs& g, int64_t N, ClusterBufs& cb, hipStream_t s) {
-    PG_TRY(launch_fill(cb.ccount, (size_t)(N + 1) * 4, s));
+    PG_TRY(launch_fill(cb.ccount, (size_t)N * 4, s));
     PG_TRY(launch_fill(cb.cfill, (size_t)N * 4, s));
     hipLaunchKernelGGL(k_ccount, grid_of(N), dim3(kBlock), 0, s, N, cb.cid, cb.ccount);
     PG_TRY(hipGetLastError());
-    PG_TRY(launch_scan_exclusive(cb.ccount, cb.cstart, N + 1, cb.cpart, s));
+    PG_TRY(launch_scan_exclusive(cb.ccount, cb.cstart, N, cb.cpart, s));
     hipLaunchKernelGGL(k_cgroup, grid_of(N), dim3(kBlock), 0, s, N, cb.cid, cb.cstart, cb.cfill, g.perm,
                        p->cluster_key, g.qs, cb.members, cb.mslot, cb.mkey, cb.mq);
     return hipGetLastError();
@@ -1314,11 +1314,11 @@ hipError_t run_clusters(const pg_paths* p, GridBufs& g, ClusterBufs& cb, hipStre
     PG_TRY(hipGetLastError());
     const unsigned long long thr = (1ull << 32) / (unsigned long long)K;
     // uniform grid of the centres
-    PG_TRY(launch_fill(cb.gcount, (size_t)(cb.ncells + 1) * 4, s));
+    PG_TRY(launch_fill(cb.gcount, (size_t)cb.ncells * 4, s));
     hipLaunchKernelGGL(k_cg_count, grid_of(N), dim3(kBlock), 0, s, N, g.perm, p->cluster_key, thr, cb.kmin, g.qs,
                        cb.bits, cb.gcount, cb.gcell, cb.grank);
     PG_TRY(hipGetLastError());
-    PG_TRY(launch_scan_exclusive(cb.gcount, cb.gcount, cb.ncells + 1, cb.gpart, s));
+    PG_TRY(launch_scan_exclusive(cb.gcount, cb.gcount, cb.ncells, cb.gpart, s));
     hipLaunchKernelGGL(k_cg_scatter, grid_of(N), dim3(kBlock), 0, s, N, g.perm, p->cluster_key, thr, cb.kmin, g.qs,
                        cb.gcell, cb.grank, cb.gcount, cb.gpts);
     PG_TRY(hipGetLastError());
@@ -1416,8 +1416,8 @@ hipError_t cluster_setup(const pg_paths* p, const pg_params* q, RenderBufs& r, c
             hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(1024), 0, s, div_up(N, kBlock), cb.part, cb.nedge);
             PG_TRY(hipGetLastError());
         }
-        PG_TRY(launch_fill(cr.rowlen + N, 4, s));
-        PG_TRY(launch_scan_exclusive(cr.rowlen, cr.rowlen, N + 1, cr.rowpart, s));
+        if (N > 0) PG_TRY(launch_scan_exclusive(cr.rowlen, cr.rowlen, N, cr.rowpart, s));
+        else PG_TRY(launch_fill(cr.rowlen, 4, s));
         hipLaunchKernelGGL(k_cexport, grid_of(N + 1), dim3(kBlock), 0, s, N, c, cr.rowlen, cb.nedge,
                            out->edge_capacity, cb.cinv, cb.crange, cb.cperm, g.perm, cr.crec, cr.tq, cr.wq, cr.mp,
                            cr.me, out->row_ptr, out->col, out->w_ind, out->w_ph, out->w_env, g.flag);

@@ -73,10 +73,10 @@ hipError_t launch_cell_range(int64_t ncells, int shift, const uint32_t* start, u
 }
 
 // ------------------------------------------------------------------ scan ---
-// Exclusive prefix sum of uint32 counts, out[n] = total.  Three passes:
-// per-block totals, a scan of the block totals, per-block scans with offset.
-// Inside a block: per-thread serial sums, a wave-level inclusive scan with
-// lane shuffles, and a scan of the wave totals through LDS.
+// Exclusive prefix sum of n uint32 counts into the n + 1 elements of out, out[n] =
+// total.  Three passes: per-block totals, a scan of the block totals, per-block
+// scans with offset.  Inside a block: per-thread serial sums, a wave-level
+// inclusive scan with lane shuffles, and a scan of the wave totals through LDS.
 
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kBlock * kScanItems;

@@ -608,7 +608,7 @@ hipError_t run_trace_count(const pg_tracer* t, int64_t* path_offsets, float* e_c
     Carver cv(ws);
     const TraceWs w = carve_trace(cv, t);
     hipError_t e;
-    if ((e = launch_fill(w.count, (size_t)(P + 1) * 4, s)) != hipSuccess) return e;
+    if ((e = launch_fill(w.count, (size_t)P * 4, s)) != hipSuccess) return e;
     if ((e = launch_fill(w.next, 4, s)) != hipSuccess) return e;
     const Tracer tr = make_tracer(t);
     if (P > 0) {
@@ -625,7 +625,7 @@ hipError_t run_trace_count(const pg_tracer* t, int64_t* path_offsets, float* e_c
         else go(std::false_type{}, std::false_type{});
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if ((e = launch_scan_exclusive(w.count, w.count, P + 1, w.part, s)) != hipSuccess) return e;
+    if ((e = launch_scan_exclusive(w.count, w.count, P, w.part, s)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_widen, dim3((unsigned)div_up(P + 1, kBlock)), dim3(kBlock), 0, s, P + 1, w.count,
                        path_offsets);
     return hipGetLastError();
