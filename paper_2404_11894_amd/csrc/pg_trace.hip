@@ -314,9 +314,9 @@ __device__ __forceinline__ void store_phase(const Slab& slab, int64_t slot, floa
 
 // The flight has ended: at the path's next vertex, whose sun ray starts, or
 // outside, which ends the path.
-template <bool PL, bool EXTRA>
+template <bool PL>
 __device__ __forceinline__ void flight_ended(const Tracer& tr, Walk& w, const Slab& slab,
-                                             uint32_t* __restrict__ count, const Out& o, float* __restrict__ ecam) {
+                                             uint32_t* __restrict__ count, float* __restrict__ ecam) {
     const pg_tracer& t = tr.t;
     const int64_t slot = (int64_t)w.p * t.max_depth + w.nv;
     const float ex = w.hit ? 0.0f : (float)t.env_L[0], ey = w.hit ? 0.0f : (float)t.env_L[1],
@@ -328,19 +328,7 @@ __device__ __forceinline__ void flight_ended(const Tracer& tr, Walk& w, const Sl
     } else {
         store_phase<PL>(slab, slot, ex, ey, ez);
     }
-    const bool first = w.nv < 0;
     if (w.hit) w.o = d3(w.o.x + w.s * w.dir.x, w.o.y + w.s * w.dir.y, w.o.z + w.s * w.dir.z);
-    if (EXTRA && first) {
-        const int64_t p = w.p;
-        if (w.hit) {
-            const int64_t pix = p / t.spp;
-            const int X = tr.cx0 + (int)(pix % tr.cw), Y = tr.cy0 + (int)(pix / tr.cw);
-            extra_samples(tr, (uint64_t)Y * (uint64_t)t.width + (uint64_t)X, (int)(p % t.spp), w.o, p, o);
-        } else {   // no first vertex: zero samples
-            for (int64_t b = p * t.extra_samples * 3; b < (p + 1) * t.extra_samples * 3; ++b)
-                o.fb_l_sun[b] = o.fb_dir_env[b] = o.fb_l_env[b] = 0.0f;
-        }
-    }
     ++w.nv;
     if (!w.hit) {
         count[w.p] = (uint32_t)w.nv;
@@ -427,17 +415,24 @@ __device__ __forceinline__ void shadow_ended(const Tracer& tr, Walk& w, const Sl
 // kinds of rays are fewer than kBehind, so not all lanes can be left behind; and
 // the queue's counter only grows: the wave leaves when it is empty and no lane
 // has a path.
+//
+// Few paths leave the chip to single waves, whose time is that of their slowest
+// lanes in turn: then fewer lanes a wave take paths (width).  64 / 16 / 8 lanes: 16
+// thousand paths of the small cube 0.348 / 0.337 / 0.362 ms, 4 thousand 0.341 / 0.331 /
+// 0.293, 4 thousand on the ball 1.44 / 1.32 / 1.05; 66 thousand of the cube 0.354 / 0.402.
 constexpr int kRefill = 8, kBehind = 8;
 constexpr int kTraceBlocks = 2048;
-template <bool PL, bool EXTRA>
-__global__ __launch_bounds__(kBlock) void k_trace(Tracer tr, uint32_t P, uint32_t* __restrict__ next,
-                                                  uint32_t* __restrict__ count, Slab slab, Out o,
+constexpr int kMinWidth = kRefill, kNarrowWaves = 512;
+template <bool PL>
+__global__ __launch_bounds__(kBlock) void k_trace(Tracer tr, uint32_t P, int width, uint32_t* __restrict__ next,
+                                                  uint32_t* __restrict__ count, Slab slab,
                                                   float* __restrict__ ecam) {
     Walk w;
     const int lane = threadIdx.x & (kWave - 1);
+    const uint64_t lanes = ~0ull >> (kWave - width);
     bool dry = false;   // the queue is empty (uniform over the wave)
     for (;;) {
-        const uint64_t idle = __ballot(w.state == kIdle);
+        const uint64_t idle = __ballot(w.state == kIdle) & lanes;
         const int n = __popcll(idle);
         if (!dry && n >= kRefill) {
             uint32_t base = 0;
@@ -445,16 +440,16 @@ __global__ __launch_bounds__(kBlock) void k_trace(Tracer tr, uint32_t P, uint32_
             base = (uint32_t)__shfl((int)base, 0, kWave);
             dry = (uint64_t)base + (uint32_t)n >= P;
             const uint64_t p = (uint64_t)base + __popcll(idle & ((1ull << lane) - 1ull));
-            if (w.state == kIdle && p < P) {
+            if (w.state == kIdle && lane < width && p < P) {
                 w.p = (uint32_t)p;
                 start_path(tr, w);
             }
-        } else if (n == kWave) {
+        } else if (n == width) {
             break;   // dry, and no path left
         }
-        const int behind = (kWave - __popcll(__ballot(w.state == kIdle))) / kBehind;
+        const int behind = __popcll(__ballot(w.state != kIdle)) / kBehind;
         track<kFlight>(tr, w, behind);
-        if (w.state == kEnd && w.ray == kFlight) flight_ended<PL, EXTRA>(tr, w, slab, count, o, ecam);
+        if (w.state == kEnd && w.ray == kFlight) flight_ended<PL>(tr, w, slab, count, ecam);
         track<kSun>(tr, w, behind);
         if (w.state == kEnd && w.ray == kSun) sun_ended(w);
         track<kEnv>(tr, w, behind);
@@ -463,6 +458,30 @@ __global__ __launch_bounds__(kBlock) void k_trace(Tracer tr, uint32_t P, uint32_
             track<kPoint>(tr, w, behind);
             if (w.state == kEnd && w.ray == kPoint) shadow_ended<PL>(tr, w, slab, count);
         }
+    }
+}
+
+// The extra samples of every path's first vertex, one thread a path: it walks the
+// camera ray again, which is short beside the samples' rays, and all lanes of a wave
+// have their samples to do together.  In k_trace, where few lanes come to a first
+// vertex at a time, 64 samples a path took the wave three times as long (256 x 256 at
+// 4 samples on a ball: 28.9 ms with the paths, 7.2 so).
+__global__ __launch_bounds__(kBlock) void k_trace_extra(Tracer tr, uint32_t P, Out o) {
+    const pg_tracer& t = tr.t;
+    const uint32_t p = blockIdx.x * kBlock + threadIdx.x;
+    if (p >= P) return;
+    Walk w;
+    w.p = p;
+    start_path(tr, w);
+    while (w.state == kStep) step<true>(tr, w);
+    if (w.hit) {
+        const int64_t pix = (int64_t)p / t.spp;
+        const int X = tr.cx0 + (int)(pix % tr.cw), Y = tr.cy0 + (int)(pix / tr.cw);
+        const D3 pt = d3(w.o.x + w.s * w.dir.x, w.o.y + w.s * w.dir.y, w.o.z + w.s * w.dir.z);
+        extra_samples(tr, (uint64_t)Y * (uint64_t)t.width + (uint64_t)X, (int)(p % (uint32_t)t.spp), pt, p, o);
+    } else {   // no first vertex: zero samples
+        for (int64_t b = (int64_t)p * t.extra_samples * 3; b < ((int64_t)p + 1) * t.extra_samples * 3; ++b)
+            o.fb_l_sun[b] = o.fb_dir_env[b] = o.fb_l_env[b] = 0.0f;
     }
 }
 
@@ -613,16 +632,19 @@ hipError_t run_trace_count(const pg_tracer* t, int64_t* path_offsets, float* e_c
     const Tracer tr = make_tracer(t);
     if (P > 0) {
         ProfScope ps(s, "trace_count");
-        const dim3 grid((unsigned)std::min<int64_t>(kTraceBlocks, div_up(P, kBlock)));
-        auto go = [&](auto pl, auto extra) {
-            hipLaunchKernelGGL((k_trace<decltype(pl)::value, decltype(extra)::value>), grid, dim3(kBlock), 0, s, tr,
-                               (uint32_t)P, w.next, w.count, w.slab, w.fb, w.ecam);
-        };
-        const bool extra = t->extra_samples > 0;
-        if (tr.point_light && extra) go(std::true_type{}, std::true_type{});
-        else if (tr.point_light) go(std::true_type{}, std::false_type{});
-        else if (extra) go(std::false_type{}, std::true_type{});
-        else go(std::false_type{}, std::false_type{});
+        int width = kWave;
+        while (width > kMinWidth && P <= (int64_t)width * kNarrowWaves) width /= 2;
+        const dim3 grid((unsigned)std::min<int64_t>(kTraceBlocks, div_up(P, width * (kBlock / kWave))));
+        if (tr.point_light)
+            hipLaunchKernelGGL(k_trace<true>, grid, dim3(kBlock), 0, s, tr, (uint32_t)P, width, w.next, w.count, w.slab,
+                               w.ecam);
+        else
+            hipLaunchKernelGGL(k_trace<false>, grid, dim3(kBlock), 0, s, tr, (uint32_t)P, width, w.next, w.count,
+                               w.slab, w.ecam);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (t->extra_samples > 0)
+            hipLaunchKernelGGL(k_trace_extra, dim3((unsigned)div_up(P, kBlock)), dim3(kBlock), 0, s, tr, (uint32_t)P,
+                               w.fb);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if ((e = launch_scan_exclusive(w.count, w.count, P, w.part, s)) != hipSuccess) return e;
