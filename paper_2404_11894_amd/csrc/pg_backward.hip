@@ -350,11 +350,11 @@ __global__ __launch_bounds__(kBlock) void k_out_adjoint(pg_paths P, Consts c, co
         in = f3{(float)group_sum<KP>(ix), (float)group_sum<KP>(iy), (float)group_sum<KP>(iz)};
         ing = f3{(float)group_sum<KP>(gx), (float)group_sum<KP>(gy), (float)group_sum<KP>(gz)};
     }
+    const bool extra = P.n_extra > 0;
+    f3 d{0.f, 0.f, 0.f}, ddg{0.f, 0.f, 0.f};
+    if (on && extra) d = extra_direct<KP>(P, p, a, ld3(P.dir_in, a), c.rho, c.g, c.sun, c.env_pdf, &ddg, lane);
     if (on && lane == 0) {
-        const bool extra = P.n_extra > 0;
-        f3 ddg{0.f, 0.f, 0.f};
-        const f3 d = extra ? extra_direct(P, p, a, ld3(P.dir_in, a), c.rho, c.g, c.sun, c.env_pdf, &ddg)
-                           : ld3(dpt, s0);
+        if (!extra) d = ld3(dpt, s0);
         if (extra) gl += (double)dot3(zb, ddg);
         if (c.final_gather == 0) {
             abar[s0] += dot3(ob, f3{d.x + in.x, d.y + in.y, d.z + in.z});

@@ -389,15 +389,19 @@ __device__ inline float one_minus_cos(f3 a, f3 b) {
 // path p (paths->n_extra = M > 0): (1/M) sum_m (rho(sun) Ls_m + rho(we_m)
 // Le_m / env_pdf), rho about the first vertex's arriving direction t; with
 // dg != NULL also its derivative with respect to g (rho h, h = d ln HG/dg).
+// KP > 1: the KP lanes of a group, all of them here, take every KP-th sample
+// (their records lie side by side) and all get the result.
 __device__ inline float hg_dlog(float g, float u);
-template <class Rho>
+template <int KP, typename T>
+__device__ inline T group_sum(T v);
+template <int KP = 1, class Rho>
 __device__ inline f3 extra_direct(const pg_paths& P, int64_t p, int64_t v0, f3 t, const Rho& rho, float g, f3 sun,
-                                  float env_pdf, f3* dg) {
+                                  float env_pdf, f3* dg, int lane = 0) {
     const int M = P.n_extra;
     const float us = one_minus_cos(t, sun);
     const float rs = rho(us), hs = dg ? hg_dlog(g, us) : 0.0f;
     f3 d{0.f, 0.f, 0.f}, e{0.f, 0.f, 0.f};
-    for (int m = 0; m < M; ++m) {
+    for (int m = lane; m < M; m += KP) {
         const int64_t o = ((int64_t)p * M + m) * 3;
         const f3 we{P.fb_dir_env[o], P.fb_dir_env[o + 1], P.fb_dir_env[o + 2]};
         const float u = one_minus_cos(t, we);
@@ -411,6 +415,14 @@ __device__ inline f3 extra_direct(const pg_paths& P, int64_t p, int64_t v0, f3 t
             e.y += rs * hs * P.fb_l_sun[o + 1] + re * he * P.fb_l_env[o + 1];
             e.z += rs * hs * P.fb_l_sun[o + 2] + re * he * P.fb_l_env[o + 2];
         }
+    }
+    if constexpr (KP > 1) {
+        auto sum = [](f3 v) {
+            return f3{(float)group_sum<KP>((double)v.x), (float)group_sum<KP>((double)v.y),
+                      (float)group_sum<KP>((double)v.z)};
+        };
+        d = sum(d);
+        if (dg) e = sum(e);
     }
     const float inv = 1.0f / (float)M;
     d = f3{d.x * inv, d.y * inv, d.z * inv};

@@ -16,6 +16,8 @@
 //    albedo_u w_u. and b_u of its successor u, so one pass per iteration
 //    computes L directly.
 // Both are sparse gathers bound by HBM bandwidth (about 0.5 flop per byte).
+#include <algorithm>
+
 #include "pg_internal.h"
 
 namespace pg {
@@ -328,8 +330,8 @@ hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t*
                            const int32_t* succ, int32_t* scol, float* sw, float* sb, float* sx, float* salpha,
                            int32_t* ssucc, hipStream_t s) {
     if (N == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_relayout, dim3((unsigned)div_up(N * (ell_k4(K) / 4), kBlock)), dim3(kBlock), 0, s, N, K, perm, inv, col, w,
-                       b, x0, alpha, succ, scol, sw, sb, sx, salpha, ssucc);
+    hipLaunchKernelGGL(k_relayout, dim3((unsigned)div_up(N * (ell_k4(K) / 4), kBlock)), dim3(kBlock), 0, s, N, K, perm,
+                       inv, col, w, b, x0, alpha, succ, scol, sw, sb, sx, salpha, ssucc);
     return hipGetLastError();
 }
 
@@ -492,8 +494,14 @@ hipError_t launch_spmv_shifted(int64_t N, int K, const int32_t* succ, const int3
 // by side a wave waits for one (5 and 225 us).  Products and sums are in double
 // precision, hidden behind the loads: in single precision, split over lanes, the
 // image was 4% further off than by one thread's chain of fused operations.
-template <int KP, int S>
-__global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const int32_t* __restrict__ inv,
+//
+// Extra samples at the first vertex are read by all lanes of the group, from
+// kExtraSpread of them on: the records of a path lie side by side, which one lane
+// reads line by line (512 x 512 at 4 samples, k = 16: 16 extra samples 0.57 -> 0.25
+// ms; two 0.23 either way, one 0.20 and 0.22).
+constexpr int kExtraSpread = 3;
+template <int KP, int S, bool SPREAD>
+__global__ __launch_bounds__(kBlock) void k_pixels(int64_t px0, pg_paths P, Consts c, const int32_t* __restrict__ inv,
                                                    const int32_t* __restrict__ col, const float* __restrict__ w,
                                                    const float* __restrict__ x, const float* __restrict__ dpt,
                                                    const float* __restrict__ r, const float* __restrict__ alpha,
@@ -503,103 +511,106 @@ __global__ __launch_bounds__(kBlock) void k_pixels(pg_paths P, Consts c, const i
     const int64_t npix = (int64_t)P.width * P.height;
     const int64_t N = P.n_vertices;
     const int K = c.K;
-    // one turn, but for an image of more threads than a launch may have
-    for (int64_t first = (int64_t)blockIdx.x * (kBlock / W); first < npix; first += (int64_t)gridDim.x * (kBlock / W)) {
-        const int64_t px = first + threadIdx.x / W;
-        double sx = 0.0, sy = 0.0, sz = 0.0;
-        for (int k0 = 0; k0 < P.spp; k0 += S) {   // the same trips on every lane: all take part in the sums
-            const int k = k0 + grp;
-            const int64_t p = px * P.spp + k;
-            const bool path = px < npix && k < P.spp;
-            int64_t a = 0;
-            bool on = false;
-            if (path) {
-                a = P.path_offsets[p];
-                const int64_t e = P.path_offsets[p + 1];
-                on = e > a;
-                if (on && (a < 0 || e > N)) {
-                    if (lane == 0) set_flag(flag, kFlagOffsets);
-                    on = false;
-                }
+    const int64_t px = px0 + ((int64_t)blockIdx.x * kBlock + threadIdx.x) / W;
+    double sx = 0.0, sy = 0.0, sz = 0.0;
+    for (int k0 = 0; k0 < P.spp; k0 += S) {   // the same trips on every lane: all take part in the sums
+        const int k = k0 + grp;
+        const int64_t p = px * P.spp + k;
+        const bool path = px < npix && k < P.spp;
+        int64_t a = 0;
+        bool on = false;
+        if (path) {
+            a = P.path_offsets[p];
+            const int64_t e = P.path_offsets[p + 1];
+            on = e > a;
+            if (on && (a < 0 || e > N)) {
+                if (lane == 0) set_flag(flag, kFlagOffsets);
+                on = false;
             }
-            const int64_t s0 = on ? (inv ? (int64_t)inv[a] : a) : 0;
-            double ix = 0.0, iy = 0.0, iz = 0.0;
-            if (c.final_gather == 0) {
-                if (on && lane < K) {
-                    const int64_t e = inv ? eidx(s0, lane, K) : s0 * K + lane;
-                    const int64_t j = col[e];
-                    if (j < 0 || j >= N) {
-                        set_flag(flag, kFlagIndex);
-                    } else {
-                        const double ww = w[e];
-                        const f3 xv = ld3(x, j);
-                        ix = ww * xv.x;
-                        iy = ww * xv.y;
-                        iz = ww * xv.z;
-                    }
-                }
-                ix = group_sum<KP>(ix);
-                iy = group_sum<KP>(iy);
-                iz = group_sum<KP>(iz);
-            } else if (on && lane == 0) {
-                double rr;
-                if (r) {
-                    rr = r[s0];
+        }
+        const int64_t s0 = on ? (inv ? (int64_t)inv[a] : a) : 0;
+        double ix = 0.0, iy = 0.0, iz = 0.0;
+        if (c.final_gather == 0) {
+            if (on && lane < K) {
+                const int64_t e = inv ? eidx(s0, lane, K) : s0 * K + lane;
+                const int64_t j = col[e];
+                if (j < 0 || j >= N) {
+                    set_flag(flag, kFlagIndex);
                 } else {
-                    const f3 t = ld3(P.dir_in, a), wo = ld3(P.dir_out, a);
-                    const float u = one_minus_cos(t, wo);
-                    rr = c.rho(u) / c.pdf(u);
+                    const double ww = w[e];
+                    const f3 xv = ld3(x, j);
+                    ix = ww * xv.x;
+                    iy = ww * xv.y;
+                    iz = ww * xv.z;
                 }
-                ix = rr * x[3 * s0];
-                iy = rr * x[3 * s0 + 1];
-                iz = rr * x[3 * s0 + 2];
             }
-            if (lane != 0) continue;
-            if (path) {
-                sx += P.e_cam[3 * p];
-                sy += P.e_cam[3 * p + 1];
-                sz += P.e_cam[3 * p + 2];
-            }
-            if (!on) continue;
-            float al;
-            if (alpha) {
-                al = alpha[s0];
-            } else if (P.albedo_grid) {
-                uint32_t idx[8];
-                float tw[8];
-                trilerp_corners(P.albedo_grid_res, P.pos[3 * a], P.pos[3 * a + 1], P.pos[3 * a + 2], idx, tw);
-                al = 0.0f;
-                for (int q = 0; q < 8; ++q) al = fmaf(tw[q], P.albedo_grid[idx[q]], al);
+            ix = group_sum<KP>(ix);
+            iy = group_sum<KP>(iy);
+            iz = group_sum<KP>(iz);
+        } else if (on && lane == 0) {
+            double rr;
+            if (r) {
+                rr = r[s0];
             } else {
-                al = P.albedo[a];
+                const f3 t = ld3(P.dir_in, a), wo = ld3(P.dir_out, a);
+                const float u = one_minus_cos(t, wo);
+                rr = c.rho(u) / c.pdf(u);
             }
-            if (P.l_emit) {   // volume emission of the first vertex, seen by the camera unscattered
-                sx += P.l_emit[3 * a];
-                sy += P.l_emit[3 * a + 1];
-                sz += P.l_emit[3 * a + 2];
-            }
-            f3 dd = ld3(dpt, s0);
-            if (P.n_extra > 0) dd = extra_direct(P, p, a, ld3(P.dir_in, a), c.rho, c.g, c.sun, c.env_pdf, nullptr);
-            sx = fma((double)al, (double)dd.x + ix, sx);
-            sy = fma((double)al, (double)dd.y + iy, sy);
-            sz = fma((double)al, (double)dd.z + iz, sz);
+            ix = rr * x[3 * s0];
+            iy = rr * x[3 * s0 + 1];
+            iz = rr * x[3 * s0 + 2];
         }
-        // the groups' sums (held by their lanes 0)
-#pragma unroll
-        for (int o = KP; o < W; o <<= 1) {
-            sx += __shfl_xor(sx, o, kWave);
-            sy += __shfl_xor(sy, o, kWave);
-            sz += __shfl_xor(sz, o, kWave);
+        f3 spread{0.f, 0.f, 0.f};
+        if (SPREAD && on)
+            spread = extra_direct<KP>(P, p, a, ld3(P.dir_in, a), c.rho, c.g, c.sun, c.env_pdf, nullptr, lane);
+        if (lane != 0) continue;
+        if (path) {
+            sx += P.e_cam[3 * p];
+            sy += P.e_cam[3 * p + 1];
+            sz += P.e_cam[3 * p + 2];
         }
-        if (px >= npix || lane != 0 || grp != 0) continue;
-        const double inv_spp = (double)(1.0f / (float)P.spp);   // the factor of the output's adjoint
-        image[3 * px] = (float)(sx * inv_spp);
-        image[3 * px + 1] = (float)(sy * inv_spp);
-        image[3 * px + 2] = (float)(sz * inv_spp);
+        if (!on) continue;
+        float al;
+        if (alpha) {
+            al = alpha[s0];
+        } else if (P.albedo_grid) {
+            uint32_t idx[8];
+            float tw[8];
+            trilerp_corners(P.albedo_grid_res, P.pos[3 * a], P.pos[3 * a + 1], P.pos[3 * a + 2], idx, tw);
+            al = 0.0f;
+            for (int q = 0; q < 8; ++q) al = fmaf(tw[q], P.albedo_grid[idx[q]], al);
+        } else {
+            al = P.albedo[a];
+        }
+        if (P.l_emit) {   // volume emission of the first vertex, seen by the camera unscattered
+            sx += P.l_emit[3 * a];
+            sy += P.l_emit[3 * a + 1];
+            sz += P.l_emit[3 * a + 2];
+        }
+        f3 dd = SPREAD ? spread : ld3(dpt, s0);
+        if (!SPREAD && P.n_extra > 0)
+            dd = extra_direct(P, p, a, ld3(P.dir_in, a), c.rho, c.g, c.sun, c.env_pdf, nullptr);
+        sx = fma((double)al, (double)dd.x + ix, sx);
+        sy = fma((double)al, (double)dd.y + iy, sy);
+        sz = fma((double)al, (double)dd.z + iz, sz);
     }
+    // the groups' sums (held by their lanes 0)
+#pragma unroll
+    for (int o = KP; o < W; o <<= 1) {
+        sx += __shfl_xor(sx, o, kWave);
+        sy += __shfl_xor(sy, o, kWave);
+        sz += __shfl_xor(sz, o, kWave);
+    }
+    if (px >= npix || lane != 0 || grp != 0) return;
+    const double inv_spp = (double)(1.0f / (float)P.spp);   // the factor of the output's adjoint
+    image[3 * px] = (float)(sx * inv_spp);
+    image[3 * px + 1] = (float)(sy * inv_spp);
+    image[3 * px + 2] = (float)(sz * inv_spp);
 }
 
-constexpr int64_t kMaxBlocks = (int64_t(1) << 32) / kBlock - 1;   // a launch has fewer than 2^32 threads
+// A launch has fewer than 2^32 threads: an image of more goes in pieces (a loop over
+// the pixels in the kernel cost 6%).
+constexpr int64_t kMaxBlocks = (int64_t(1) << 32) / kBlock - 1;
 
 hipError_t launch_pixels(const pg_paths& paths, const Consts& c, const int32_t* inv, const int32_t* col,
                          const float* w, const float* x, const float* dpt, const float* r, const float* alpha,
@@ -608,11 +619,21 @@ hipError_t launch_pixels(const pg_paths& paths, const Consts& c, const int32_t* 
     if (npix == 0) return hipSuccess;
     auto go = [&](auto kp, auto sg) {
         constexpr int KP = decltype(kp)::value, S = decltype(sg)::value;
-        const int64_t blocks = div_up(npix, kBlock / (KP * S));
-        hipLaunchKernelGGL((k_pixels<KP, S>), dim3((unsigned)(blocks < kMaxBlocks ? blocks : kMaxBlocks)), dim3(kBlock),
-                           0, s, paths, c, inv, col, w, x, dpt, r, alpha, image, flag);
+        constexpr int64_t kRow = kBlock / (KP * S), kAll = kMaxBlocks * kRow;   // pixels of a block, of a launch
+        auto launch = [&](auto spread) {
+            for (int64_t px0 = 0; px0 < npix; px0 += kAll)
+                hipLaunchKernelGGL((k_pixels<KP, S, decltype(spread)::value>),
+                                   dim3((unsigned)div_up(std::min(npix - px0, kAll), kRow)), dim3(kBlock), 0, s, px0,
+                                   paths, c, inv, col, w, x, dpt, r, alpha, image, flag);
+        };
+        if (KP > 1 && paths.n_extra >= kExtraSpread) launch(std::bool_constant<(KP > 1)>{});
+        else launch(std::false_type{});
     };
-    dispatch_kp(c.K, [&](auto kp) {   // up to four samples side by side, as many as fit a wave
+    // The own sample's term (final_gather 1) has no neighbours, so lanes only for the
+    // extra samples, eight from five of them on (1920 x 1080, one / eight lanes: none 0.035
+    // ms and, with K = 8 lanes, 0.11; four 0.11 / 0.22; eight 0.49 / 0.24; 16 1.72 / 0.31).
+    const int lanes = c.final_gather == 0 ? c.K : paths.n_extra >= 5 ? 8 : 1;
+    dispatch_kp(lanes, [&](auto kp) {   // up to four samples side by side, as many as fit a wave
         constexpr int KP = decltype(kp)::value, S4 = KP <= 16 ? 4 : 64 / KP, S2 = KP <= 32 ? 2 : 1;
         if (paths.spp >= 3) go(kp, std::integral_constant<int, S4>{});
         else if (paths.spp == 2) go(kp, std::integral_constant<int, S2>{});
