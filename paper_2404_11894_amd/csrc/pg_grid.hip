@@ -579,6 +579,7 @@ struct KnnSearch {
     float bound;            // not below the worst kept squared distance; inf until the list is full
     int nr, np;             // queued ranges, pending candidates
     int m, sub;             // keys wanted, lane of the query's group
+    uint32_t dense;         // vertices from which a cell is searched before its neighbours are queued
     uint64_t k[KM];
     KnnScratch<SUB>* sc;
 
@@ -691,11 +692,11 @@ struct KnnSearch {
             return d == 0 ? 0.0f : (d < 0 ? l + (float)(-d - 1) * cs : h + (float)(d - 1) * cs);
         };
         // Passes over the cells at Chebyshev distance (rin, rout] from the
-        // query's own: first the 27 around it, then, where the bound is known,
-        // all that it can still reach at once (one shell more where the list is
-        // not full yet).  (iz, iy, ix): the next cells to test, the same for the
-        // whole wave, rows nearest first.  Each turn drains what is queued, then
-        // tests cells until the queue may be full or the pass is through.
+        // query's own: first the 27 around it (where a lane's own cell is populous,
+        // that one alone, and then the 26), after that one shell a pass.  (iz, iy,
+        // ix): the next cells to test, the same for the whole wave, rows nearest
+        // first.  Each turn drains what is queued, then tests cells until the queue
+        // may be full or the pass is through.
         bool live = true;
         int rin = -1, rout = -1, iz = 0, iy = 0, ix = 0;
         int stage = 0;           // 0, 1: the nearer and farther seeds, 2: cells
@@ -714,7 +715,8 @@ struct KnnSearch {
                 } else if (stage == 1) {
                     lo = a2;
                     nwin = e2 - 1 - a2;
-                    rout = 1;
+                    const uint2 own = cells[cell0];
+                    rout = __any(own.y - own.x > dense) ? 0 : 1;
                     pass_end = false;
                 } else {
                     // the nearest unvisited cell on any axis: every unvisited vertex is at least `gap` steps away
@@ -779,13 +781,15 @@ struct KnnSearch {
 
 // SUB: lanes a query, a power of two.
 // WPE: the minimum waves per SIMD the compiler must fit the search in: 6 for
-// lists of up to 16 keys (80 registers, nothing spilled; 7 and 8 spill and are
-// 2% and 13% slower at k = 16, 5 is 4% slower); longer lists take no bound.
+// lists of up to 16 keys (80 registers, three words spilled at 16 keys, nothing
+// below; 7 and 8 spill and are 2% and 13% slower at k = 16, 5 is 4% slower);
+// longer lists take no bound.
 template <int KM, int WPE, int SUB>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) void k_knn(
     int64_t N, int K, int shift, const float4* __restrict__ pts, const int32_t* __restrict__ inv,
     const uint2* __restrict__ cell_range, int32_t* __restrict__ col_sorted, int32_t* __restrict__ col_canon,
-    int64_t* __restrict__ row_ptr, uint32_t* __restrict__ redo, uint32_t* __restrict__ nredo, const KeyFmt f) {
+    int64_t* __restrict__ row_ptr, uint32_t* __restrict__ redo, uint32_t* __restrict__ nredo, const KeyFmt f,
+    uint32_t dense) {
     __shared__ KnnScratch<SUB> scratch;
     const int64_t tile = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t s = (tile * kBlock + threadIdx.x) / SUB;
@@ -799,6 +803,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WPE))) v
     ks.pts = pts;
     ks.cells = cell_range;
     ks.f = f;
+    ks.dense = dense;
     ks.sc = &scratch;
     ks.qx = q.x;
     ks.qy = q.y;
@@ -876,12 +881,20 @@ hipError_t launch_knn(int64_t N, int K, int shift, const float4* pts, const int3
     if (N == 0) return hipSuccess;
     const int m = K - 1;
     const KeyFmt f = key_fmt(N);
-    // below 2^21 vertices a key holds any distance in the cube: no query is redone
+    // up to 2^22 vertices a key holds any distance in the cube: no query is redone
     const bool redone = exact_only || f.sat <= 3ull * kQMax * kQMax;
     if (redone) {
         hipError_t e = launch_fill(nredo, sizeof(uint32_t), s);
         if (e != hipSuccess) return e;
     }
+    // Cells are queued by the bound of the moment, which the seeds leave loose where a
+    // cell holds many vertices: its neighbours were then read to the end although the
+    // cell itself rules them out.  A pass more for it pays where the launch is bound by
+    // its instructions (1M vertices of deviation 0.01: k = 2 0.73 -> 0.19 s, k = 16 0.36
+    // -> 0.27 s; deviation 0.1, k = 16: 3.8 -> 3.4 ms; on a plane 1.6 -> 1.1 ms; even
+    // clouds the same), not where few waves wait for their slowest (3 thousand
+    // vertices of deviation 0.01, k = 18: 0.69 and 1.2 ms).
+    const uint32_t dense = N * K > int64_t(1) << 19 ? 64u : ~0u;
     auto launch = [&](auto km, auto sub) {
         constexpr int KM = decltype(km)::value, SUB = decltype(sub)::value;
         constexpr int WPE = KM <= 16 && SUB == 1 ? 6 : 1;
@@ -889,10 +902,10 @@ hipError_t launch_knn(int64_t N, int K, int shift, const float4* pts, const int3
             hipLaunchKernelGGL(k_redo_all, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, redo, nredo);
         else
             hipLaunchKernelGGL((k_knn<KM, WPE, SUB>), dim3((unsigned)div_up(N * SUB, kBlock)), dim3(kBlock), 0, s, N, K,
-                               shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, redo, nredo, f);
+                               shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, redo, nredo, f, dense);
         if (redone)
-            hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, pts, inv, cell_range, col_sorted, col_canon, row_ptr, (const uint32_t*)redo,
-                           (const uint32_t*)nredo);
+            hipLaunchKernelGGL(k_knn_exact<KM>, dim3(256), dim3(kBlock), 0, s, N, K, shift, pts, inv, cell_range,
+                               col_sorted, col_canon, row_ptr, (const uint32_t*)redo, (const uint32_t*)nredo);
     };
     // The fewer queries, the more lanes to each: a small launch lasts as long as its
     // slowest wave, a large one as long as its instructions, of which groups take
