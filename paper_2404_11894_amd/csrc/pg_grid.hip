@@ -394,7 +394,7 @@ __device__ __forceinline__ void list_reset(uint64_t (&d)[KM], uint32_t (&o)[KM],
 // cell whose box is farther from q than the current (K-1)-th distance cannot
 // contribute and is skipped without reading it (only once the list is full:
 // before that the worst key is (inf, inf)); a cell at exactly that distance is
-// still read, since a tie may win on id.
+// still read, since a tie may win on id.  Candidates are loaded two at a time.
 template <int KM>
 __device__ __forceinline__ void shell_search(int64_t s, int shift, int32_t qx, int32_t qy, int32_t qz,
                                              const float4* __restrict__ pts, const uint2* __restrict__ cell_range,
@@ -402,6 +402,10 @@ __device__ __forceinline__ void shell_search(int64_t s, int shift, int32_t qx, i
     const int G = 1 << (kQBits - shift);
     const int cx = qx >> shift, cy = qy >> shift, cz = qz >> shift;
     const int64_t cs = (int64_t)1 << shift;
+    auto offer = [&](const float4& p) {
+        const int64_t ex = (int32_t)p.x - qx, ey = (int32_t)p.y - qy, ez = (int32_t)p.z - qz;
+        list_insert<KM>(d, o, (uint64_t)(ex * ex + ey * ey + ez * ez), __float_as_uint(p.w));
+    };
     for (int r = 0;; ++r) {
         for (int dz = -r; dz <= r; ++dz) {
             const int z = cz + dz;
@@ -419,11 +423,11 @@ __device__ __forceinline__ void shell_search(int64_t s, int shift, int32_t qx, i
                     const int64_t gx = dx < 0 ? (int64_t)qx - ((int64_t)(x + 1) * cs - 1) : (dx > 0 ? (int64_t)x * cs - qx : 0);
                     if ((uint64_t)(gx * gx + gy * gy + gz * gz) > d[KM - 1]) continue;   // whole cell too far
                     const uint2 cr = cell_range[((uint32_t)z * (uint32_t)G + (uint32_t)y) * (uint32_t)G + (uint32_t)x];
-                    for (uint32_t t = cr.x; t < cr.y; ++t) {
-                        if ((int64_t)t == s) continue;
-                        const float4 p = pts[t];
-                        const int64_t ex = (int32_t)p.x - qx, ey = (int32_t)p.y - qy, ez = (int32_t)p.z - qz;
-                        list_insert<KM>(d, o, (uint64_t)(ex * ex + ey * ey + ez * ez), __float_as_uint(p.w));
+                    for (uint32_t t = cr.x; t < cr.y; t += 2) {
+                        const bool two = t + 1 < cr.y;
+                        const float4 p0 = pts[t], p1 = pts[two ? t + 1 : t];
+                        if ((int64_t)t != s) offer(p0);
+                        if (two && (int64_t)t + 1 != s) offer(p1);
                     }
                 }
             }
