@@ -350,10 +350,12 @@ pg_status pg_edges(const pg_paths* paths, const pg_params* params, const int64_t
  * lplus holds L_0 on entry and L_D on return.  traj, if not NULL, receives
  * L_1..L_D as [D][N][3].  row_ptr / col: the k-nearest layout, checked as in
  * pg_edges.  Where the work pays for it, the size call asks for room to move
- * the graph to the spatially sorted order and iterate there (same results bit
- * for bit); a workspace that only holds the path-order buffers (20 bytes per
- * vertex plus alignment) is accepted for every graph and iterates in path
- * order. */
+ * the graph to an order of its own (the spatial one where neighbours are near in
+ * space and far in path order; same results bit for bit) and iterate there: 70
+ * + 14 k bytes per vertex (294 at k = 16; k rounded up to a multiple of 8), plus the
+ * grid's cells; pos is read then.  A workspace that only holds the path-order
+ * buffers (20 bytes per vertex plus alignment) is accepted for every graph and
+ * iterates in path order. */
 pg_status pg_propagate_workspace_size(const pg_paths* paths, const pg_params* params, size_t* bytes);
 pg_status pg_propagate(const pg_paths* paths, const pg_params* params, const int64_t* row_ptr,
                        const int32_t* col, const float* w_ind, const float* b, float* lplus, float* traj,

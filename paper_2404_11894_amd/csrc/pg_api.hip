@@ -180,20 +180,22 @@ void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift) {
     g.nredo = cv.take<uint32_t>(64);
 }
 
-static hipError_t order_rest(const pg_paths* p, GridBufs& g, hipStream_t s) {
+static hipError_t order_rest(const pg_paths* p, GridBufs& g, hipStream_t s, const int32_t* as_given = nullptr) {
     hipError_t e;
     if ((e = launch_scan_exclusive(g.cells, g.cells, g.ncells, g.partials, s)) != hipSuccess) return e;
-    return launch_scatter(p->n_vertices, *p, g.cellid, g.rank, g.cells, g.perm, g.inv, g.out_qs, g.out_pts, s);
+    return launch_scatter(p->n_vertices, *p, g.cellid, g.rank, g.cells, g.perm, g.inv, g.out_qs, g.out_pts, s,
+                          as_given);
 }
 
-// quantise, count, scan, scatter: perm and inv of the spatial order alone.
-hipError_t run_order(const pg_paths* p, GridBufs& g, hipStream_t s) {
+// quantise, count, scan, scatter: perm and inv of the spatial order alone (the
+// identity where as_given holds other than 0).
+hipError_t run_order(const pg_paths* p, GridBufs& g, const int32_t* as_given, hipStream_t s) {
     hipError_t e;
     if ((e = launch_fill(g.cells, (size_t)(g.ncells + 1) * 4, s)) != hipSuccess) return e;
-    if ((e = launch_quantize_count(p->n_vertices, p->pos, g.shift, g.cells, g.cellid, g.rank, nullptr, s)) !=
+    if ((e = launch_quantize_count(p->n_vertices, p->pos, g.shift, g.cells, g.cellid, g.rank, nullptr, s, as_given)) !=
         hipSuccess)
         return e;
-    return order_rest(p, g, s);
+    return order_rest(p, g, s, as_given);
 }
 
 // The grid with its error flag; with recp also the records packed in path order,
@@ -261,18 +263,24 @@ static void carve_propagate(Carver& cv, PropBufs& b, const pg_paths* p, const pg
     b.c16_ovf = cv.take<int32_t>(E);
 }
 
-// Whether the iterations run in the sorted order.  The move costs about 300 ns a
-// row at K = 16 and an iteration there saves 160 ns a row once L is far larger
-// than the caches (5M vertices: path order 987 us an iteration, sorted 188 us,
-// the move 1.6 ms), less below: both orders took the same time at D = 16 with
-// 270 thousand vertices, D = 7 with 540 thousand and D = 4 with 1.1M, all about
-// kSortedMinWork edge updates (K = 8 and 24 likewise).  Fewer vertices than
-// kSortedMinN stay in the L2 caches in either order.
+// Whether the graph may be moved (to the order that launch_place chooses).  The
+// move to the sorted order costs about 300 ns a row at K = 16 and an iteration there
+// saves 160 ns a row once L is far larger than the caches (5M vertices: path order
+// 987 us an iteration, product and shift there 170 us, the move 1.6 ms), less below:
+// both orders took the same time at D = 16 with 270 thousand vertices, D = 7 with
+// 540 thousand and D = 4 with 1.1M, all about kSortedMinWork edge updates (K = 8 and
+// 24 likewise).  Fewer vertices than kSortedMinN stay in the L2 caches in either
+// order.  What a row costs beside its edges has to be won back too (5M vertices,
+// path order / sorted: k = 2, D = 64 8.2 / 11.8 ms; k = 3, D = 16 3.5 / 4.2, D = 64
+// 13.8 / 12.1; k = 4, D = 8 2.6 / 3.0, D = 16 4.9 / 4.2; k = 8, D = 3 at 3M 1.17 / 1.25).
 constexpr int64_t kSortedMinN = 1 << 18, kSortedMinWork = 1 << 26;
 constexpr int kSortedMinD = 3;
+constexpr int64_t kSortedSlowN = 1 << 19;
+constexpr int kSortedFewEdges = 20;
 static bool propagate_sorted(const pg_paths* p, const pg_params* q) {
     const int64_t N = p->n_vertices;
     if (N < kSortedMinN || q->D < kSortedMinD || q->k > 32) return false;
+    if (N >= kSortedSlowN && (int64_t)q->D * (q->k - 2) < kSortedFewEdges) return false;
     return N * q->D * q->k >= kSortedMinWork && ell_size(N, q->k) < ((int64_t)1 << 32);
 }
 
@@ -292,16 +300,18 @@ static pg_status propagate_in_order(const pg_paths* p, const pg_params* q, PropB
     GridBufs& g = b.g;
     hipError_t e;
     // any positions give an order, so none is reported here
-    if ((e = run_order(p, g, s)) != hipSuccess) return hip_fail(e, "order");
+    int32_t* place = b.flag + 32;   // beside the error flag
+    if ((e = launch_place(N, K, q->D, col, p->pos, place, s)) != hipSuccess) return hip_fail(e, "place");
+    if ((e = run_order(p, g, place, s)) != hipSuccess) return hip_fail(e, "order");
     if ((e = launch_relayout(N, K, g.perm, g.inv, col, w, bc, lplus, alpha, b.succ, b.scol, b.sw, b.sb, b.sx,
-                             b.salpha, b.ssucc, s)) != hipSuccess)
+                             b.salpha, b.ssucc, place, s)) != hipSuccess)
         return hip_fail(e, "relayout");
-    if ((e = launch_c16_build(N, K, b.scol, b.c16, b.c16_cnt, b.c16_base, b.c16_part, b.c16_ovf, s, b.start)) !=
-        hipSuccess)
+    if ((e = launch_c16_build(N, K, b.scol, b.c16, b.c16_cnt, b.c16_base, b.c16_part, b.c16_ovf, s, b.start,
+                              place)) != hipSuccess)
         return hip_fail(e, "compact ids");
     for (int t = 1; t <= q->D; ++t) {
         if ((e = launch_spmv_sorted(N, K, b.c16, b.start, b.c16_base, b.c16_ovf, b.sw, b.sx, b.sb, b.salpha, b.y,
-                                    s)) != hipSuccess)
+                                    col, w, place, s)) != hipSuccess)
             return hip_fail(e, "spmv");
         if ((e = launch_shift(N, b.ssucc, b.y, b.sx, s, 512)) != hipSuccess) return hip_fail(e, "shift");
         if (traj && (e = launch_permute3(N, g.inv, b.sx, traj + (size_t)(t - 1) * N * 3, 1, s)) != hipSuccess)
@@ -322,8 +332,10 @@ pg_status propagate_run(const pg_paths* paths, const pg_params* params, const in
         return fail(PG_ERR_ARG, "row_ptr, col, w_ind, b and lplus are required");
     if ((st = check_ws(ws, ws_bytes, propagate_size(paths, params)))) return st;
     const int K = (int)(N < params->k ? N : params->k);
-    // a workspace that holds only the path-order iteration's buffers gets that
-    const bool sorted = propagate_sorted(paths, params) && ws_bytes >= propagate_bytes(paths, params, true);
+    // A workspace that holds only the path-order iteration's buffers gets that, and so
+    // do one or two neighbours (300 thousand vertices, k = 2, D = 128: 1.1 and 1.8 ms moved).
+    const bool sorted =
+        propagate_sorted(paths, params) && params->k > 2 && ws_bytes >= propagate_bytes(paths, params, true);
     Carver cv(ws);
     PropBufs pb;
     carve_propagate(cv, pb, paths, params, sorted);

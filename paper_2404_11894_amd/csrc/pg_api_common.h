@@ -93,7 +93,7 @@ struct GridBufs {
 };
 
 void carve_order(Carver& cv, GridBufs& g, int64_t N, int shift);
-hipError_t run_order(const pg_paths* p, GridBufs& g, hipStream_t s);
+hipError_t run_order(const pg_paths* p, GridBufs& g, const int32_t* as_given, hipStream_t s);
 void carve_grid(Carver& cv, GridBufs& g, int64_t N, int shift);
 // What the grid is built for: the neighbour search (points and cell ranges) or
 // the cluster relation (packed positions).

@@ -39,17 +39,18 @@ __device__ __forceinline__ void count_vertex(int64_t i, float x, float y, float 
 __global__ __launch_bounds__(kBlock) void k_quantize_count(int64_t N, const float* __restrict__ pos, int shift,
                                                            uint32_t* __restrict__ count,
                                                            uint32_t* __restrict__ cellid,
-                                                           uint32_t* __restrict__ rank, int32_t* flag) {
+                                                           uint32_t* __restrict__ rank, int32_t* flag,
+                                                           const int32_t* __restrict__ as_given) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
+    if (i >= N || (as_given && *as_given != 0)) return;
     count_vertex(i, pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], shift, count, cellid, rank, flag);
 }
 
 hipError_t launch_quantize_count(int64_t N, const float* pos, int shift, uint32_t* count, uint32_t* cellid,
-                                 uint32_t* rank, int32_t* flag, hipStream_t s) {
+                                 uint32_t* rank, int32_t* flag, hipStream_t s, const int32_t* as_given) {
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_quantize_count, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, pos, shift,
-                       count, cellid, rank, flag);
+                       count, cellid, rank, flag, as_given);
     return hipGetLastError();
 }
 
@@ -250,10 +251,12 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P,
                                                     const uint32_t* __restrict__ rank,
                                                     const uint32_t* __restrict__ cell_start,
                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv,
-                                                    uint64_t* __restrict__ qsorted, float4* __restrict__ pts) {
+                                                    uint64_t* __restrict__ qsorted, float4* __restrict__ pts,
+                                                    const int32_t* __restrict__ as_given) {
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= N) return;
-    int64_t s = (int64_t)cell_start[cellid[v]] + rank[v];
+    const bool given = as_given && *as_given != 0;
+    int64_t s = given ? v : (int64_t)cell_start[cellid[v]] + rank[v];
     perm[s] = (int32_t)v;
     inv[v] = (int32_t)s;
     if (!qsorted && !pts) return;
@@ -264,10 +267,10 @@ __global__ __launch_bounds__(kBlock) void k_scatter(int64_t N, pg_paths P,
 
 hipError_t launch_scatter(int64_t N, const pg_paths& paths, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
-                          uint64_t* qsorted, float4* pts, hipStream_t s) {
+                          uint64_t* qsorted, float4* pts, hipStream_t s, const int32_t* as_given) {
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_scatter, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, paths, cellid,
-                       rank, cell_start, perm, inv, qsorted, pts);
+                       rank, cell_start, perm, inv, qsorted, pts, as_given);
     return hipGetLastError();
 }
 

@@ -567,8 +567,10 @@ struct Consts {
 // Each returns hipSuccess or the launch error.  All take the stream last.
 
 // grid build: quantise + histogram, exclusive scan, scatter into cell order
+// (as_given, nullable: where it holds other than 0 nothing is counted, and the
+// scatter makes the identity of perm and inv)
 hipError_t launch_quantize_count(int64_t N, const float* pos, int shift, uint32_t* count, uint32_t* cellid,
-                                 uint32_t* rank, int32_t* flag, hipStream_t s);
+                                 uint32_t* rank, int32_t* flag, hipStream_t s, const int32_t* as_given = nullptr);
 hipError_t launch_count_pack(int64_t N, const pg_paths& paths, int shift, uint32_t* count, uint32_t* cellid,
                              uint32_t* rank, VRec* rec, int32_t* flag, hipStream_t s);
 size_t scan_partials_bytes(int64_t n);
@@ -576,7 +578,7 @@ hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, int64_t n, u
                                  hipStream_t s);
 hipError_t launch_scatter(int64_t N, const pg_paths& paths, const uint32_t* cellid,
                           const uint32_t* rank, const uint32_t* cell_start, int32_t* perm, int32_t* inv,
-                          uint64_t* qsorted, float4* pts, hipStream_t s);
+                          uint64_t* qsorted, float4* pts, hipStream_t s, const int32_t* as_given = nullptr);
 // redo: [N] scratch list, nredo: one counter (queries the fast 64-bit-key
 // search hands to the exact one)
 hipError_t launch_cell_range(int64_t ncells, int shift, const uint32_t* start, uint2* range, hipStream_t s);
@@ -667,15 +669,20 @@ hipError_t launch_check_rows(int64_t N, int K, const int64_t* row_ptr, int32_t* 
 // start (nullable, [N]): slot 0 is kept as an id and the rows' list starts go
 // there (c16_row_ids<KT, true>)
 hipError_t launch_c16_build(int64_t N, int K, const int32_t* col, int16_t* c16, uint32_t* cnt, uint32_t* c16_base,
-                            uint32_t* partials, int32_t* ovf, hipStream_t s, uint16_t* start = nullptr);
-// a caller's path-order graph moved to the sorted order and iterated there
+                            uint32_t* partials, int32_t* ovf, hipStream_t s, uint16_t* start = nullptr,
+                            const int32_t* place = nullptr);
+// a caller's path-order graph moved to the order that launch_place chooses and
+// iterated there
+enum Place : int32_t { kPlaceSorted = 0, kPlacePaths = 1, kPlaceRows = 2 };
+hipError_t launch_place(int64_t N, int K, int D, const int32_t* col, const float* pos, int32_t* place, hipStream_t s);
 hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t* inv, const int32_t* col,
                            const float* w, const float* b, const float* x0, const float* alpha,
                            const int32_t* succ, int32_t* scol, float* sw, float* sb, float* sx, float* salpha,
-                           int32_t* ssucc, hipStream_t s);
+                           int32_t* ssucc, const int32_t* place, hipStream_t s);
 hipError_t launch_spmv_sorted(int64_t N, int K, const int16_t* c16, const uint16_t* start, const uint32_t* c16_base,
                               const int32_t* ovf, const float* w, const float* x, const float* b, const float* alpha,
-                              float* y, hipStream_t s);
+                              float* y, const int32_t* col_rows, const float* w_rows, const int32_t* place,
+                              hipStream_t s);
 hipError_t launch_spmv_c16(int64_t N, int K, const int16_t* c16, const uint32_t* c16_base, const int32_t* ovf,
                            const int32_t* col, const float* w, const float* x, const float* b, const float* alpha,
                            float* y, hipStream_t s, int tile = 0, int tile_group = 0);

@@ -17,6 +17,7 @@
 //    computes L directly.
 // Both are sparse gathers bound by HBM bandwidth (about 0.5 flop per byte).
 #include <algorithm>
+#include <cmath>
 
 #include "pg_internal.h"
 
@@ -147,7 +148,9 @@ hipError_t launch_spmv_scatter(int64_t N, int K, const int32_t* col, const float
 // offset 0 in every slot.
 __global__ __launch_bounds__(kBlock) void k_c16_build(int64_t N, int K, const int32_t* __restrict__ col,
                                                       int16_t* __restrict__ c16, uint32_t* __restrict__ cnt,
-                                                      uint16_t* __restrict__ row_start) {
+                                                      uint16_t* __restrict__ row_start,
+                                                      const int32_t* __restrict__ place) {
+    if (place && *place == kPlaceRows) return;   // there is no sliced ELL
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t nsl = div_up(N, kSlice);
@@ -196,7 +199,9 @@ __global__ __launch_bounds__(kBlock) void k_c16_escapes(int64_t N, int K, const 
                                                         const int16_t* __restrict__ c16,
                                                         const uint32_t* __restrict__ c16_base,
                                                         const uint16_t* __restrict__ row_start,
-                                                        int32_t* __restrict__ ovf) {
+                                                        int32_t* __restrict__ ovf,
+                                                        const int32_t* __restrict__ place) {
+    if (place && *place == kPlaceRows) return;
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= N) return;
     int64_t p = (int64_t)c16_base[i >> 6] + (row_start ? row_start[i] : (uint16_t)c16[c16_row(i, K)]);
@@ -209,15 +214,16 @@ __global__ __launch_bounds__(kBlock) void k_c16_escapes(int64_t N, int K, const 
 }
 
 hipError_t launch_c16_build(int64_t N, int K, const int32_t* col, int16_t* c16, uint32_t* cnt, uint32_t* c16_base,
-                            uint32_t* partials, int32_t* ovf, hipStream_t s, uint16_t* start) {
+                            uint32_t* partials, int32_t* ovf, hipStream_t s, uint16_t* start,
+                            const int32_t* place) {
     if (N == 0) return hipSuccess;
     const int64_t nsl = div_up(N, kSlice);
     hipLaunchKernelGGL(k_c16_build, dim3((unsigned)div_up(nsl * kSlice, kBlock)), dim3(kBlock), 0, s, N, K, col,
-                       c16, cnt, start);
+                       c16, cnt, start, place);
     hipError_t e = launch_scan_exclusive(cnt, c16_base, nsl, partials, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_c16_escapes, dim3((unsigned)div_up(N, kBlock)), dim3(kBlock), 0, s, N, K, col, c16,
-                       c16_base, (const uint16_t*)start, ovf);
+                       c16_base, (const uint16_t*)start, ovf, place);
     return hipGetLastError();
 }
 
@@ -277,8 +283,72 @@ hipError_t launch_check_rows(int64_t N, int K, const int64_t* row_ptr, int32_t* 
 // pg_propagate takes rows and ids in path order, where neighbours lie anywhere
 // in memory: every gathered x costs a cache line of its own (5M vertices, K =
 // 16: 970 us an iteration, 1.1 TB/s of the bytes it needs).  Moved once to the
-// spatially sorted order, the iteration runs as the render's does (145 us).
+// spatially sorted order, the iteration runs as the render's does (product 141 us,
+// shift 25 us).
 //
+// Where a graph's ids are near each other in path order already, that is as fast
+// there (the identity in place of the permutation); where they are far in space
+// too, no order helps, and from kPlaceRowsMinN vertices on the caller's own rows are
+// read (below, the test in each iteration costs more than it saves).  Which it is, a
+// sample says: the share of edges farther than a compact id reaches, in path order,
+// and that of edges longer than half the radius of the vertices that an XCD works on
+// at a time (65536; in space).  5M vertices, K = 16, D = 64, in path order / always
+// sorted / so: neighbours 92 / 16.8 / 16.9 ms, ids within 40 rows 26 / 99 / 9.8, ids at
+// random 92 / 106 / 94; D = 3: 4.3 / 2.6 / 2.6, 1.26 / 6.9 / 1.20, 4.5 / 8.4 / 4.7.  At 1M,
+// D = 64, ids at random: 13.6 / 15.8 / 15.3.
+constexpr int kPlaceSamples = 128, kPlaceLanes = 8, kPlaceMaxK = 32;
+constexpr int64_t kPlaceRowsMinN = 1 << 21;
+__global__ __launch_bounds__(kPlaceSamples* kPlaceLanes) void k_place(int64_t N, int K, int D,
+                                                                      const int32_t* __restrict__ col,
+                                                                      const float* __restrict__ pos, float reach,
+                                                                      bool rows, int32_t* __restrict__ place) {
+    constexpr int M = kPlaceMaxK / kPlaceLanes;
+    __shared__ int edges, far_path, far_space;
+    if (threadIdx.x == 0) edges = far_path = far_space = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)(threadIdx.x / kPlaceLanes) * N / kPlaceSamples;
+    const f3 p = ld3(pos, i);
+    int32_t j[M];   // all ids in flight, then all positions: two waits for memory
+    f3 q[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int l = threadIdx.x % kPlaceLanes + m * kPlaceLanes;
+        j[m] = l < K ? col[i * K + l] : -1;
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) q[m] = ld3(pos, (uint32_t)j[m] < (uint32_t)N ? j[m] : i);
+    int n = 0, fp = 0, fs = 0;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const bool ok = (uint32_t)j[m] < (uint32_t)N;
+        n += ok;
+        fp += ok && (j[m] - i < -32767 || j[m] - i > 32767);
+        fs += !(fabsf(q[m].x - p.x) <= reach && fabsf(q[m].y - p.y) <= reach && fabsf(q[m].z - p.z) <= reach);
+    }
+    for (int o = kWave / 2; o > 0; o >>= 1) {
+        n += __shfl_xor(n, o, kWave);
+        fp += __shfl_xor(fp, o, kWave);
+        fs += __shfl_xor(fs, o, kWave);
+    }
+    if (threadIdx.x % kWave == 0) {
+        atomicAdd(&edges, n);
+        atomicAdd(&far_path, fp);
+        atomicAdd(&far_space, fs);
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    // moving an edge costs about what two iterations save where it is brought near
+    const bool sorted = (int64_t)(far_path - far_space) * D >= 2 * edges;
+    *place = sorted ? kPlaceSorted : (rows && 2 * far_path >= edges ? kPlaceRows : kPlacePaths);
+}
+
+hipError_t launch_place(int64_t N, int K, int D, const int32_t* col, const float* pos, int32_t* place, hipStream_t s) {
+    const float reach = 0.25f * cbrtf(65536.0f / (float)N);
+    hipLaunchKernelGGL(k_place, dim3(1), dim3(kPlaceSamples * kPlaceLanes), 0, s, N, K, D, col, pos, reach,
+                       N >= kPlaceRowsMinN, place);
+    return hipGetLastError();
+}
+
 // Row s of the sliced ELL = row perm[s] of the caller's, ids through inv, with
 // b, L_0, albedo and successors beside it.  Ids from callers are not trusted:
 // one out of range points at row N, which holds 0, with weight 0 (x has N + 1
@@ -291,7 +361,7 @@ __global__ __launch_bounds__(kBlock) void k_relayout(int64_t N, int K, const int
                                                      const int32_t* __restrict__ succ, int32_t* __restrict__ scol,
                                                      float* __restrict__ sw, float* __restrict__ sb,
                                                      float* __restrict__ sx, float* __restrict__ salpha,
-                                                     int32_t* __restrict__ ssucc) {
+                                                     int32_t* __restrict__ ssucc, const int32_t* __restrict__ place) {
     const int nq = ell_k4(K) / 4;
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (t == 0) st3(sx, N, f3{0.f, 0.f, 0.f});
@@ -300,23 +370,25 @@ __global__ __launch_bounds__(kBlock) void k_relayout(int64_t N, int K, const int
     const int q = (int)(t - s * nq);
     const int64_t v = perm[s];
     const int64_t row = v * (int64_t)K;
-    int32_t j[4];
-    float ww[4];
+    if (*place != kPlaceRows) {
+        int32_t j[4];
+        float ww[4];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int l = 4 * q + c;
-        j[c] = l < K ? col[row + l] : -1;
-        ww[c] = l < K ? w[row + l] : 0.0f;
-    }
+        for (int c = 0; c < 4; ++c) {
+            const int l = 4 * q + c;
+            j[c] = l < K ? col[row + l] : -1;
+            ww[c] = l < K ? w[row + l] : 0.0f;
+        }
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const bool ok = (uint32_t)j[c] < (uint32_t)N;
-        j[c] = ok ? inv[j[c]] : (4 * q + c < K ? (int32_t)N : (int32_t)s);
-        ww[c] = ok ? ww[c] : 0.0f;
+        for (int c = 0; c < 4; ++c) {
+            const bool ok = (uint32_t)j[c] < (uint32_t)N;
+            j[c] = ok ? inv[j[c]] : (4 * q + c < K ? (int32_t)N : (int32_t)s);
+            ww[c] = ok ? ww[c] : 0.0f;
+        }
+        const int64_t e = ell_row(s, K) + q * kQuadStride;
+        *reinterpret_cast<i32x4*>(scol + e) = i32x4{j[0], j[1], j[2], j[3]};
+        *reinterpret_cast<f32x4*>(sw + e) = f32x4{ww[0], ww[1], ww[2], ww[3]};
     }
-    const int64_t e = ell_row(s, K) + q * kQuadStride;
-    *reinterpret_cast<i32x4*>(scol + e) = i32x4{j[0], j[1], j[2], j[3]};
-    *reinterpret_cast<f32x4*>(sw + e) = f32x4{ww[0], ww[1], ww[2], ww[3]};
     if (q != 0) return;
     st3(sb, s, ld3(b, v));
     st3(sx, s, ld3(x0, v));
@@ -328,11 +400,50 @@ __global__ __launch_bounds__(kBlock) void k_relayout(int64_t N, int K, const int
 hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t* inv, const int32_t* col,
                            const float* w, const float* b, const float* x0, const float* alpha,
                            const int32_t* succ, int32_t* scol, float* sw, float* sb, float* sx, float* salpha,
-                           int32_t* ssucc, hipStream_t s) {
+                           int32_t* ssucc, const int32_t* place, hipStream_t s) {
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_relayout, dim3((unsigned)div_up(N * (ell_k4(K) / 4), kBlock)), dim3(kBlock), 0, s, N, K, perm,
-                       inv, col, w, b, x0, alpha, succ, scol, sw, sb, sx, salpha, ssucc);
+                       inv, col, w, b, x0, alpha, succ, scol, sw, sb, sx, salpha, ssucc, place);
     return hipGetLastError();
+}
+
+// The rows of a block as k_spmv takes them, a group of KP lanes each, over the
+// caller's arrays.
+template <int KP, int BS>
+__device__ __forceinline__ void spmv_rows(int64_t N, int K, const int32_t* __restrict__ col,
+                                          const float* __restrict__ w, const float* __restrict__ x,
+                                          const float* __restrict__ b, const float* __restrict__ alpha,
+                                          float* __restrict__ y) {
+#pragma clang fp contract(off)
+    constexpr int GR = BS / KP, U = KP < 4 ? KP : 4;   // U rows of a group in flight
+    const int lane = threadIdx.x % KP;
+    const int64_t first = (int64_t)blockIdx.x * BS + threadIdx.x / KP;
+    for (int r = 0; r < KP; r += U) {
+        f3 a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = first + (r + u) * GR;
+            a[u] = f3{0.f, 0.f, 0.f};
+            if (i < N && lane < K) {
+                const int64_t e = i * K + lane;
+                const int64_t j = col[e];
+                const float ww = w[e];
+                if (j >= 0 && j < N) {
+                    const f3 xv = ld3(x, j);
+                    a[u] = f3{ww * xv.x, ww * xv.y, ww * xv.z};
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = first + (r + u) * GR;
+            const f3 z{group_sum<KP>(a[u].x), group_sum<KP>(a[u].y), group_sum<KP>(a[u].z)};
+            if (i >= N || lane != 0) continue;
+            const f3 bb = ld3(b, i);
+            const float al = alpha[i];
+            st3(y, i, f3{fmaf(al, z.x, bb.x), fmaf(al, z.y, bb.y), fmaf(al, z.z, bb.z)});
+        }
+    }
 }
 
 // One thread per row over the compact ids, every product rounded and the K
@@ -341,17 +452,24 @@ hipError_t launch_relayout(int64_t N, int K, const int32_t* perm, const int32_t*
 // give the same results bit for bit.  Left to itself the compiler interleaves
 // gathers and products (73 registers at K = 16, 210 us on 5M vertices); with all
 // gathers issued first (86 registers) it takes 141 us.
-template <int KT, int BS, bool NT>
+template <int KT, int BS, bool NT, bool ROWS>
 __global__ __launch_bounds__(BS) void k_spmv_sorted(int64_t N, int K, const int16_t* __restrict__ c16,
                                                     const uint16_t* __restrict__ start,
                                                     const uint32_t* __restrict__ c16_base,
                                                     const int32_t* __restrict__ ovf, const float* __restrict__ w,
                                                     const float* __restrict__ x, const float* __restrict__ b,
-                                                    const float* __restrict__ alpha, float* __restrict__ y) {
+                                                    const float* __restrict__ alpha, float* __restrict__ y,
+                                                    const int32_t* __restrict__ col_rows,
+                                                    const float* __restrict__ w_rows,
+                                                    const int32_t* __restrict__ place) {
 #pragma clang fp contract(off)
+    constexpr int NQ = KT / 4, KP = KT <= 4 ? 4 : (KT <= 8 ? 8 : (KT <= 16 ? 16 : 32));
+    if (ROWS && *place == kPlaceRows) {
+        spmv_rows<KP, BS>(N, K, col_rows, w_rows, x, b, alpha, y);
+        return;
+    }
     const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
     if (i >= N) return;
-    constexpr int NQ = KT / 4, KP = KT <= 4 ? 4 : (KT <= 8 ? 8 : (KT <= 16 ? 16 : 32));
     const int64_t base = ell_row(i, K);
     f32x4 ww[NQ];
 #pragma unroll
@@ -378,15 +496,21 @@ __global__ __launch_bounds__(BS) void k_spmv_sorted(int64_t N, int K, const int1
 
 hipError_t launch_spmv_sorted(int64_t N, int K, const int16_t* c16, const uint16_t* start, const uint32_t* c16_base,
                               const int32_t* ovf, const float* w, const float* x, const float* b, const float* alpha,
-                              float* y, hipStream_t s) {
+                              float* y, const int32_t* col_rows, const float* w_rows, const int32_t* place,
+                              hipStream_t s) {
     if (N == 0) return hipSuccess;
     constexpr int BS = 512;   // as the render's aggregation over the compact ids
     dispatch_k4(K, [&](auto kt) {
         constexpr int KT = decltype(kt)::value;
         if constexpr (KT > 0)
             dispatch_nt(N, [&](auto nt) {
-                hipLaunchKernelGGL((k_spmv_sorted<KT, BS, decltype(nt)::value>), dim3((unsigned)div_up(N, BS)),
-                                   dim3(BS), 0, s, N, K, c16, start, c16_base, ovf, w, x, b, alpha, y);
+                auto go = [&](auto rows) {
+                    hipLaunchKernelGGL((k_spmv_sorted<KT, BS, decltype(nt)::value, decltype(rows)::value>),
+                                       dim3((unsigned)div_up(N, BS)), dim3(BS), 0, s, N, K, c16, start, c16_base, ovf,
+                                       w, x, b, alpha, y, col_rows, w_rows, place);
+                };
+                if (N >= kPlaceRowsMinN) go(std::true_type{});
+                else go(std::false_type{});
             });
     });
     return hipGetLastError();
