@@ -190,9 +190,12 @@ __device__ inline void st3_nt(float* p, int64_t i, f3 v) {
 //   500 thousand  2.467 / 2.481          700 thousand  3.10 / 3.06
 //   1M  4.08 / 3.90   2.5M  9.80 / 9.40   5M  17.5 / 16.8
 //   8.5M  31.1 / 31.1                    20M  71.4 / 73.0
+// K = 4 to 32, taped, and the reverse sweep's vectors agree within 2%, but for those
+// that just fit the L2 (170 thousand rows: kept 2 to 3% slower, the reverse rows over
+// stored sums 8%), so the line lies at 3 MB.
 inline bool iter_past_caches(int64_t n) {
     const int64_t bytes = n * 24;
-    return bytes > (int64_t(200) << 20) || (bytes > (int64_t(4) << 20) && bytes <= (int64_t(12) << 20));
+    return bytes > (int64_t(200) << 20) || (bytes > (int64_t(3) << 20) && bytes <= (int64_t(12) << 20));
 }
 // The choice is a template parameter NT of the kernels: of two stores in one
 // kernel that differ in nothing but the hint the compiler makes one without it.
