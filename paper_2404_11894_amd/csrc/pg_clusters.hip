@@ -761,13 +761,16 @@ __device__ __forceinline__ void stage_span(const Span& sp, int64_t i0, int64_t N
                                            const float4* __restrict__ aq, const float* __restrict__ xq,
                                            const int32_t* __restrict__ succ, float4* sa, float* sx) {
     const uint32_t rows = (uint32_t)(N - i0 < kBlock ? N - i0 : kBlock), first = (uint32_t)i0 - sp.lo;
-    // one turn, but for the last block, which has fewer rows and so up to kSpan - 1 others
-    for (uint32_t u = threadIdx.x; u < sp.n - rows; u += kBlock) {
+    auto turn = [&](uint32_t u) {
+        if (u >= sp.n - rows) return;
         const uint32_t t = u < first ? u : u + rows;
         Stage<SHIFTED, NT> margin;
         margin.load((int64_t)sp.lo + t, aq, xq, succ);
         margin.store(t, sa, sx);
-    }
+    };
+    turn(threadIdx.x);
+    if (rows < kBlock) turn(threadIdx.x + kBlock);   // the last block: up to kSpan - 1 members outside its rows
+    static_assert(kSpan <= 2 * kBlock, "two turns");
     if (threadIdx.x < rows) own.store(first + threadIdx.x, sa, sx);
 }
 
