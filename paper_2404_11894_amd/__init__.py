@@ -405,7 +405,9 @@ def pg_edges(paths: DevicePaths, q: Params, row_ptr, col):
 
 def pg_propagate(paths: DevicePaths, q: Params, row_ptr, col, w_ind, b, lplus, traj: bool = False):
     """D iterations of aggregation + propagation.  lplus (L_0, [N,3]) is
-    updated in place to L_D; with traj also returns L_1..L_D [D,N,3]."""
+    updated in place to L_D; with traj also returns L_1..L_D [D,N,3].  The
+    workspace is allocated for the call: 20 bytes a vertex, or about 300 (k = 16)
+    where the graph is moved to an order of its own."""
     torch = _torch()
     L, s = lib(), paths.struct()
     nb = ctypes.c_size_t()

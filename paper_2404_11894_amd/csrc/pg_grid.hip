@@ -551,10 +551,11 @@ struct KnnScratch {
     uint32_t pend[kKnnPend][kBlock];
 };
 
-// The search is bound by the instructions a wave issues (the VALU was busy 94%
-// of the time when every lane searched by itself, 32 thousand instructions a
-// wave on a dense cloud of 69M vertices), and what a wave issues is the union of
-// what its 64 lanes do.  So the lanes stay together wherever the work is heavy:
+// The search is bound by the instructions a wave issues (32 thousand a wave with
+// 29% of the lanes active when every lane searched by itself, a dense cloud of 69M
+// vertices; now 17 thousand with 90%, a fifth of a wave's cycles waiting for memory),
+// and what a wave issues is the union of what its 64 lanes do.  So the lanes stay
+// together wherever the work is heavy:
 //  * cells are tested at offsets the whole wave shares, in single precision
 //    (gap and table index a few operations each), and only queued;
 //  * the queued ranges are then read as one flat loop per lane, so a wave
